@@ -57,7 +57,7 @@ struct MvResolve {
 
 // Depth passes of views[0 .. nv) over one chunk: the points are loaded
 // once and stay in registers while each view is rasterized in turn.
-template <int PPT, bool VEC, bool XCD, int BIN, bool PW>
+template <int PPT, bool XCD, int BIN, bool PW>
 __global__ void __launch_bounds__(512) k_mv_raster_min(Pts p, const MvView *__restrict__ views,
                                                        int32_t nv, int64_t nchunks,
                                                        uint32_t words)
@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(512) k_mv_raster_min(Pts p, const MvView *__re
     uint32_t c[PPT];
     bool in[PPT];
     // points past the end load as NaN and are culled: no bounds flags
-    load_points_nan<PPT, VEC>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
+    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(512) k_mv_raster_min(Pts p, const MvView *__re
 }
 
 // Accumulate passes of the splatting views views[0 .. nv) over one chunk.
-template <int PPT, bool VEC, bool XCD, int BIN, bool PW>
+template <int PPT, bool XCD, int BIN, bool PW>
 __global__ void __launch_bounds__(512) k_mv_hq_accum(Pts p, const MvView *__restrict__ views,
                                                      int32_t nv, int64_t nchunks,
                                                      uint32_t words)
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(512) k_mv_hq_accum(Pts p, const MvView *__rest
     uint32_t c[PPT];
     bool in[PPT];
     // points past the end load as NaN and are culled: no bounds flags
-    load_points_nan<PPT, VEC>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
+    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(256) k_mv_checksum(const MvResolve *__restrict
         atomicAdd(out, h);
 }
 
-template <int PPT, bool VEC, bool XCD, int BIN>
+template <int PPT, bool XCD, int BIN>
 hipError_t mv_launch_ppt(bool hq, bool pw, const Pts &p, const MvView *views, int32_t nv,
                          const Tune &t, hipStream_t s)
 {
@@ -194,41 +194,39 @@ hipError_t mv_launch_ppt(bool hq, bool pw, const Pts &p, const MvView *views, in
     const size_t lds =
         BIN == kBinWave ? (size_t)(t.block / 64) * words * sizeof(uint64_t) : 0;
     if (hq && pw)
-        hipLaunchKernelGGL((k_mv_hq_accum<PPT, VEC, XCD, BIN, true>), dim3((uint32_t)grid),
+        hipLaunchKernelGGL((k_mv_hq_accum<PPT, XCD, BIN, true>), dim3((uint32_t)grid),
                            dim3(t.block), lds, s, p, views, nv, nchunks, words);
     else if (hq)
-        hipLaunchKernelGGL((k_mv_hq_accum<PPT, VEC, XCD, BIN, false>), dim3((uint32_t)grid),
+        hipLaunchKernelGGL((k_mv_hq_accum<PPT, XCD, BIN, false>), dim3((uint32_t)grid),
                            dim3(t.block), lds, s, p, views, nv, nchunks, words);
     else if (pw)
-        hipLaunchKernelGGL((k_mv_raster_min<PPT, VEC, XCD, BIN, true>), dim3((uint32_t)grid),
+        hipLaunchKernelGGL((k_mv_raster_min<PPT, XCD, BIN, true>), dim3((uint32_t)grid),
                            dim3(t.block), lds, s, p, views, nv, nchunks, words);
     else
-        hipLaunchKernelGGL((k_mv_raster_min<PPT, VEC, XCD, BIN, false>), dim3((uint32_t)grid),
+        hipLaunchKernelGGL((k_mv_raster_min<PPT, XCD, BIN, false>), dim3((uint32_t)grid),
                            dim3(t.block), lds, s, p, views, nv, nchunks, words);
     return hipGetLastError();
 }
 
-template <int PPT, bool VEC, bool XCD>
+template <int PPT, bool XCD>
 hipError_t mv_launch_bin(bool hq, bool pw, const Pts &p, const MvView *views, int32_t nv,
                          const Tune &t, hipStream_t s)
 {
     switch (t.bin) {
-    case kBinBlock: return mv_launch_ppt<PPT, VEC, XCD, kBinBlock>(hq, pw, p, views, nv, t, s);
+    case kBinBlock: return mv_launch_ppt<PPT, XCD, kBinBlock>(hq, pw, p, views, nv, t, s);
     case kBinWave:
     case kBinWaveSmall:
-        return mv_launch_ppt<PPT, VEC, XCD, kBinWave>(hq, pw, p, views, nv, t, s);
-    default: return mv_launch_ppt<PPT, VEC, XCD, kBinNone>(hq, pw, p, views, nv, t, s);
+        return mv_launch_ppt<PPT, XCD, kBinWave>(hq, pw, p, views, nv, t, s);
+    default: return mv_launch_ppt<PPT, XCD, kBinNone>(hq, pw, p, views, nv, t, s);
     }
 }
 
 template <int PPT>
 hipError_t mv_launch_sel(bool hq, bool pw, const Pts &p, const MvView *views, int32_t nv,
-                         const Tune &t, bool vec, hipStream_t s)
+                         const Tune &t, hipStream_t s)
 {
-    if (vec)
-        return t.xcd_remap ? mv_launch_bin<PPT, true, true>(hq, pw, p, views, nv, t, s)
-                           : mv_launch_bin<PPT, true, false>(hq, pw, p, views, nv, t, s);
-    return mv_launch_bin<PPT, false, false>(hq, pw, p, views, nv, t, s);
+    return t.xcd_remap ? mv_launch_bin<PPT, true>(hq, pw, p, views, nv, t, s)
+                       : mv_launch_bin<PPT, false>(hq, pw, p, views, nv, t, s);
 }
 
 hipError_t mv_launch(bool hq, bool pw, const Pts &p, const MvView *views, int32_t nv,
@@ -236,12 +234,10 @@ hipError_t mv_launch(bool hq, bool pw, const Pts &p, const MvView *views, int32_
 {
     if (p.n == 0 || nv == 0)
         return hipSuccess;
-    const bool vec = (((uintptr_t)p.x | (uintptr_t)p.y | (uintptr_t)p.z | (uintptr_t)p.rgb) &
-                      15u) == 0;
     switch (t.ppt) {
-    case 4: return mv_launch_sel<4>(hq, pw, p, views, nv, t, vec, s);
-    case 8: return mv_launch_sel<8>(hq, pw, p, views, nv, t, vec, s);
-    case 16: return mv_launch_sel<16>(hq, pw, p, views, nv, t, vec, s);
+    case 4: return mv_launch_sel<4>(hq, pw, p, views, nv, t, s);
+    case 8: return mv_launch_sel<8>(hq, pw, p, views, nv, t, s);
+    case 16: return mv_launch_sel<16>(hq, pw, p, views, nv, t, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -72,7 +72,6 @@ __device__ __forceinline__ Cover wave_cover(const Box &box, int32_t k, int32_t w
     return c;
 }
 
-template <bool VEC>
 __global__ void __launch_bounds__(kGenBlock) k_raster_points(Pts p, Proj P, int32_t k,
                                                              uint64_t *__restrict__ fb)
 {
@@ -82,7 +81,7 @@ __global__ void __launch_bounds__(kGenBlock) k_raster_points(Pts p, Proj P, int3
     float x[kGenPpt], y[kGenPpt], z[kGenPpt];
     uint32_t c[kGenPpt];
     bool in[kGenPpt];
-    load_points<kGenPpt, VEC>(p, base, x, y, z, c, in);
+    load_points<kGenPpt>(p, base, x, y, z, c, in);
     uint32_t px[kGenPpt], py[kGenPpt];
     uint64_t key[kGenPpt];
     bool live[kGenPpt];
@@ -163,7 +162,7 @@ __global__ void __launch_bounds__(kGenBlock) k_raster_points(Pts p, Proj P, int3
     }
 }
 
-template <bool VEC, bool PW>
+template <bool PW>
 __global__ void __launch_bounds__(kGenBlock) k_hq_points(Pts p, Proj P, int32_t k,
                                                          uint32_t eps_num, uint32_t eps_den,
                                                          const uint64_t *__restrict__ fb,
@@ -176,7 +175,7 @@ __global__ void __launch_bounds__(kGenBlock) k_hq_points(Pts p, Proj P, int32_t 
     float x[kGenPpt], y[kGenPpt], z[kGenPpt];
     uint32_t c[kGenPpt];
     bool in[kGenPpt];
-    load_points<kGenPpt, VEC>(p, base, x, y, z, c, in);
+    load_points<kGenPpt>(p, base, x, y, z, c, in);
     uint32_t px[kGenPpt], py[kGenPpt];
     uint64_t q[kGenPpt];
     bool live[kGenPpt];
@@ -268,11 +267,6 @@ __global__ void __launch_bounds__(kGenBlock) k_hq_points(Pts p, Proj P, int32_t 
     }
 }
 
-bool aligned16(const Pts &p)
-{
-    return (((uintptr_t)p.x | (uintptr_t)p.y | (uintptr_t)p.z | (uintptr_t)p.rgb) & 15u) == 0;
-}
-
 }  // namespace
 
 hipError_t launch_raster_points(const Pts &p, const Proj &P, int32_t k, uint64_t *fb,
@@ -282,10 +276,7 @@ hipError_t launch_raster_points(const Pts &p, const Proj &P, int32_t k, uint64_t
     if (p.n == 0)
         return hipSuccess;
     const dim3 grid((uint32_t)((p.n + kGenBlock * kGenPpt - 1) / (kGenBlock * kGenPpt)));
-    if (aligned16(p))
-        hipLaunchKernelGGL((k_raster_points<true>), grid, dim3(kGenBlock), kLds, s, p, P, k, fb);
-    else
-        hipLaunchKernelGGL((k_raster_points<false>), grid, dim3(kGenBlock), kLds, s, p, P, k, fb);
+    hipLaunchKernelGGL(k_raster_points, grid, dim3(kGenBlock), kLds, s, p, P, k, fb);
     return hipGetLastError();
 }
 
@@ -296,18 +287,11 @@ hipError_t launch_hq_points(const Pts &p, const Proj &P, int32_t k, uint32_t eps
     if (p.n == 0)
         return hipSuccess;
     const dim3 grid((uint32_t)((p.n + kGenBlock * kGenPpt - 1) / (kGenBlock * kGenPpt)));
-    const bool v = aligned16(p), pw = P.nr != 0;
-    if (v && pw)
-        hipLaunchKernelGGL((k_hq_points<true, true>), grid, dim3(kGenBlock), kLdsHq, s, p, P, k,
-                           eps_num, eps_den, fb, acc);
-    else if (v)
-        hipLaunchKernelGGL((k_hq_points<true, false>), grid, dim3(kGenBlock), kLdsHq, s, p, P, k,
-                           eps_num, eps_den, fb, acc);
-    else if (pw)
-        hipLaunchKernelGGL((k_hq_points<false, true>), grid, dim3(kGenBlock), kLdsHq, s, p, P, k,
+    if (P.nr != 0)
+        hipLaunchKernelGGL((k_hq_points<true>), grid, dim3(kGenBlock), kLdsHq, s, p, P, k,
                            eps_num, eps_den, fb, acc);
     else
-        hipLaunchKernelGGL((k_hq_points<false, false>), grid, dim3(kGenBlock), kLdsHq, s, p, P, k,
+        hipLaunchKernelGGL((k_hq_points<false>), grid, dim3(kGenBlock), kLdsHq, s, p, P, k,
                            eps_num, eps_den, fb, acc);
     return hipGetLastError();
 }

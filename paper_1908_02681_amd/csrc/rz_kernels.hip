@@ -20,7 +20,7 @@ using namespace dev;
 
 // Depth pass of section 2.1 for one view: one workgroup per chunk of
 // blockDim * PPT consecutive points.
-template <int PPT, bool VEC, bool EARLY, bool XCD, int BIN, bool PW>
+template <int PPT, bool EARLY, bool XCD, int BIN, bool PW>
 __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__restrict__ fb,
                                                     int64_t nchunks, uint32_t words)
 {
@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
     const int64_t base = chunk * (int64_t)blockDim.x * PPT;
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
     // no per-point bounds flags: points past the end load as NaN and are culled
-    load_points_nan<PPT, VEC>(p, base, x, y, z, c);
+    load_points_nan<PPT>(p, base, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
 
 // Depth pass for the float depth encodings (RZ_DEPTH_GL24, RZ_DEPTH_F32REV)
 // at one pixel per point: the per-wave tile kernel with the encoding's key.
-template <bool VEC, int ZK>
+template <int ZK>
 __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *__restrict__ fb,
                                                        int64_t nchunks, uint32_t words)
 {
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
     float x[PPT], y[PPT], z[PPT];
     uint32_t c[PPT];
     bool in[PPT];
-    load_points_nan<PPT, VEC>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
+    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
 }
 
 // Accumulation pass of section 2.2 for one view.
-template <int PPT, bool VEC, bool XCD, int BIN, bool PW>
+template <int PPT, bool XCD, int BIN, bool PW>
 __global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, uint32_t eps_num,
                                                   uint32_t eps_den,
                                                   const uint64_t *__restrict__ fb,
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, uint32_t eps_nu
     bool in[PPT];
     const int64_t base = chunk * (int64_t)blockDim.x * PPT;
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
-    load_points_nan<PPT, VEC>(p, base, x, y, z, c);
+    load_points_nan<PPT>(p, base, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
@@ -178,7 +178,7 @@ size_t wave_lds(int bin, int block)
                : 0;
 }
 
-template <int PPT, bool VEC, bool EARLY, int BIN, bool PW>
+template <int PPT, bool EARLY, int BIN, bool PW>
 hipError_t raster_min_ppt(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t,
                           hipStream_t s)
 {
@@ -187,17 +187,17 @@ hipError_t raster_min_ppt(const Pts &p, const Proj &P, uint64_t *fb, const Tune 
     const uint32_t words = wave_tile_words(t.bin);
     if (t.xcd_remap) {
         const int64_t grid = (nchunks + kXcds - 1) / kXcds * kXcds;
-        hipLaunchKernelGGL((k_raster_min<PPT, VEC, EARLY, true, BIN, PW>), dim3((uint32_t)grid),
+        hipLaunchKernelGGL((k_raster_min<PPT, EARLY, true, BIN, PW>), dim3((uint32_t)grid),
                            dim3(t.block), lds, s, p, P, fb, nchunks, words);
     } else {
-        hipLaunchKernelGGL((k_raster_min<PPT, VEC, EARLY, false, BIN, PW>),
+        hipLaunchKernelGGL((k_raster_min<PPT, EARLY, false, BIN, PW>),
                            dim3((uint32_t)nchunks),
                            dim3(t.block), lds, s, p, P, fb, nchunks, words);
     }
     return hipGetLastError();
 }
 
-template <int PPT, bool VEC, int BIN, bool PW>
+template <int PPT, int BIN, bool PW>
 hipError_t hq_accum_ppt(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
                         const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
 {
@@ -206,77 +206,56 @@ hipError_t hq_accum_ppt(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
     const uint32_t words = wave_tile_words(t.bin);
     if (t.xcd_remap) {
         const int64_t grid = (nchunks + kXcds - 1) / kXcds * kXcds;
-        hipLaunchKernelGGL((k_hq_accum<PPT, VEC, true, BIN, PW>), dim3((uint32_t)grid),
+        hipLaunchKernelGGL((k_hq_accum<PPT, true, BIN, PW>), dim3((uint32_t)grid),
                            dim3(t.block), lds, s, p, P, num, den, fb, acc, nchunks, words);
     } else {
-        hipLaunchKernelGGL((k_hq_accum<PPT, VEC, false, BIN, PW>), dim3((uint32_t)nchunks),
+        hipLaunchKernelGGL((k_hq_accum<PPT, false, BIN, PW>), dim3((uint32_t)nchunks),
                            dim3(t.block), lds, s, p, P, num, den, fb, acc, nchunks, words);
     }
     return hipGetLastError();
 }
 
-bool planes_aligned(const Pts &p)
-{
-    return aligned16(p.x) && aligned16(p.y) && aligned16(p.z) && aligned16(p.rgb);
-}
-
-template <int PPT, bool VEC, bool PW>
+template <int PPT, bool PW>
 hipError_t raster_min_bin(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t,
                           hipStream_t s)
 {
     switch (t.bin) {
-    case kBinBlock: return raster_min_ppt<PPT, VEC, true, kBinBlock, PW>(p, P, fb, t, s);
+    case kBinBlock: return raster_min_ppt<PPT, true, kBinBlock, PW>(p, P, fb, t, s);
     case kBinWave:
-    case kBinWaveSmall: return raster_min_ppt<PPT, VEC, true, kBinWave, PW>(p, P, fb, t, s);
+    case kBinWaveSmall: return raster_min_ppt<PPT, true, kBinWave, PW>(p, P, fb, t, s);
     default:
-        return t.early_out ? raster_min_ppt<PPT, VEC, true, kBinNone, PW>(p, P, fb, t, s)
-                           : raster_min_ppt<PPT, VEC, false, kBinNone, PW>(p, P, fb, t, s);
+        return t.early_out ? raster_min_ppt<PPT, true, kBinNone, PW>(p, P, fb, t, s)
+                           : raster_min_ppt<PPT, false, kBinNone, PW>(p, P, fb, t, s);
     }
-}
-
-template <int PPT, bool VEC>
-hipError_t raster_min_vec(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t,
-                          hipStream_t s)
-{
-    return P.nr ? raster_min_bin<PPT, VEC, true>(p, P, fb, t, s)
-                : raster_min_bin<PPT, VEC, false>(p, P, fb, t, s);
 }
 
 template <int PPT>
 hipError_t raster_min_dispatch(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t,
                                hipStream_t s)
 {
-    return planes_aligned(p) ? raster_min_vec<PPT, true>(p, P, fb, t, s)
-                             : raster_min_vec<PPT, false>(p, P, fb, t, s);
+    return P.nr ? raster_min_bin<PPT, true>(p, P, fb, t, s)
+                : raster_min_bin<PPT, false>(p, P, fb, t, s);
 }
 
-template <int PPT, bool VEC, bool PW>
+template <int PPT, bool PW>
 hipError_t hq_accum_bin(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
                         const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
 {
     switch (t.bin) {
-    case kBinBlock: return hq_accum_ppt<PPT, VEC, kBinBlock, PW>(p, P, num, den, fb, acc, t, s);
+    case kBinBlock: return hq_accum_ppt<PPT, kBinBlock, PW>(p, P, num, den, fb, acc, t, s);
     case kBinWave:
     case kBinWaveSmall:
-        return hq_accum_ppt<PPT, VEC, kBinWave, PW>(p, P, num, den, fb, acc, t, s);
-    default: return hq_accum_ppt<PPT, VEC, kBinNone, PW>(p, P, num, den, fb, acc, t, s);
+        return hq_accum_ppt<PPT, kBinWave, PW>(p, P, num, den, fb, acc, t, s);
+    default: return hq_accum_ppt<PPT, kBinNone, PW>(p, P, num, den, fb, acc, t, s);
     }
-}
-
-template <int PPT, bool VEC>
-hipError_t hq_accum_vec(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
-                        const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
-{
-    return P.nr ? hq_accum_bin<PPT, VEC, true>(p, P, num, den, fb, acc, t, s)
-                : hq_accum_bin<PPT, VEC, false>(p, P, num, den, fb, acc, t, s);
 }
 
 template <int PPT>
 hipError_t hq_accum_dispatch(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
                              const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
 {
-    return planes_aligned(p) ? hq_accum_vec<PPT, true>(p, P, num, den, fb, acc, t, s)
-                             : hq_accum_vec<PPT, false>(p, P, num, den, fb, acc, t, s);
+    return P.nr ? hq_accum_bin<PPT, true>(p, P, num, den, fb, acc, t, s)
+                : hq_accum_bin<PPT, false>(p, P, num, den, fb, acc, t, s);
 }
 
 template <int ZK>
@@ -285,12 +264,8 @@ hipError_t raster_min_zk(const Pts &p, const Proj &P, uint64_t *fb, const Tune &
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * 16);
     const size_t lds = wave_lds(t.bin, t.block);
     const uint32_t words = wave_tile_words(t.bin);
-    if (planes_aligned(p))
-        hipLaunchKernelGGL((k_raster_min_zk<true, ZK>), dim3((uint32_t)nchunks), dim3(t.block),
-                           lds, s, p, P, fb, nchunks, words);
-    else
-        hipLaunchKernelGGL((k_raster_min_zk<false, ZK>), dim3((uint32_t)nchunks), dim3(t.block),
-                           lds, s, p, P, fb, nchunks, words);
+    hipLaunchKernelGGL((k_raster_min_zk<ZK>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
+                       fb, nchunks, words);
     return hipGetLastError();
 }
 

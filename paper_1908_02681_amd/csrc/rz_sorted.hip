@@ -154,7 +154,6 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v)
 
 // Pass A: on-screen points per bucket in this workgroup's contiguous range
 // of points, written as row blockIdx.x of ccounts ([groups][nb]).
-template <bool VEC>
 __global__ void __launch_bounds__(kCountBlock) k_sort_count(Pts p, Proj P, uint32_t *ccounts,
                                                             int32_t ntx, int32_t nb,
                                                             int64_t per_wg)
@@ -170,7 +169,7 @@ __global__ void __launch_bounds__(kCountBlock) k_sort_count(Pts p, Proj P, uint3
     for (int64_t base = lo; base < q.n; base += kCountStep) {
         float x[kCountPpt], y[kCountPpt], z[kCountPpt];
         uint32_t c[kCountPpt];
-        load_points_nan<kCountPpt, VEC>(q, base, x, y, z, c);   // past the end: NaN, culled
+        load_points_nan<kCountPpt>(q, base, x, y, z, c);   // past the end: NaN, culled
 #pragma unroll
         for (int j = 0; j < kCountPpt; ++j) {
             uint32_t px, py;
@@ -306,7 +305,7 @@ __global__ void __launch_bounds__(kScanThreads) k_sort_scan(const uint32_t *tota
 // owns buckets t * kScBuckets .. t * kScBuckets + kScBuckets - 1 in every
 // per-bucket phase and keeps the workgroup's cursors of those buckets in
 // registers.
-template <bool VEC, bool PW>
+template <bool PW>
 __global__ void __launch_bounds__(kScBlock) k_sort_scatter(Pts p, Proj P,
                                                            const uint32_t *__restrict__ cursors,
                                                            const uint32_t *__restrict__ bstart,
@@ -336,7 +335,7 @@ __global__ void __launch_bounds__(kScBlock) k_sort_scatter(Pts p, Proj P,
     float x[kScPpt], y[kScPpt], z[kScPpt];
     uint32_t c[kScPpt];
     if (lo < q.n)
-        load_points_nan<kScPpt, VEC>(q, lo, x, y, z, c);   // past the end: NaN, culled
+        load_points_nan<kScPpt>(q, lo, x, y, z, c);   // past the end: NaN, culled
     for (int64_t base = lo; base < q.n; base += kScStep) {
 #pragma unroll
         for (int r = 0; r < kScBuckets; ++r)
@@ -357,7 +356,7 @@ __global__ void __launch_bounds__(kScBlock) k_sort_scatter(Pts p, Proj P,
             rank[j] = v ? atomicAdd(&s_off[lb[j] >> 12], 1u) : ~0u;
         }
         if (base + kScStep < q.n)   // workgroup-uniform
-            load_points_nan<kScPpt, VEC>(q, base + kScStep, x, y, z, c);
+            load_points_nan<kScPpt>(q, base + kScStep, x, y, z, c);
         __syncthreads();   // counts complete
         // exclusive scan of the counts over the buckets; staging index i of
         // bucket b goes to cursor(b) + (i - off(b)): each bucket's delta
@@ -588,24 +587,24 @@ __global__ void __launch_bounds__(kAccumBlock) k_sort_accum(const uint64_t *__re
     }
 }
 
-template <bool VEC, bool PW>
+template <bool PW>
 void launch_count_scatter(const Pts &p, const Proj &P, const Layout &L, uint32_t *ccounts,
                           uint32_t *btotal, uint32_t *bstart, uint32_t *bchunk, uint64_t *keys,
                           uint16_t *lps, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_sort_count<VEC>), dim3(L.groups), dim3(kCountBlock), 0, s, p, P,
+    hipLaunchKernelGGL(k_sort_count, dim3(L.groups), dim3(kCountBlock), 0, s, p, P,
                        ccounts, L.ntx, L.nb, L.per_wg);
     hipLaunchKernelGGL(k_sort_prefix, dim3((L.nb + kPrefixCols - 1) / kPrefixCols),
                        dim3(kPrefixCols * kPrefixSegs), 0, s, ccounts, L.groups, L.nb, btotal);
     hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(kScanThreads), 0, s, btotal, bstart, bchunk,
                        L.nb, L.chunk);
-    hipLaunchKernelGGL((k_sort_scatter<VEC, PW>), dim3(L.groups), dim3(kScBlock), 0, s, p, P,
+    hipLaunchKernelGGL((k_sort_scatter<PW>), dim3(L.groups), dim3(kScBlock), 0, s, p, P,
                        ccounts, bstart, keys, lps, L.ntx, L.nb, L.per_wg);
 }
 
 // Passes A to C: leaves the buckets (keys, lps), their starts and the work
 // list of E.
-hipError_t sort_passes(const Pts &p, const Proj &P, const Layout &L, char *ws, bool vec,
+hipError_t sort_passes(const Pts &p, const Proj &P, const Layout &L, char *ws,
                        hipStream_t s)
 {
     Range r("rz sort: count, offsets, scatter");
@@ -615,16 +614,10 @@ hipError_t sort_passes(const Pts &p, const Proj &P, const Layout &L, char *ws, b
     uint32_t *bchunk = (uint32_t *)(ws + L.bchunk);
     uint64_t *keys = (uint64_t *)(ws + L.keys);
     uint16_t *lps = (uint16_t *)(ws + L.lps);
-    const bool pw = P.nr != 0;
-    if (vec && pw)
-        launch_count_scatter<true, true>(p, P, L, ccounts, btotal, bstart, bchunk, keys, lps, s);
-    else if (vec)
-        launch_count_scatter<true, false>(p, P, L, ccounts, btotal, bstart, bchunk, keys, lps, s);
-    else if (pw)
-        launch_count_scatter<false, true>(p, P, L, ccounts, btotal, bstart, bchunk, keys, lps, s);
+    if (P.nr != 0)
+        launch_count_scatter<true>(p, P, L, ccounts, btotal, bstart, bchunk, keys, lps, s);
     else
-        launch_count_scatter<false, false>(p, P, L, ccounts, btotal, bstart, bchunk, keys, lps,
-                                           s);
+        launch_count_scatter<false>(p, P, L, ccounts, btotal, bstart, bchunk, keys, lps, s);
     return hipGetLastError();
 }
 
@@ -676,10 +669,8 @@ int rasterize_sorted(const rz_points *pts, const rz_view *view, const rz_depth_m
     hipError_t e = hipSuccess;
     if (pts->n > 0) {
         const Pts p{pts->x, pts->y, pts->z, pts->rgb, pts->n};
-        const bool vec = (((uintptr_t)p.x | (uintptr_t)p.y | (uintptr_t)p.z | (uintptr_t)p.rgb) &
-                          15u) == 0;
         char *ws = (char *)workspace;
-        e = sort_passes(p, P, L, ws, vec, s);
+        e = sort_passes(p, P, L, ws, s);
         const uint64_t *keys = (const uint64_t *)(ws + L.keys);
         const uint16_t *lps = (const uint16_t *)(ws + L.lps);
         const uint32_t *bstart = (const uint32_t *)(ws + L.bstart);
