@@ -311,8 +311,9 @@ int rz_resolve_hq(uint64_t *fb, uint64_t *acc, int64_t npix,
  *              its fragments fall in a small screen rectangle); 2: one LDS
  *              tile per wave (no workgroup barrier), 8 KiB; 3: the same with
  *              a 2 KiB tile (more waves per SIMD when registers allow them;
- *              a wave whose fragments span more than 256 pixels, 128 when
- *              splatting, takes the direct atomics instead).
+ *              6 KiB in the splat pass; a wave whose fragments span more than
+ *              256 pixels, 768 when splatting, takes the direct atomics
+ *              instead).
  */
 typedef struct rz_launch {
     int32_t block;
@@ -324,7 +325,8 @@ typedef struct rz_launch {
 /* Sets the launch shape of both point passes of the one-view calls and the
    server (RZ_EINVAL if out of range); NULL restores the library defaults
    (depth pass 64 threads x 16 points with the 8 KiB per-wave tile, splat
-   pass 64 x 8 with the 2 KiB per-wave tile, early-out, no XCD remap).  rz_get_launch reports the depth pass's shape.
+   pass 64 x 8 with the small per-wave tile, early-out, no XCD remap).
+   rz_get_launch reports the depth pass's shape.
    Thread-safe: a call running concurrently launches with either the old
    or the new shape, and both give the same result. */
 int rz_set_launch(const rz_launch *launch);

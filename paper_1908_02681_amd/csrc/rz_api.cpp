@@ -171,6 +171,23 @@ int make_proj(const rz_view *v, const rz_depth_map *dm, Proj *P)
     P->wfp = z0 < 4503599627370496.0 ? 1 : 0;   // 2^52
     P->width = v->width;
     P->height = v->height;
+    // depths that need no clamp: far itself, unless the depths just below it
+    // reach past 2^40 - 2 (rounding next to far); then a bound a little
+    // nearer, or none if that is not enough
+    auto top = [&](double d) { return floor((d - o) * s); };
+    for (int32_t k = 0; k < 8; ++k)
+        P->dlo[k] = P->dhi[k] = v->near_;
+    if (P->nr == 0) {
+        double hi = v->far_;
+        if (top(hi) > kQRange - 1.0)
+            hi = v->far_ - (v->far_ - v->near_) * 0x1p-20;
+        P->dhi[0] = hi > v->near_ && top(hi) <= kQRange - 1.0 ? hi : v->near_;
+    } else {   // the checks above bound q at the end of every range that is used
+        for (int32_t k = 0; k < P->nr; ++k) {
+            P->dlo[k] = fmax(P->rb[k], v->near_);
+            P->dhi[k] = k + 1 < P->nr ? fmin(P->rb[k + 1], v->far_) : v->far_;
+        }
+    }
     return RZ_OK;
 }
 

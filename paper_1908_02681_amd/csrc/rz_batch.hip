@@ -58,7 +58,7 @@ struct MvResolve {
 // Depth passes of views[0 .. nv) over one chunk: the points are loaded
 // once and stay in registers while each view is rasterized in turn.
 template <int PPT, bool XCD, int BIN, bool PW>
-__global__ void __launch_bounds__(512) k_mv_raster_min(Pts p, const MvView *__restrict__ views,
+__global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(Pts p, const MvView *__restrict__ views,
                                                        int32_t nv, int64_t nchunks,
                                                        uint32_t words)
 {
@@ -76,11 +76,23 @@ __global__ void __launch_bounds__(512) k_mv_raster_min(Pts p, const MvView *__re
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
+    // the points' loads end here, so that no view waits for another's atomics
+    // on their account (one counter covers all memory operations of a wave)
+#pragma unroll
+    for (int j = 0; j < PPT; ++j)
+        own(x[j]), own(y[j]), own(z[j]), own(c[j]);
     for (int32_t k = 0; k < nv; ++k) {
         const Proj P = views[k].P;
+        const Trans T = lane_trans(P);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j)   // nothing derived from the points is kept across views
+            own(x[j]), own(y[j]), own(z[j]), own(c[j]);
         if (BIN == kBinWave) {
-            raster_chunk_wave<PPT, PW>(P, views[k].fb, x, y, z, c, in,
-                                       s_waves + (threadIdx.x >> 6) * words, words);
+            uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
+            MinFlush flush;
+            raster_chunk_wave<PPT, PW>(P, T, views[k].fb, x, y, z, c, w_tile, words, flush,
+                                       [] {});
+            raster_wave_flush(views[k].fb, w_tile, flush);
         } else {
             if (BIN == kBinBlock && k > 0)
                 __syncthreads();   // previous view's tile fully flushed
@@ -92,7 +104,7 @@ __global__ void __launch_bounds__(512) k_mv_raster_min(Pts p, const MvView *__re
 
 // Accumulate passes of the splatting views views[0 .. nv) over one chunk.
 template <int PPT, bool XCD, int BIN, bool PW>
-__global__ void __launch_bounds__(512) k_mv_hq_accum(Pts p, const MvView *__restrict__ views,
+__global__ void __launch_bounds__(512, PPT == 4 && !PW ? 6 : 1) k_mv_hq_accum(Pts p, const MvView *__restrict__ views,
                                                      int32_t nv, int64_t nchunks,
                                                      uint32_t words)
 {
@@ -110,16 +122,27 @@ __global__ void __launch_bounds__(512) k_mv_hq_accum(Pts p, const MvView *__rest
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
+    // the points' loads end here, so that no view waits for another's atomics
+    // on their account (one counter covers all memory operations of a wave)
+#pragma unroll
+    for (int j = 0; j < PPT; ++j)
+        own(x[j]), own(y[j]), own(z[j]), own(c[j]);
     for (int32_t k = 0; k < nv; ++k) {
         const Proj P = views[k].P;
+        const Trans T = lane_trans(P);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j)   // nothing derived from the points is kept across views
+            own(x[j]), own(y[j]), own(z[j]), own(c[j]);
         if (BIN == kBinWave) {
-            accum_chunk_wave<PPT, PW>(P, views[k].eps_num, views[k].eps_den, views[k].fb,
-                                      views[k].acc, x, y, z, c, in,
-                                      s_waves + (threadIdx.x >> 6) * words, words);
+            uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
+            SumFlush<PPT> flush;
+            accum_chunk_wave<PPT, PW>(P, T, views[k].eps, views[k].fb, views[k].acc, x, y, z, c,
+                                      w_tile, words, flush, [] {});
+            accum_wave_flush<PPT>(views[k].acc, w_tile, flush);
         } else {
             if (BIN == kBinBlock && k > 0)
                 __syncthreads();
-            accum_chunk<PPT, BIN == kBinBlock, PW>(P, views[k].eps_num, views[k].eps_den,
+            accum_chunk<PPT, BIN == kBinBlock, PW>(P, views[k].eps.num, views[k].eps.den,
                                                    views[k].fb, views[k].acc, x, y, z, c, in,
                                                    s_tile, s_box);
         }
@@ -190,7 +213,7 @@ hipError_t mv_launch_ppt(bool hq, bool pw, const Pts &p, const MvView *views, in
 {
     const int64_t nchunks = (p.n + (int64_t)t.block * PPT - 1) / ((int64_t)t.block * PPT);
     const int64_t grid = XCD ? (nchunks + kXcds - 1) / kXcds * kXcds : nchunks;
-    const uint32_t words = wave_tile_words(t.bin);
+    const uint32_t words = wave_tile_words(t.bin, hq);
     const size_t lds =
         BIN == kBinWave ? (size_t)(t.block / 64) * words * sizeof(uint64_t) : 0;
     if (hq && pw)
@@ -519,8 +542,9 @@ int rz_batch_plan(const rz_points *pts, const rz_batch_view *views, int32_t nvie
                 hp.eps_num = 1;
                 hp.eps_den = 100;
             }
-            if ((rc = check_hq(&hp, m.P, &m.eps_num, &m.eps_den)))
+            if ((rc = check_hq(&hp, m.P, &m.eps.num, &m.eps.den)))
                 return rc;
+            m.eps.inv_den = 1.0 / (double)m.eps.den;
         }
         for (int32_t j = 0; j < i; ++j)   // buffers of two views must not coincide
             if (views[j].fb == v.fb || views[j].img == v.img || (hq && views[j].acc == v.acc))

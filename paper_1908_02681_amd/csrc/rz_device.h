@@ -50,10 +50,14 @@ constexpr uint32_t kWaveTileSmallWords = 256;
 // share the kBinWave code.
 enum : int { kBinNone = 0, kBinBlock = 1, kBinWave = 2, kBinWaveSmall = 3 };
 
-// Words of one wave's tile in a per-wave tiling mode.
-__host__ __device__ constexpr uint32_t wave_tile_words(int bin)
+// Words of one wave's tile in a per-wave tiling mode.  The accumulate pass's
+// small tile has 6 KiB: three words a pixel (two copies of the sums and the
+// window's threshold) for the 256 pixels of the depth pass's.
+__host__ __device__ constexpr uint32_t wave_tile_words(int bin, bool hq)
 {
-    return bin == kBinWaveSmall ? kWaveTileSmallWords : kWaveTileWords;
+    return bin != kBinWaveSmall ? kWaveTileWords
+           : hq                 ? 3 * kWaveTileSmallWords
+                                : kWaveTileSmallWords;
 }
 
 // Four points of a plane.  The hardware's 16-byte loads need no more than
@@ -62,6 +66,21 @@ typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+
+// Device memory and LDS as such: pointers that come out of a table are
+// otherwise taken through flat instructions, which occupy both paths.
+typedef __attribute__((address_space(1))) uint64_t gu64;
+typedef __attribute__((address_space(3))) uint64_t lu64;
+typedef __attribute__((address_space(3))) u64x2 lu64x2;
+__device__ __forceinline__ gu64 *global_ptr(const uint64_t *p) { return (gu64 *)p; }
+// LDS by its byte address: LDS addresses are 32 bits, so that a tile's origin
+// folds into its base.
+__device__ __forceinline__ uint32_t lds_addr(const uint64_t *p)
+{
+    return (uint32_t)(uintptr_t)(lu64 *)p;
+}
+__device__ __forceinline__ lu64 *lds_ptr(uint32_t a) { return (lu64 *)(uintptr_t)a; }
+__device__ __forceinline__ lu64x2 *lds_ptr2(uint32_t a) { return (lu64x2 *)(uintptr_t)a; }
 
 // Streaming (non-temporal) access: the data is touched once per pass.
 template <typename T>
@@ -178,8 +197,8 @@ __device__ __forceinline__ float recip_rn(float w)
 
 // Translation column of the float matrix (clip x, y, w) and of the depth
 // row in double, the addend of the first fused step of each row.
-// lane_trans() returns it as per-lane values (identity DPP moves), made once
-// per chunk: a fused multiply-add can take only one scalar-register operand
+// lane_trans() returns it as per-lane values (moves that the compiler cannot
+// fold back), made once per chunk: a fused multiply-add can take only one scalar-register operand
 // on gfx950, so with the scalar copies every row of every point would need
 // a move first.
 struct Trans {
@@ -189,8 +208,9 @@ struct Trans {
 
 __device__ __forceinline__ float lane_copy(float v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xE4, 0xF, 0xF,
-                                                      false));   // quad_perm [0,1,2,3]
+    float r;
+    asm("v_mov_b32_e32 %0, %1" : "=v"(r) : "s"(v));
+    return r;
 }
 
 __device__ __forceinline__ double lane_copy(double v)
@@ -244,13 +264,18 @@ __device__ __forceinline__ bool project(const Proj &P, const Trans &T, float x, 
 
 // Depth in double precision (section 1, section 2.1): row 3 of VP, fused
 // in the same order as the clip coordinates.
-__device__ __forceinline__ double depth_of(const Proj &P, const Trans &T, float x, float y,
-                                           float z)
+__device__ __forceinline__ double depth_of(const Proj &P, double td, float x, float y, float z)
 {
-    double d = __builtin_fma(P.v[0], (double)x, T.td);
+    double d = __builtin_fma(P.v[0], (double)x, td);
     d = __builtin_fma(P.v[1], (double)y, d);
     d = __builtin_fma(P.v[2], (double)z, d);
     return d;
+}
+
+__device__ __forceinline__ double depth_of(const Proj &P, const Trans &T, float x, float y,
+                                           float z)
+{
+    return depth_of(P, T.td, x, y, z);
 }
 
 __device__ __forceinline__ double depth_of(const Proj &P, float x, float y, float z)
@@ -375,18 +400,6 @@ __device__ __forceinline__ bool fragment_zk(const Proj &P, const Trans &T, float
     return vis & in_range & clip;
 }
 
-// The fragment of the kernels templated on the depth encoding: ZK = 0 for
-// the integer maps, else RZ_DEPTH_GL24 or RZ_DEPTH_F32REV.
-template <bool PW, int ZK>
-__device__ __forceinline__ bool fragment_enc(const Proj &P, const Trans &T, float x, float y,
-                                             float z, uint32_t &px, uint32_t &py, uint64_t &q)
-{
-    if constexpr (ZK == 0)
-        return fragment<PW>(P, T, x, y, z, px, py, q);
-    else
-        return fragment_zk<ZK>(P, T, x, y, z, px, py, q);
-}
-
 // Workgroup -> chunk of points.  Workgroups are dealt round-robin to the 8
 // XCDs; with the remap, XCD k works through the k-th eighth of the chunks,
 // so spatially coherent (e.g. Morton-ordered) ranges share one L2.
@@ -418,18 +431,18 @@ __device__ __forceinline__ void load_full(const Pts &p, int64_t base, float (&x)
                                           float (&y)[PPT], float (&z)[PPT], uint32_t (&c)[PPT])
 {
     const int64_t stride = 4 * (int64_t)blockDim.x;
-    const int64_t first = base + 4 * (int64_t)threadIdx.x;
+    const uint32_t lane = 4 * threadIdx.x;   // beside a base that the whole workgroup shares
 #pragma unroll
     for (int g = 0; g < PPT / 4; ++g) {
-        const int64_t i = first + g * stride;
+        const int64_t i = base + g * stride;
         const f32x4 vx =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.x + i));
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.x + i + lane));
         const f32x4 vy =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.y + i));
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.y + i + lane));
         const f32x4 vz =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.z + i));
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.z + i + lane));
         const u32x4 vc =
-            __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p.rgb + i));
+            __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p.rgb + i + lane));
         x[4 * g + 0] = vx.x; x[4 * g + 1] = vx.y; x[4 * g + 2] = vx.z; x[4 * g + 3] = vx.w;
         y[4 * g + 0] = vy.x; y[4 * g + 1] = vy.y; y[4 * g + 2] = vy.z; y[4 * g + 3] = vy.w;
         z[4 * g + 0] = vz.x; z[4 * g + 1] = vz.y; z[4 * g + 2] = vz.z; z[4 * g + 3] = vz.w;
@@ -768,26 +781,475 @@ __device__ __forceinline__ Box wave_box_live_min(const uint32_t (&px)[PPT],
     return Box{wave_min(lx), wave_min(ly), wave_max(hx), wave_max(hy)};
 }
 
+// A register of its own for v: keeps the compiler from carrying values that it
+// derived from v over to here in further registers.
+__device__ __forceinline__ void own(float &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void own(uint32_t &v) { asm volatile("" : "+v"(v)); }
+
+// The loads of v end here, whether v is used or not: a register with a load
+// pending would make whatever takes it next wait for every memory operation
+// since (one counter covers them all, in order).
+__device__ __forceinline__ void arrive(uint64_t &v) { asm volatile("" : "+v"(v)); }
+
+// Window position of one point without the cull and the IEEE division: the
+// steps of project() with the corrected estimate of 1 / w, which is the IEEE
+// quotient for w in [2^-126, 2^126).  (The matrix unit's 4x4x1 instruction
+// gives the same bits for a whole column of rows and issues three instructions
+// for nine here, but takes longer: a batch of 64 views of 100M points 17.2 ms
+// with it, 16.2 ms with these.)
+__device__ __forceinline__ void window_pos(const Proj &P, const Trans &T, float x, float y, float z,
+                                           float &cw, float &fx, float &fy)
+{
+    float cx = __builtin_fmaf(P.m[0], x, T.tx);
+    cx = __builtin_fmaf(P.m[1], y, cx);
+    cx = __builtin_fmaf(P.m[2], z, cx);
+    float cy = __builtin_fmaf(P.m[4], x, T.ty);
+    cy = __builtin_fmaf(P.m[5], y, cy);
+    cy = __builtin_fmaf(P.m[6], z, cy);
+    cw = __builtin_fmaf(P.m[8], x, T.tw);
+    cw = __builtin_fmaf(P.m[9], y, cw);
+    cw = __builtin_fmaf(P.m[10], z, cw);
+    const float iw = recip_newton(cw);
+    fx = __builtin_fmaf(cx * iw, P.hw, P.hw);
+    fy = __builtin_fmaf(cy * iw, P.hh, P.hh);
+}
+
+// Minimum within each row of 16 lanes.
+__device__ __forceinline__ int32_t row_min(int32_t v)
+{
+#define RZ_DPP_ROW(ctrl)                                                                   \
+    {                                                                                      \
+        const int32_t t = __builtin_amdgcn_update_dpp(0x7FFFFFFF, v, ctrl, 0xF, 0xF, false); \
+        v = v < t ? v : t;                                                                 \
+    }
+    RZ_DPP_ROW(0xB1)    // quad_perm [1,0,3,2]
+    RZ_DPP_ROW(0x4E)    // quad_perm [2,3,0,1]
+    RZ_DPP_ROW(0x141)   // row_half_mirror
+    RZ_DPP_ROW(0x140)   // row_mirror
+#undef RZ_DPP_ROW
+    return v;
+}
+
+// Window positions of a wave's points, all of them inside the screen: true,
+// with their pixel rectangle, when every point of the wave has a w in
+// [2^-126, 2^126) and an on-screen window position; false (and the rest
+// meaningless) otherwise.  The common case of a chunk of an ordered cloud: it
+// needs no flag per point.  The tests run on bit patterns, where the order of
+// non-negative floats is that of the integers and every other value (negative,
+// NaN, infinite) falls outside: w through an unsigned minimum and maximum, x
+// and y through signed ones.
+//
+// The four reductions over the lanes share their steps: two half-wave swaps
+// leave x (rows 0, 1) beside y (rows 2, 3), a row swap puts the minima into
+// the even rows and the complemented maxima into the odd ones, and one 16-lane
+// reduction finishes all four: 11 instructions where four 64-lane reductions
+// take 24.
+template <int PPT>
+__device__ __forceinline__ bool window_all(const Proj &P, const Trans &T, const float (&x)[PPT],
+                                           const float (&y)[PPT], const float (&z)[PPT],
+                                           float (&fx)[PPT], float (&fy)[PPT], Box &box)
+{
+    static_assert(PPT % 2 == 0, "points are taken in pairs");
+    uint32_t wlo = ~0u, whi = 0u;
+    int32_t xlo = 0x7FFFFFFF, ylo = 0x7FFFFFFF, xhi = -0x7FFFFFFF - 1, yhi = -0x7FFFFFFF - 1;
+#pragma unroll
+    for (int j = 0; j < PPT; j += 2) {   // pairs: three-operand min and max
+        float w0, w1;
+        window_pos(P, T, x[j], y[j], z[j], w0, fx[j], fy[j]);
+        window_pos(P, T, x[j + 1], y[j + 1], z[j + 1], w1, fx[j + 1], fy[j + 1]);
+        const uint32_t a = __float_as_uint(w0), b = __float_as_uint(w1);
+        wlo = min(wlo, min(a, b));
+        whi = max(whi, max(a, b));
+        const int32_t x0 = __float_as_int(fx[j]), x1 = __float_as_int(fx[j + 1]);
+        const int32_t y0 = __float_as_int(fy[j]), y1 = __float_as_int(fy[j + 1]);
+        xlo = min(xlo, min(x0, x1));
+        xhi = max(xhi, max(x0, x1));
+        ylo = min(ylo, min(y0, y1));
+        yhi = max(yhi, max(y0, y1));
+        if (j % 4)
+            __builtin_amdgcn_sched_barrier(0);
+    }
+    // rows 0 and 1: x, rows 2 and 3: y
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)xlo, (uint32_t)ylo, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)~xhi, (uint32_t)~yhi, false, false);
+    const int32_t l2 = min((int32_t)lo[0], (int32_t)lo[1]);
+    const int32_t h2 = min((int32_t)hi[0], (int32_t)hi[1]);
+    // rows 0 and 2: the minima, rows 1 and 3: the complements of the maxima
+    const auto lh = __builtin_amdgcn_permlane16_swap((uint32_t)l2, (uint32_t)h2, false, false);
+    const int32_t m = row_min(min((int32_t)lh[0], (int32_t)lh[1]));
+    const uint32_t lane = threadIdx.x & 63u;
+    const bool odd = (lane & 16u) != 0;
+    const int32_t size = (lane & 32u) ? __float_as_int(P.fh) : __float_as_int(P.fw);
+    // even rows: minimum >= 0; odd rows: maximum < size, on the complement
+    const bool ok = (wlo >= 0x00800000u) & (whi < 0x7E800000u) & (m >= (odd ? -size : 0));
+    if (wave_any(!ok))
+        return false;
+    const int32_t px = (int32_t)__int_as_float(odd ? ~m : m);
+    box.x0 = (uint32_t)__builtin_amdgcn_readlane(px, 0);
+    box.x1 = (uint32_t)__builtin_amdgcn_readlane(px, 16);
+    box.y0 = (uint32_t)__builtin_amdgcn_readlane(px, 32);
+    box.y1 = (uint32_t)__builtin_amdgcn_readlane(px, 48);
+    return true;
+}
+
+// One uniform range of the depth map for a whole chunk: the linear and scale
+// maps have one; of a piecewise map, the one that holds depth d of lane 0.
+struct Range1 {
+    double lo, hi;   // depths it serves without a clamp
+    double o, s;     // q = base + floor((d - o) * s)
+    uint64_t base;
+};
+
+template <bool PW>
+__device__ __forceinline__ Range1 uniform_range(const Proj &P, double d)
+{
+    if (!PW || P.nr == 0)
+        return Range1{P.dlo[0], P.dhi[0], P.o, P.s, 0ull};
+    int k = 0;
+    for (int i = 1; i < P.nr; ++i)
+        k = d >= P.rb[i] ? i : k;
+    k = __builtin_amdgcn_readfirstlane(k);
+    return Range1{P.dlo[k], P.dhi[k], P.rb[k], P.rs[k], P.rbase[k]};
+}
+
+// q << 24 | rgb from floor((d - o) * s) + 2^52, whose mantissa is q: the key's
+// high word is the shifted pair, its low word takes three bytes of colour.
+__device__ __forceinline__ uint64_t make_key(uint64_t q52, uint32_t c)
+{
+    const uint32_t lo = (uint32_t)q52, hi = (uint32_t)(q52 >> 32);
+    const uint32_t kh = __builtin_amdgcn_alignbyte(hi, lo, 1);
+    const uint32_t kl = __builtin_amdgcn_perm(lo, c, 0x04020100u);
+    return ((uint64_t)kh << 32) | kl;
+}
+
+// The screen rectangle of a wave's fragments as a tile in LDS.
+struct WaveTile {
+    uint32_t x0, y0, bw, area;
+    float inv_bw;
+    uint32_t width;
+};
+
+__device__ __forceinline__ WaveTile wave_tile(const Proj &P, const Box &box)
+{
+    WaveTile t;
+    t.x0 = box.x0;
+    t.y0 = box.y0;
+    t.bw = box.x1 - box.x0 + 1;
+    t.area = t.bw * (box.y1 - box.y0 + 1);   // both at most 2^15
+    t.inv_bw = __builtin_amdgcn_rcpf((float)t.bw);   // tile_rc corrects it
+    t.width = (uint32_t)P.width;
+    return t;
+}
+
+// Pixel of entry i of the tile, in the framebuffer.
+__device__ __forceinline__ uint32_t tile_pixel(const WaveTile &t, uint32_t i)
+{
+    uint32_t r, col;
+    tile_rc(i, t.bw, t.inv_bw, r, col);
+    return __umul24(t.y0 + r, t.width) + t.x0 + col;
+}
+
+// LDS address of a point's entry in a tile of 1 << sh bytes per pixel whose
+// entry 0 lies at `first` - origin << sh (modulo 2^32).
+__device__ __forceinline__ uint32_t tile_entry(const WaveTile &t, float fx, float fy, uint32_t sh,
+                                               uint32_t first)
+{
+    return ((__umul24((uint32_t)(int32_t)fy, t.bw) + (uint32_t)(int32_t)fx) << sh) + first;
+}
+
+// `first` of a wave's tile at LDS address base: kept in one register.
+__device__ __forceinline__ uint32_t tile_first(const WaveTile &t, uint32_t base, uint32_t sh)
+{
+    uint32_t v = base - ((t.y0 * t.bw + t.x0) << sh);
+    asm("" : "+v"(v));
+    return v;
+}
+
+// What raster_wave_fast leaves to be flushed: its tile (area 0: nothing), and
+// of the lane's first entry the pixel and the nearest key read before.
+struct MinFlush {
+    WaveTile t;
+    uint32_t p0;
+    uint64_t cur;
+    bool four;
+};
+
+// The flush: one coalesced global atomic per touched pixel whose nearest key
+// it lowers.
+__device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, const uint64_t *w_tile,
+                                                  MinFlush &f)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t base = lds_addr(w_tile);
+    gu64 *gfb = global_ptr(fb);
+    arrive(f.cur);
+    if (f.t.area == 0)
+        return;
+    auto nearest = [&](uint32_t i) -> uint64_t {   // of entry i of the tile
+        if (!f.four)
+            return *lds_ptr(base + 8 * i);
+        const u64x2 a = *lds_ptr2(base + 32 * i), b = *lds_ptr2(base + 32 * i + 16);
+        const uint64_t m = a.x < a.y ? a.x : a.y, n = b.x < b.y ? b.x : b.y;
+        return m < n ? m : n;
+    };
+    if (lane < f.t.area) {
+        const uint64_t v = nearest(lane);
+        if (v < f.cur)
+            __hip_atomic_fetch_min(gfb + f.p0, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (uint32_t i = lane + 64; i < f.t.area; i += 64) {
+        const uint64_t v = nearest(i);
+        if (v != ~0ull) {
+            gu64 *dst = gfb + tile_pixel(f.t, i);
+            const uint64_t was = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v < was)
+                __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    wave_sync();   // the tile is free for the next use
+}
+
+// raster_chunk_wave for a wave whose points are all on screen and, as it turns
+// out, in one range of the depth map and in [near, far): no flag per point, and
+// neither the clamp nor the test for a slow reciprocal.  Returns false, with
+// fb untouched or holding nothing but keys of the wave, when that does not
+// hold.  The nearest keys that the flush compares with are read before the
+// depths are computed, so that their latency passes meanwhile (a key read early
+// is an upper bound of the later one).
+//
+// A tile that fits four times is kept four times, lane i taking copy i & 3:
+// neighbouring lanes hold neighbouring points, and LDS atomics of one address
+// follow each other one per cycle (a depth pass of 100M points over 8 views:
+// 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
+template <int PPT, bool PW>
+__device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
+                                                 uint64_t *__restrict__ fb,
+                                                 const float (&x)[PPT], const float (&y)[PPT],
+                                                 const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                 uint64_t *w_tile, uint32_t words, MinFlush &flush)
+{
+    float fx[PPT], fy[PPT];
+    Box box;
+    if (!window_all<PPT>(P, T, x, y, z, fx, fy, box))
+        return false;
+    const uint32_t lane = threadIdx.x & 63u;
+    const WaveTile t = wave_tile(P, box);
+    gu64 *gfb = global_ptr(fb);
+    const Range1 R = uniform_range<PW>(P, depth_of(P, T.td, x[0], y[0], z[0]));
+    bool in = true;
+    auto key_of = [&](int j) {
+        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
+        in = in & (d >= R.lo) & (d < R.hi);
+        const double f = floor((d - R.o) * R.s);
+        uint64_t q52 = (uint64_t)__double_as_longlong(f + 0x1p52);
+        if (PW)
+            q52 += R.base;
+        return make_key(q52, c[j]);
+    };
+    if (t.area <= words) {
+        const uint32_t base = lds_addr(w_tile);
+        const uint32_t p0 = tile_pixel(t, lane);
+        uint64_t cur = 0ull;
+        if (lane < t.area)
+            cur = __hip_atomic_load(gfb + p0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool four = 4 * t.area <= words;
+        const uint32_t sh = four ? 5u : 3u;
+        const uint32_t bytes = t.area << sh;
+        u64x2 none;
+        none.x = none.y = ~0ull;
+        if (16 * lane < bytes)
+            *lds_ptr2(base + 16 * lane) = none;
+        for (uint32_t i = 1024 + 16 * lane; i < bytes; i += 1024)
+            *lds_ptr2(base + i) = none;
+        wave_sync();
+        const uint32_t first = tile_first(t, base + (four ? 8 * (lane & 3u) : 0u), sh);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)), key_of(j),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (j % 2)
+                __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+        flush = MinFlush{t, p0, cur, four};
+        if (wave_any(!in)) {
+            arrive(flush.cur);
+            return false;
+        }
+        flush.t.area = t.area;
+        return true;
+    }
+    flush.t.area = 0;
+    // spread too far for the tile: groups of four points, their early-out reads
+    // in flight while their keys are computed.  A point out of range takes no
+    // part here, and then the whole chunk is redone by the caller (a minimum may
+    // be taken twice).
+    constexpr int G = 4;
+    bool all = true;
+#pragma unroll
+    for (int g = 0; g < PPT; g += G) {
+        uint32_t pix[G];
+        uint64_t cur[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            pix[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.width) +
+                     (uint32_t)(int32_t)fx[g + k];
+            cur[k] = __hip_atomic_load(gfb + pix[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            in = true;
+            const uint64_t key = key_of(g + k);
+            all = all & in;
+            if (in & (key < cur[k]))
+                __hip_atomic_fetch_min(gfb + pix[k], key, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return !wave_any(!all);
+}
+
+// Box of the on-screen points of a wave.
+template <int PPT>
+__device__ __forceinline__ Box wave_screen_box(const Proj &P, const Trans &T, const float (&x)[PPT],
+                                               const float (&y)[PPT], const float (&z)[PPT])
+{
+    uint32_t lx = 0xFFFFFFFFu, ly = 0xFFFFFFFFu, hx = 0u, hy = 0u;
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+        float xx = x[j], yy = y[j], zz = z[j], cw, iw;
+        own(xx), own(yy), own(zz);
+        uint32_t px, py;   // 0 for a point off screen, which cannot raise a maximum
+        const bool vis = project(P, T, xx, yy, zz, px, py, cw, iw);
+        lx = min(lx, vis ? px : 0xFFFFFFFFu);
+        ly = min(ly, vis ? py : 0xFFFFFFFFu);
+        hx = max(hx, px);
+        hy = max(hy, py);
+        // this point's work ends here, and with it its registers
+        own(lx), own(ly), own(hx), own(hy);
+    }
+    // no point on screen: lx = ~0 > hx, an empty box
+    return Box{wave_min(lx), wave_min(ly), wave_max(hx), wave_max(hy)};
+}
+
+// raster_chunk_wave for any wave: each point with its own flags.  The points
+// are projected once for the rectangle and again for their keys, so that no
+// array of keys or pixels is held: these waves are few (those across the
+// screen's edge or a range of the depth map), and the registers of this path
+// are those of the whole kernel.
+template <int PPT, bool PW>
+__device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
+                                                uint64_t *__restrict__ fb, const float (&x)[PPT],
+                                                const float (&y)[PPT], const float (&z)[PPT],
+                                                const uint32_t (&c)[PPT], uint64_t *w_tile,
+                                                uint32_t words)
+{
+    const Box box = wave_screen_box<PPT>(P, T, x, y, z);
+    if (box.x0 > box.x1)
+        return;
+    const uint32_t lane = threadIdx.x & 63u;
+    const WaveTile t = wave_tile(P, box);
+    const bool tiled = t.area <= words;
+    const uint32_t base = lds_addr(w_tile);
+    gu64 *gfb = global_ptr(fb);
+    if (tiled) {
+        for (uint32_t i = lane; i < t.area; i += 64)
+            *lds_ptr(base + 8 * i) = ~0ull;
+        wave_sync();
+    }
+    const uint32_t first = tile_first(t, base, 3);
+    constexpr int G = 4;   // early-out reads in flight
+#pragma unroll
+    for (int g = 0; g < PPT; g += G) {
+        uint32_t at[G];   // LDS entry or pixel
+        uint64_t key[G], was[G];
+        bool live[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            float xx = x[g + k], yy = y[g + k], zz = z[g + k];
+            own(xx), own(yy), own(zz);
+            uint32_t px = 0, py = 0;
+            uint64_t q = 0;
+            live[k] = fragment<PW>(P, T, xx, yy, zz, px, py, q);
+            key[k] = (q << 24) | ((uint64_t)c[g + k] & kRgbMask);
+            at[k] = tiled ? ((__umul24(py, t.bw) + px) << 3) + first
+                          : __umul24(py, t.width) + px;
+            own(at[k]);
+        }
+        if (tiled) {
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+                if (live[k])
+                    __hip_atomic_fetch_min(lds_ptr(at[k]), key[k], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else {
+#pragma unroll
+            for (int k = 0; k < G; ++k)   // a discarded fragment reads pixel 0
+                was[k] = __hip_atomic_load(gfb + (live[k] ? at[k] : 0u), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+                if (live[k] && key[k] < was[k])
+                    __hip_atomic_fetch_min(gfb + at[k], key[k], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!tiled)
+        return;
+    wave_sync();
+    for (uint32_t i = lane; i < t.area; i += 64) {
+        const uint64_t v = *lds_ptr(base + 8 * i);
+        if (v != ~0ull) {
+            gu64 *dst = gfb + tile_pixel(t, i);
+            const uint64_t was = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v < was)
+                __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    wave_sync();   // the tile is free for the next use
+}
+
 // Depth pass over one chunk with a private LDS tile per wave: like
 // raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
-// in its own slice of `words` keys (w_tile) and flushes it, so no workgroup
-// barrier is needed.  Same result bits as raster_chunk, for any tile size.
-template <int PPT, bool PW, int ZK = 0>
-__device__ __forceinline__ void raster_chunk_wave(const Proj &P, uint64_t *__restrict__ fb,
+// in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
+// Same result bits as raster_chunk, for any tile size.  Integer depth maps.
+// raster_wave_flush must follow with the same `flush`.  again() puts the points
+// back into x .. c: where it loads them anew, raster_wave_fast need not hold
+// them in registers until it is sure not to give up.
+template <int PPT, bool PW, typename Again>
+__device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
+                                                  uint64_t *__restrict__ fb,
                                                   const float (&x)[PPT], const float (&y)[PPT],
                                                   const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                  const bool (&in)[PPT], uint64_t *w_tile,
-                                                  uint32_t words)
+                                                  uint64_t *w_tile, uint32_t words,
+                                                  MinFlush &flush, const Again &again)
+{
+    if (raster_wave_fast<PPT, PW>(P, T, fb, x, y, z, c, w_tile, words, flush))
+        return;
+    again();
+    flush.t.area = 0;
+    flush.cur = 0;
+    raster_wave_any<PPT, PW>(P, T, fb, x, y, z, c, w_tile, words);
+}
+
+// The same for the float depth encodings (ZK), the flush included.
+template <int PPT, int ZK>
+__device__ __forceinline__ void raster_chunk_wave_zk(const Proj &P, const Trans &T,
+                                                  uint64_t *__restrict__ fb,
+                                                  const float (&x)[PPT], const float (&y)[PPT],
+                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                     uint64_t *w_tile, uint32_t words)
 {
     uint32_t px[PPT], py[PPT], pix[PPT];
     uint64_t key[PPT];
     bool live[PPT];
-    const Trans T = lane_trans(P);
-#pragma unroll
+    #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         uint64_t q = 0;
         uint32_t a = 0, b = 0;
-        live[j] = fragment_enc<PW, ZK>(P, T, x[j], y[j], z[j], a, b, q) & in[j];
+        live[j] = fragment_zk<ZK>(P, T, x[j], y[j], z[j], a, b, q);
         px[j] = a;
         py[j] = b;
         key[j] = (q << 24) | ((uint64_t)c[j] & kRgbMask);
@@ -978,170 +1440,303 @@ __device__ __forceinline__ void accum_chunk(const Proj &P, uint32_t eps_num, uin
     }
 }
 
-// Accumulate pass over one chunk with a private LDS tile per wave of
-// `words` words, one or two per pixel (see raster_chunk_wave and the
-// weights below).  Same result bits as accum_chunk.
-template <int PPT, bool PW>
-__device__ __forceinline__ void accum_chunk_wave(const Proj &P, uint32_t eps_num,
-                                                 uint32_t eps_den,
-                                                 const uint64_t *__restrict__ fb,
-                                                 uint64_t *__restrict__ acc,
-                                                 const float (&x)[PPT], const float (&y)[PPT],
-                                                 const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                 const bool (&in)[PPT], uint64_t *w_tile,
-                                                 uint32_t words)
+// What accum_wave_fast leaves to be flushed: its tile (area 0: nothing) and the
+// pixels of the lane's first entries.
+template <int PPT>
+struct SumFlush {
+    static constexpr int kPre = PPT / 2;   // entries per lane whose depths are read ahead
+    WaveTile t;
+    uint32_t pix[kPre];
+    bool four;
+};
+
+template <int PPT>
+__device__ __forceinline__ void accum_wave_flush(uint64_t *__restrict__ acc, const uint64_t *w_tile,
+                                                 const SumFlush<PPT> &f)
 {
-    uint32_t px[PPT], py[PPT], pix[PPT];
-    uint64_t q[PPT];
-    double tq[PPT];
-    bool ok[PPT];
-    const Trans T = lane_trans(P);
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        uint32_t a = 0, b = 0;
-        uint64_t qq = 0;
-        double t = 0.0;
-        ok[j] = fragment<PW>(P, T, x[j], y[j], z[j], a, b, qq, t) & in[j];
-        px[j] = a;
-        py[j] = b;
-        pix[j] = __umul24(b, (uint32_t)P.width) + a;   // both below 2^15
-        q[j] = qq;
-        tq[j] = t;
-    }
-    uint64_t fbv[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j)
-        fbv[j] = fb[ok[j] ? pix[j] : 0u];
-    if (PW && P.nr != 0) {
-#pragma unroll
-        for (int j = 0; j < PPT; ++j)
-            ok[j] = ok[j] && in_window<PW>(P, eps_num, eps_den, q[j], fbv[j] >> 24);
-    } else if (!P.wfp) {   // linear or scale map, z0 >= 2^52: integer test only
-#pragma unroll
-        for (int j = 0; j < PPT; ++j)
-            ok[j] = ok[j] && in_window<false>(P, eps_num, eps_den, to_u64(tq[j]), fbv[j] >> 24);
-    } else {
-        // the double-precision pre-test of in_window_live(), with q as the
-        // double the fragment floored, and one integer fallback per chunk
-        bool edge[PPT];
-        bool any_edge = false;
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-            const double dm = int52_to_double(fbv[j] >> 24);
-            const double lhs = (double)eps_den * (tq[j] - dm);
-            const double rhs = (double)eps_num * (dm + P.z0d);
-            edge[j] = ok[j] & (lhs == rhs);
-            ok[j] = ok[j] & (lhs < rhs);
-            any_edge = any_edge | edge[j];
-        }
-        if (wave_any(any_edge)) {   // reads the pixels again: rare
-#pragma unroll
-            for (int j = 0; j < PPT; ++j) {
-                const uint64_t qmin = fb[edge[j] ? pix[j] : 0u] >> 24;
-                const bool ex = (uint64_t)eps_den * (to_u64(tq[j]) - qmin) <=
-                                (uint64_t)eps_num * (qmin + P.z0);
-                ok[j] = edge[j] ? ex : ok[j];
-            }
-        }
-    }
-    // Weights.  A wave of at most 512 points (PPT <= 8) adds one packed word
-    // per fragment, R | G << 17 | B << 34 | count << 51: no field of a sum
-    // over the wave can carry into the next (512 * 255 < 2^17, 512 < 2^13),
-    // so the tile holds one word per pixel and each fragment takes one LDS
-    // add; larger waves keep the accumulator's own two words.
-    constexpr bool kPacked = PPT <= 8;
-    constexpr uint32_t kPerPix = kPacked ? 1u : 2u;
-    uint64_t w0[PPT], w1[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        const uint32_t r = c[j] & 0xFFu, g = (c[j] >> 8) & 0xFFu, b = (c[j] >> 16) & 0xFFu;
-        if (kPacked) {
-            w0[j] = ((uint64_t)((b << 2) | (1u << 19)) << 32) | (r | (g << 17));
-            w1[j] = 0;
-        } else {
-            w0[j] = (uint64_t)r | ((uint64_t)g << 32);
-            w1[j] = (uint64_t)b | (1ull << 32);
-        }
-    }
-    // runs of one pixel summed in registers: unlike the depth pass's LDS
-    // minimum, the tile's LDS adds are slower than this merge on runs of
-    // Morton-ordered points.  Only within each group of four consecutive
-    // points: the next group lies 4 * blockDim points further on.
-#pragma unroll
-    for (int j = 1; j < PPT; ++j) {
-        if (j % 4 == 0)
-            continue;
-        const bool same = ok[j] && ok[j - 1] && pix[j] == pix[j - 1];
-        w0[j] += same ? w0[j - 1] : 0ull;
-        if (!kPacked)
-            w1[j] += same ? w1[j - 1] : 0ull;
-        ok[j - 1] = ok[j - 1] && !same;
-    }
-    // the accumulator's two words of a packed sum
-    auto unpack = [](uint64_t w, uint64_t &a0, uint64_t &a1) {
-        a0 = (w & 0x1FFFFull) | (((w >> 17) & 0x1FFFFull) << 32);
-        a1 = ((w >> 34) & 0x1FFFFull) | ((w >> 51) << 32);
-    };
-    const Box box = wave_box_live_min<PPT>(px, py, ok);
-    const uint32_t lane = threadIdx.x & 63u;
-    bool tiled = false;
-    uint32_t bw = 0, bh = 0;
-    if (box.x0 <= box.x1) {
-        bw = box.x1 - box.x0 + 1;
-        bh = box.y1 - box.y0 + 1;
-        tiled = (uint64_t)bw * bh <= words / kPerPix;
-    }
-    if (tiled) {
-        // every accepted fragment of the wave lies in the box (see
-        // raster_chunk_wave)
-        const uint32_t area = bw * bh;
-        const uint32_t org = box.y0 * bw + box.x0;
-        for (uint32_t i = lane; i < kPerPix * area; i += 64)
-            w_tile[i] = 0ull;
-        wave_sync();
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-            if (ok[j]) {
-                uint64_t *t = &w_tile[kPerPix * (__umul24(py[j], bw) + px[j] - org)];
-                __hip_atomic_fetch_add(t, w0[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (!kPacked)
-                    __hip_atomic_fetch_add(t + 1, w1[j], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-        wave_sync();
-        const float inv_bw = 1.0f / (float)bw;
-        for (uint32_t i = lane; i < area; i += 64) {
-            uint64_t a0, a1;
-            if (kPacked) {
-                unpack(w_tile[i], a0, a1);
-            } else {
-                a0 = w_tile[2 * i];
-                a1 = w_tile[2 * i + 1];
-            }
-            if (a1 != 0ull) {   // count > 0
-                uint32_t r, col;
-                tile_rc(i, bw, inv_bw, r, col);
-                uint64_t *dst =
-                    acc + 2 * (uint64_t)(__umul24(box.y0 + r, (uint32_t)P.width) + box.x0 + col);
-                __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        wave_sync();
+    if (f.t.area == 0)
         return;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t base = lds_addr(w_tile), sh = f.four ? 5u : 4u;
+    gu64 *gacc = global_ptr(acc);
+    auto flush = [&](uint32_t i, uint32_t p) {
+        uint64_t a0 = 0, a1 = 0;
+        auto add = [&](uint64_t w) {
+            a0 += (w & 0xFFFFull) | (((w >> 16) & 0xFFFFull) << 32);
+            a1 += ((w >> 32) & 0xFFFFull) | ((w >> 48) << 32);
+        };
+        const u64x2 a = *lds_ptr2(base + (i << sh));
+        if (f.four) {   // pairs hold at most 256 points
+            const u64x2 b = *lds_ptr2(base + (i << sh) + 16);
+            add(a.x + a.y);
+            add(b.x + b.y);
+        } else {
+            add(a.x);
+            add(a.y);
+        }
+        if (a1 != 0ull) {   // count > 0
+            gu64 *dst = gacc + 2 * (uint64_t)p;
+            __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < SumFlush<PPT>::kPre; ++k) {
+        if (k > 0 && f.t.area <= 64u * k)
+            break;
+        if (lane + 64 * k < f.t.area)
+            flush(lane + 64 * k, f.pix[k]);
     }
+    for (uint32_t i = lane + 64 * SumFlush<PPT>::kPre; i < f.t.area; i += 64)
+        flush(i, tile_pixel(f.t, i));
+    wave_sync();   // the tile is free for the next use
+}
+
+// accum_chunk_wave for a wave whose points are all on screen and in one range
+// of a linear or scale map, as raster_wave_fast.  Returns false, with acc
+// untouched, when that does not hold, when the rectangle does not fit the tile,
+// or when the window's products are not exact in double precision (see below).
+//
+// The window test is one comparison per point against a threshold per pixel:
+// den * (q - qmin) <= num * S with S = qmin + z0 holds exactly for the integers
+// q <= qmin + floor(num * S / den).  num * S stays below 2^50 for the eps and z0
+// accepted here, so that the product, the remainder of the estimated quotient
+// and with it the corrected floor are exact.  The thresholds lie in LDS beside
+// the sums: the nearest depths of the rectangle are read in coalesced rows
+// while the depths are computed, instead of one by one.
+//
+// Sums: R | G << 16 | B << 32 | count << 48 in copies of the tile, four where
+// they fit, else two (neighbouring lanes hold neighbouring points, and the LDS
+// adds of one address follow each other one per cycle).  One of two copies, or a
+// pair of the four, takes the points of 32 lanes of at most 8 points:
+// 256 * 255 < 2^16, so no field carries before the fields are unpacked.
+template <int PPT, bool PW>
+__device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, const Eps &eps,
+                                                const uint64_t *__restrict__ fb,
+                                                const float (&x)[PPT], const float (&y)[PPT],
+                                                const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                uint64_t *w_tile, uint32_t words,
+                                                SumFlush<PPT> &flush)
+{
+    static_assert(PPT <= 8, "16-bit fields");
+    if ((PW && P.nr != 0) || eps.num > 256u || eps.den > 4096u || P.z0 > (1ull << 41))
+        return false;
+    float fx[PPT], fy[PPT];
+    Box box;
+    if (!window_all<PPT>(P, T, x, y, z, fx, fy, box))
+        return false;
+    const uint32_t lane = threadIdx.x & 63u;
+    const WaveTile t = wave_tile(P, box);
+    const gu64 *gfb = (const gu64 *)global_ptr(fb);
+    const double num = (double)eps.num, den = (double)eps.den;
+    bool in = true;
+    auto depth_q = [&](int j) {   // q as a double
+        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
+        in = in & (d >= P.dlo[0]) & (d < P.dhi[0]);
+        return floor((d - P.o) * P.s);
+    };
+    if (3 * t.area > words)
+        return false;
+    constexpr int kPre = SumFlush<PPT>::kPre;
+    const uint32_t base = lds_addr(w_tile);
+    const bool four = 5 * t.area <= words;
+    const uint32_t sh = four ? 5u : 4u;
+    const uint32_t thr = base + (t.area << sh);   // the thresholds' LDS address
+    uint32_t pix[kPre] = {};
+    uint64_t near[kPre];
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+        if (k > 0 && t.area <= 64u * k)
+            break;
+        pix[k] = tile_pixel(t, lane + 64 * k);
+        near[k] = lane + 64 * k < t.area ? gfb[pix[k]] : 0ull;
+    }
+    u64x2 zero;
+    zero.x = zero.y = 0ull;
+    for (uint32_t i = 16 * lane; i < (t.area << sh); i += 1024)
+        *lds_ptr2(base + i) = zero;
+    double q[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        if (ok[j]) {
-            uint64_t a0 = w0[j], a1 = w1[j];
-            if (kPacked)
-                unpack(w0[j], a0, a1);
-            uint64_t *a = acc + 2 * (uint64_t)pix[j];
-            __hip_atomic_fetch_add(a, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(a + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        q[j] = depth_q(j);
+        if (j % 2)
+            __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < PPT; ++j)   // not before the depths are there
+        asm volatile("" : "+v"(near[0]) : "v"(q[j]));
+#pragma unroll
+    for (int k = 1; k < kPre; ++k)
+        if (t.area > 64u * k)
+            arrive(near[k]);
+    if (wave_any(!in))
+        return false;
+    auto threshold = [&](uint64_t key) {
+        const double dm = int52_to_double(key >> 24);
+        const double r = num * (dm + P.z0d);
+        const double f = floor(r * eps.inv_den);
+        const double rem = __builtin_fma(-f, den, r);
+        return dm + (rem < 0.0 ? f - 1.0 : rem >= den ? f + 1.0 : f);
+    };
+    typedef __attribute__((address_space(3))) double lf64;
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+        if (k > 0 && t.area <= 64u * k)
+            break;
+        if (lane + 64 * k < t.area)
+            *(lf64 *)(uintptr_t)(thr + 8 * (lane + 64 * k)) = threshold(near[k]);
+    }
+    for (uint32_t i = lane + 64 * kPre; i < t.area; i += 64)
+        *(lf64 *)(uintptr_t)(thr + 8 * i) = threshold(gfb[tile_pixel(t, i)]);
+    wave_sync();
+    const uint32_t sub = lane & (four ? 3u : 1u);
+    const uint32_t first = tile_first(t, base + 8 * sub, sh);
+    const uint32_t tfirst = tile_first(t, thr, 3);
+    constexpr int G = 4;   // thresholds in flight
+#pragma unroll
+    for (int g = 0; g < PPT; g += G) {
+        uint32_t e[G];
+        double most[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            e[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.bw) +
+                   (uint32_t)(int32_t)fx[g + k];
+            most[k] = *(lf64 *)(uintptr_t)((e[k] << 3) + tfirst);
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            if (q[g + k] <= most[k]) {
+                const uint32_t lo = __builtin_amdgcn_perm(1u, c[g + k], 0x0c010c00u);   // R, G
+                const uint32_t hi = __builtin_amdgcn_perm(1u, c[g + k], 0x0c040c02u);   // B, 1
+                __hip_atomic_fetch_add(lds_ptr((e[k] << sh) + first),
+                                       ((uint64_t)hi << 32) | lo, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
         }
     }
+    wave_sync();
+    flush.t = t;
+    flush.four = four;
+#pragma unroll
+    for (int k = 0; k < kPre; ++k)
+        flush.pix[k] = pix[k];
+    return true;
+}
+
+// accum_chunk_wave for any wave: each point with its own flags, as
+// raster_wave_any.  A wave of at most 512 points (PPT <= 8) adds one packed word
+// per fragment, R | G << 17 | B << 34 | count << 51: no field of a sum over the
+// wave can carry into the next (512 * 255 < 2^17, 512 < 2^13); larger waves keep
+// the accumulator's own two words.
+template <int PPT, bool PW>
+__device__ __forceinline__ void accum_wave_any(const Proj &P, const Trans &T, const Eps &eps,
+                                               const uint64_t *__restrict__ fb,
+                                               uint64_t *__restrict__ acc, const float (&x)[PPT],
+                                               const float (&y)[PPT], const float (&z)[PPT],
+                                               const uint32_t (&c)[PPT], uint64_t *w_tile,
+                                               uint32_t words)
+{
+    constexpr bool kPacked = PPT <= 8;
+    constexpr uint32_t kSh = kPacked ? 3u : 4u;   // bytes per pixel, log2
+    const Box box = wave_screen_box<PPT>(P, T, x, y, z);
+    if (box.x0 > box.x1)
+        return;
+    const uint32_t lane = threadIdx.x & 63u;
+    const WaveTile t = wave_tile(P, box);
+    const bool tiled = (t.area << kSh) <= 8 * words;
+    const uint32_t base = lds_addr(w_tile);
+    const gu64 *gfb = (const gu64 *)global_ptr(fb);
+    gu64 *gacc = global_ptr(acc);
+    auto add_pixel = [&](uint32_t p, uint64_t a0, uint64_t a1) {
+        gu64 *dst = gacc + 2 * (uint64_t)p;
+        __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (tiled) {
+        for (uint32_t i = lane; i < (t.area << (kSh - 3)); i += 64)
+            *lds_ptr(base + 8 * i) = 0ull;
+        wave_sync();
+    }
+    const uint32_t first = tile_first(t, base, kSh);
+    constexpr int G = 4;   // nearest depths in flight
+#pragma unroll
+    for (int g = 0; g < PPT; g += G) {
+        uint32_t px[G], py[G];
+        uint64_t q[G], near[G];
+        bool ok[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            float xx = x[g + k], yy = y[g + k], zz = z[g + k];
+            own(xx), own(yy), own(zz);
+            px[k] = py[k] = 0;
+            q[k] = 0;
+            ok[k] = fragment<PW>(P, T, xx, yy, zz, px[k], py[k], q[k]);
+            // a discarded fragment reads pixel 0
+            near[k] = gfb[ok[k] ? __umul24(py[k], t.width) + px[k] : 0u];
+            if (k % 2)
+                __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            const bool in = in_window_live<PW>(P, eps.num, eps.den, q[k], near[k] >> 24, ok[k]);
+            const uint32_t col = c[g + k];
+            const uint32_t cr = col & 0xFFu, cg = (col >> 8) & 0xFFu, cb = (col >> 16) & 0xFFu;
+            if (in) {
+                lu64 *w = lds_ptr(((__umul24(py[k], t.bw) + px[k]) << kSh) + first);
+                const uint64_t a0 = (uint64_t)cr | ((uint64_t)cg << 32);
+                const uint64_t a1 = (uint64_t)cb | (1ull << 32);
+                if (!tiled) {
+                    add_pixel(__umul24(py[k], t.width) + px[k], a0, a1);
+                } else if (kPacked) {
+                    const uint64_t one = ((uint64_t)((cb << 2) | (1u << 19)) << 32) |
+                                         (cr | (cg << 17));
+                    __hip_atomic_fetch_add(w, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                } else {
+                    __hip_atomic_fetch_add(w, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __hip_atomic_fetch_add(w + 1, a1, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!tiled)
+        return;
+    wave_sync();
+    for (uint32_t i = lane; i < t.area; i += 64) {
+        const uint64_t w = *lds_ptr(base + (i << kSh));
+        uint64_t a0 = w, a1;
+        if (kPacked) {
+            a0 = (w & 0x1FFFFull) | (((w >> 17) & 0x1FFFFull) << 32);
+            a1 = ((w >> 34) & 0x1FFFFull) | ((w >> 51) << 32);
+        } else {
+            a1 = *lds_ptr(base + (i << kSh) + 8);
+        }
+        if (a1 != 0ull)   // count > 0
+            add_pixel(tile_pixel(t, i), a0, a1);
+    }
+    wave_sync();   // the tile is free for the next use
+}
+
+// Accumulate pass over one chunk with a private LDS tile per wave of `words`
+// words (see raster_chunk_wave).  Same result bits as accum_chunk.
+// accum_wave_flush must follow with the same `flush`; again() as there.
+template <int PPT, bool PW, typename Again>
+__device__ __forceinline__ void accum_chunk_wave(const Proj &P, const Trans &T, const Eps &eps,
+                                                 const uint64_t *__restrict__ fb,
+                                                 uint64_t *__restrict__ acc, const float (&x)[PPT],
+                                                 const float (&y)[PPT], const float (&z)[PPT],
+                                                 const uint32_t (&c)[PPT], uint64_t *w_tile,
+                                                 uint32_t words, SumFlush<PPT> &flush,
+                                                 const Again &again)
+{
+    if constexpr (PPT <= 8) {
+        if (accum_wave_fast<PPT, PW>(P, T, eps, fb, x, y, z, c, w_tile, words, flush))
+            return;
+        again();
+    }
+    flush.t.area = 0;
+    accum_wave_any<PPT, PW>(P, T, eps, fb, acc, x, y, z, c, w_tile, words);
 }
 
 // Colour of one pixel from its packed splat sums (section 2.2, third pass):

@@ -29,6 +29,10 @@ struct Proj {
     double rs[8];         // values per unit
     double rinv[8];       // 1 / rs
     uint64_t rbase[9];    // first integer of each range; rbase[nr] = 2^40 - 1
+    // Range k of the depth map (0 for the linear and scale maps): a depth in
+    // [dlo[k], dhi[k]) is in [near, far), lies in the range and has a q of at
+    // most 2^40 - 2 without the clamp.
+    double dlo[8], dhi[8];
     double z0d;           // z0 as a double (exact when wfp is set)
     int32_t wfp;          // z0 < 2^52: the eps window may be pre-tested in double
     int32_t pad2_;
@@ -47,6 +51,12 @@ struct Tune {
 };
 
 constexpr Tune kHqTune = {64, 8, 1, 0, 3};
+
+// The splat window's eps = num / den, with 1 / den rounded once.
+struct Eps {
+    uint32_t num, den;
+    double inv_den;
+};
 
 constexpr uint64_t kDepthOnes = 0xFFFFFFFFFF000000ull;
 constexpr uint64_t kRgbMask = 0xFFFFFFull;
@@ -79,7 +89,7 @@ struct MvView {
     Proj P;
     uint64_t *fb;
     uint64_t *acc;
-    uint32_t eps_num, eps_den;
+    Eps eps;
 };
 constexpr int kMaxGroupViews = 8;   // views per multi-view launch
 

@@ -33,17 +33,20 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
     float x[PPT], y[PPT], z[PPT];
     uint32_t c[PPT];
     bool in[PPT];
-    const int64_t base = chunk * (int64_t)blockDim.x * PPT;
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
     // no per-point bounds flags: points past the end load as NaN and are culled
-    load_points_nan<PPT>(p, base, x, y, z, c);
+    auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
+    load();
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
-    if (BIN == kBinWave)
-        raster_chunk_wave<PPT, PW>(P, fb, x, y, z, c, in, w_tile, words);
-    else
+    if (BIN == kBinWave) {
+        MinFlush flush;
+        raster_chunk_wave<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load);
+        raster_wave_flush(fb, w_tile, flush);
+    } else {
         raster_chunk<PPT, EARLY, BIN == kBinBlock, PW>(P, fb, x, y, z, c, in, s_tile, s_box);
+    }
 }
 
 // Depth pass for the float depth encodings (RZ_DEPTH_GL24, RZ_DEPTH_F32REV)
@@ -59,19 +62,14 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
         return;
     float x[PPT], y[PPT], z[PPT];
     uint32_t c[PPT];
-    bool in[PPT];
     load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
-#pragma unroll
-    for (int j = 0; j < PPT; ++j)
-        in[j] = true;
-    raster_chunk_wave<PPT, false, ZK>(P, fb, x, y, z, c, in,
-                                      s_waves + (threadIdx.x >> 6) * words, words);
+    raster_chunk_wave_zk<PPT, ZK>(P, lane_trans(P), fb, x, y, z, c,
+                                  s_waves + (threadIdx.x >> 6) * words, words);
 }
 
 // Accumulation pass of section 2.2 for one view.
 template <int PPT, bool XCD, int BIN, bool PW>
-__global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, uint32_t eps_num,
-                                                  uint32_t eps_den,
+__global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, Eps eps,
                                                   const uint64_t *__restrict__ fb,
                                                   uint64_t *__restrict__ acc, int64_t nchunks,
                                                   uint32_t words)
@@ -85,17 +83,22 @@ __global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, uint32_t eps_nu
     float x[PPT], y[PPT], z[PPT];
     uint32_t c[PPT];
     bool in[PPT];
-    const int64_t base = chunk * (int64_t)blockDim.x * PPT;
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
-    load_points_nan<PPT>(p, base, x, y, z, c);
+    // no per-point bounds flags: points past the end load as NaN and are culled
+    auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
+    load();
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
-    if (BIN == kBinWave)
-        accum_chunk_wave<PPT, PW>(P, eps_num, eps_den, fb, acc, x, y, z, c, in, w_tile, words);
-    else
-        accum_chunk<PPT, BIN == kBinBlock, PW>(P, eps_num, eps_den, fb, acc, x, y, z, c, in,
+    if (BIN == kBinWave) {
+        SumFlush<PPT> flush;
+        accum_chunk_wave<PPT, PW>(P, lane_trans(P), eps, fb, acc, x, y, z, c, w_tile, words, flush,
+                                  load);
+        accum_wave_flush<PPT>(acc, w_tile, flush);
+    } else {
+        accum_chunk<PPT, BIN == kBinBlock, PW>(P, eps.num, eps.den, fb, acc, x, y, z, c, in,
                                                s_tile, s_box);
+    }
 }
 
 // Resolve of section 2.1: colour bits to the image, framebuffer cleared.
@@ -171,10 +174,10 @@ bool aligned16(const void *ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 int64_t blocks_for(int64_t n, int64_t per) { return (n + per - 1) / per; }
 
 // Dynamic LDS of a launch: the per-wave tiles of kBinWave / kBinWaveSmall.
-size_t wave_lds(int bin, int block)
+size_t wave_lds(int bin, int block, bool hq)
 {
     return bin == kBinWave || bin == kBinWaveSmall
-               ? (size_t)(block / 64) * wave_tile_words(bin) * sizeof(uint64_t)
+               ? (size_t)(block / 64) * wave_tile_words(bin, hq) * sizeof(uint64_t)
                : 0;
 }
 
@@ -183,8 +186,8 @@ hipError_t raster_min_ppt(const Pts &p, const Proj &P, uint64_t *fb, const Tune 
                           hipStream_t s)
 {
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * PPT);
-    const size_t lds = wave_lds(t.bin, t.block);
-    const uint32_t words = wave_tile_words(t.bin);
+    const size_t lds = wave_lds(t.bin, t.block, false);
+    const uint32_t words = wave_tile_words(t.bin, false);
     if (t.xcd_remap) {
         const int64_t grid = (nchunks + kXcds - 1) / kXcds * kXcds;
         hipLaunchKernelGGL((k_raster_min<PPT, EARLY, true, BIN, PW>), dim3((uint32_t)grid),
@@ -198,19 +201,18 @@ hipError_t raster_min_ppt(const Pts &p, const Proj &P, uint64_t *fb, const Tune 
 }
 
 template <int PPT, int BIN, bool PW>
-hipError_t hq_accum_ppt(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
-                        const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
+hipError_t hq_accum_ppt(const Pts &p, const Proj &P, const Eps &eps, const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
 {
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * PPT);
-    const size_t lds = wave_lds(t.bin, t.block);
-    const uint32_t words = wave_tile_words(t.bin);
+    const size_t lds = wave_lds(t.bin, t.block, true);
+    const uint32_t words = wave_tile_words(t.bin, true);
     if (t.xcd_remap) {
         const int64_t grid = (nchunks + kXcds - 1) / kXcds * kXcds;
         hipLaunchKernelGGL((k_hq_accum<PPT, true, BIN, PW>), dim3((uint32_t)grid),
-                           dim3(t.block), lds, s, p, P, num, den, fb, acc, nchunks, words);
+                           dim3(t.block), lds, s, p, P, eps, fb, acc, nchunks, words);
     } else {
         hipLaunchKernelGGL((k_hq_accum<PPT, false, BIN, PW>), dim3((uint32_t)nchunks),
-                           dim3(t.block), lds, s, p, P, num, den, fb, acc, nchunks, words);
+                           dim3(t.block), lds, s, p, P, eps, fb, acc, nchunks, words);
     }
     return hipGetLastError();
 }
@@ -238,32 +240,32 @@ hipError_t raster_min_dispatch(const Pts &p, const Proj &P, uint64_t *fb, const 
 }
 
 template <int PPT, bool PW>
-hipError_t hq_accum_bin(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
+hipError_t hq_accum_bin(const Pts &p, const Proj &P, const Eps &eps,
                         const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
 {
     switch (t.bin) {
-    case kBinBlock: return hq_accum_ppt<PPT, kBinBlock, PW>(p, P, num, den, fb, acc, t, s);
+    case kBinBlock: return hq_accum_ppt<PPT, kBinBlock, PW>(p, P, eps, fb, acc, t, s);
     case kBinWave:
     case kBinWaveSmall:
-        return hq_accum_ppt<PPT, kBinWave, PW>(p, P, num, den, fb, acc, t, s);
-    default: return hq_accum_ppt<PPT, kBinNone, PW>(p, P, num, den, fb, acc, t, s);
+        return hq_accum_ppt<PPT, kBinWave, PW>(p, P, eps, fb, acc, t, s);
+    default: return hq_accum_ppt<PPT, kBinNone, PW>(p, P, eps, fb, acc, t, s);
     }
 }
 
 template <int PPT>
-hipError_t hq_accum_dispatch(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
+hipError_t hq_accum_dispatch(const Pts &p, const Proj &P, const Eps &eps,
                              const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
 {
-    return P.nr ? hq_accum_bin<PPT, true>(p, P, num, den, fb, acc, t, s)
-                : hq_accum_bin<PPT, false>(p, P, num, den, fb, acc, t, s);
+    return P.nr ? hq_accum_bin<PPT, true>(p, P, eps, fb, acc, t, s)
+                : hq_accum_bin<PPT, false>(p, P, eps, fb, acc, t, s);
 }
 
 template <int ZK>
 hipError_t raster_min_zk(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t, hipStream_t s)
 {
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * 16);
-    const size_t lds = wave_lds(t.bin, t.block);
-    const uint32_t words = wave_tile_words(t.bin);
+    const size_t lds = wave_lds(t.bin, t.block, false);
+    const uint32_t words = wave_tile_words(t.bin, false);
     hipLaunchKernelGGL((k_raster_min_zk<ZK>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
                        fb, nchunks, words);
     return hipGetLastError();
@@ -300,10 +302,11 @@ hipError_t launch_hq_accum(const Pts &p, const Proj &P, uint32_t num, uint32_t d
     Range r("rz splat accumulate pass");
     if (p.n == 0)
         return hipSuccess;
+    const Eps eps{num, den, 1.0 / (double)den};
     switch (t.ppt) {
-    case 4: return hq_accum_dispatch<4>(p, P, num, den, fb, acc, t, s);
-    case 8: return hq_accum_dispatch<8>(p, P, num, den, fb, acc, t, s);
-    case 16: return hq_accum_dispatch<16>(p, P, num, den, fb, acc, t, s);
+    case 4: return hq_accum_dispatch<4>(p, P, eps, fb, acc, t, s);
+    case 8: return hq_accum_dispatch<8>(p, P, eps, fb, acc, t, s);
+    case 16: return hq_accum_dispatch<16>(p, P, eps, fb, acc, t, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -321,8 +321,7 @@ int launch_group(rz_server *s, const std::vector<Req *> &g)
         m.P = r->P;
         m.fb = fb;
         m.acc = acc;
-        m.eps_num = r->num;
-        m.eps_den = r->den;
+        m.eps = Eps{r->num, r->den, 1.0 / (double)r->den};
         stage[nv++] = m;
         pw = pw || r->P.nr > 0;
         if (r->r.mode == RZ_MODE_HQ) {

@@ -52,3 +52,90 @@ def test_planes_at_any_dword_offset(rz, oracle, offs):
                                     point_size=2)
     fb2, _, _, _ = rz.rasterize_points(pts, v, point_size=2, keep_keys=True)
     assert np.array_equal(rz.to_u64(fb2), k2)
+
+
+def rectangle_scene(w, h, n, seed, W=400, H=300, ox=37, oy=21, outside=0, behind=0,
+                    pile=False):
+    """n points over a w x h pixel rectangle (its corners in every 64 points),
+    most of them white, depths spread over a few eps windows; `outside` points
+    beyond far and `behind` points behind the camera in the middle of the cloud;
+    pile: all points but the corners in one pixel, within one window."""
+    rng = np.random.default_rng(seed)
+    px, py = ox + rng.integers(0, w, n), oy + rng.integers(0, h, n)
+    if pile:
+        px[:], py[:] = ox, oy
+    k = np.arange(n) % 64
+    px[k == 3], py[k == 3] = ox, oy
+    px[k == 40], py[k == 40] = ox + w - 1, oy + h - 1
+    z = (rng.choice([2.0, 2.01, 2.02, 2.5], n) * rng.uniform(1.0, 1.004, n)).astype(np.float32)
+    if pile:
+        z[:] = 2.0
+    m = n // 2
+    z[m:m + outside] = 60.0
+    x = ((2 * (px + 0.5) / W - 1) * z).astype(np.float32)
+    y = ((2 * (py + 0.5) / H - 1) * z).astype(np.float32)
+    z[m + 100:m + 100 + behind] *= -1
+    vp = np.zeros((4, 4))
+    vp[0, 0] = vp[1, 1] = vp[3, 2] = 1.0   # clip = (x, y, ., z)
+    vp[2, 2] = 1.0
+    rgb = np.full(n, 0xFFFFFF, np.uint32)
+    if not pile:
+        rgb[::5] = rng.integers(0, 1 << 24, rgb[::5].size)
+    return gen.Cloud(x, y, z, rgb), gen.View(vp, 0.5, 50.0, W, H)
+
+
+TILES = [(1, 1), (2, 1), (8, 8), (64, 1), (65, 1), (13, 10), (51, 3), (14, 11), (16, 16), (257, 1),
+         (32, 32), (41, 25)]
+
+
+@pytest.mark.parametrize("wh", TILES)
+@pytest.mark.parametrize("shape", [None, (64, 4, 1, 0, 3), (128, 8, 1, 0, 2), (64, 16, 1, 0, 3)])
+def test_wave_tiles(rz, oracle, wh, shape):
+    """Waves whose points are all on screen, over rectangles on both sides of
+    every limit of the LDS tile (one pixel, one and several lanes' worth of
+    entries, four, two and one copy, none): keys, sums and images."""
+    cases = [dict(), dict(outside=3), dict(behind=2), dict(pile=True)]
+    for i, kw in enumerate(cases):
+        c, v = rectangle_scene(*wh, n=2500, seed=i, **kw)
+        keys, img, sums, himg = full_render(oracle, c, v, bg=0x204060)
+        pts = rz.Points.from_cloud(c)
+        rz.reset_launch() if shape is None else rz.set_launch(*shape)
+        try:
+            fb, _ = rz.rasterize_atomicmin(pts, v, keep_keys=True, background=0x204060)
+            assert np.array_equal(rz.to_u64(fb), keys), (wh, kw)
+            _, acc, _, _ = rz.rasterize_hq_splat(pts, v, keep_keys=True, background=0x204060)
+            assert np.array_equal(rz.unpack_acc(acc), sums), (wh, kw)
+            _, _, got, st = rz.rasterize_hq_splat(pts, v, background=0x204060)
+            assert np.array_equal(rz.to_u32(got), himg) and int(st.item()) == 0
+            launch = None if shape is None else shape
+            b = rz.Batch(pts, [v] * 3, [0, 1, 1], backgrounds=[0x204060] * 3, launch=launch)
+            b.run()
+            got = b.images()
+            assert np.array_equal(got[0], img) and all(np.array_equal(g, himg) for g in got[1:])
+        finally:
+            rz.reset_launch()
+
+
+@pytest.mark.parametrize("depth", [(0, 0.0), (1, 1000.0), (1, 2.0 ** 40 / 51.0),
+                                   (2, ((0.0, 1e9), (2.015, 1e6), (10.0, 1e3))),
+                                   (2, ((0.0, 1e9), (10.0, 1e6)))])
+@pytest.mark.parametrize("eps", [(1, 100), (0, 1), (1, 3), (256, 4096), (257, 4096), (1, 4097),
+                                 (1048576, 1)])
+def test_wave_windows(rz, oracle, depth, eps):
+    """The splat window per pixel: eps on both sides of the exact range, eps = 0,
+    windows of many quanta and of less than one, piecewise maps whose ranges
+    split a wave."""
+    c, v = rectangle_scene(9, 7, 2000, 5)
+    try:
+        fbk, sums, himg = oracle.render_hq(c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width,
+                                           v.height, depth[0], depth[1], eps=eps)
+    except Exception as e:   # the oracle refuses what the interface refuses
+        with pytest.raises(rz.RzError):
+            rz.rasterize_hq_splat(rz.Points.from_cloud(c), v, depth=depth, eps=eps)
+        pytest.skip(f"refused by both: {e}")
+    pts = rz.Points.from_cloud(c)
+    fb, acc, _, _ = rz.rasterize_hq_splat(pts, v, depth=depth, eps=eps, keep_keys=True)
+    assert np.array_equal(rz.to_u64(fb), fbk)
+    assert np.array_equal(rz.unpack_acc(acc), sums)
+    _, _, img, _ = rz.rasterize_hq_splat(pts, v, depth=depth, eps=eps)
+    assert np.array_equal(rz.to_u32(img), himg)
