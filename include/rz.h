@@ -325,8 +325,9 @@ typedef struct rz_launch {
 /* Sets the launch shape of both point passes of the one-view calls and the
    server (RZ_EINVAL if out of range); NULL restores the library defaults
    (depth pass 64 threads x 16 points with the 8 KiB per-wave tile, splat
-   pass 64 x 8 with the small per-wave tile, early-out, no XCD remap).
-   rz_get_launch reports the depth pass's shape.
+   pass 64 x 8 with the small per-wave tile, both 256 x 4 with the small tile
+   for clouds of fewer than 2^23 points; early-out, no XCD remap).  rz_get_launch
+   reports the depth pass's shape for large clouds.
    Thread-safe: a call running concurrently launches with either the old
    or the new shape, and both give the same result. */
 int rz_set_launch(const rz_launch *launch);

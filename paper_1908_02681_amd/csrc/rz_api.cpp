@@ -370,6 +370,7 @@ int rz_set_launch(const rz_launch *l)
     g_tune.early_out = l->early_out;
     g_tune.xcd_remap = l->xcd_remap;
     g_tune.bin = l->bin;
+    g_tune.by_size = 0;
     g_tune_hq = g_tune;
     return RZ_OK;
 }

@@ -431,18 +431,18 @@ __device__ __forceinline__ void load_full(const Pts &p, int64_t base, float (&x)
                                           float (&y)[PPT], float (&z)[PPT], uint32_t (&c)[PPT])
 {
     const int64_t stride = 4 * (int64_t)blockDim.x;
-    const uint32_t lane = 4 * threadIdx.x;   // beside a base that the whole workgroup shares
+    const int64_t first = base + 4 * (int64_t)threadIdx.x;
 #pragma unroll
     for (int g = 0; g < PPT / 4; ++g) {
-        const int64_t i = base + g * stride;
+        const int64_t i = first + g * stride;
         const f32x4 vx =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.x + i + lane));
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.x + i));
         const f32x4 vy =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.y + i + lane));
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.y + i));
         const f32x4 vz =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.z + i + lane));
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p.z + i));
         const u32x4 vc =
-            __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p.rgb + i + lane));
+            __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p.rgb + i));
         x[4 * g + 0] = vx.x; x[4 * g + 1] = vx.y; x[4 * g + 2] = vx.z; x[4 * g + 3] = vx.w;
         y[4 * g + 0] = vy.x; y[4 * g + 1] = vy.y; y[4 * g + 2] = vy.z; y[4 * g + 3] = vy.w;
         z[4 * g + 0] = vz.x; z[4 * g + 1] = vz.y; z[4 * g + 2] = vz.z; z[4 * g + 3] = vz.w;
@@ -830,11 +830,11 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
     return v;
 }
 
-// Window positions of a wave's points, all of them inside the screen: true,
-// with their pixel rectangle, when every point of the wave has a w in
-// [2^-126, 2^126) and an on-screen window position; false (and the rest
-// meaningless) otherwise.  The common case of a chunk of an ordered cloud: it
-// needs no flag per point.  The tests run on bit patterns, where the order of
+// Window positions of a wave's points: kOnScreen, with their pixel rectangle,
+// when every point of the wave has a w in [2^-126, 2^126) and an on-screen window
+// position; kOffScreen when all lie beyond one edge of the screen; kMixed (and
+// the rest meaningless) otherwise.  The first two are nearly all chunks of an
+// ordered cloud, and need no flag per point.  The tests run on bit patterns, where the order of
 // non-negative floats is that of the integers and every other value (negative,
 // NaN, infinite) falls outside: w through an unsigned minimum and maximum, x
 // and y through signed ones.
@@ -844,8 +844,10 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
 // the even rows and the complemented maxima into the odd ones, and one 16-lane
 // reduction finishes all four: 11 instructions where four 64-lane reductions
 // take 24.
+enum Where { kOnScreen, kOffScreen, kMixed };
+
 template <int PPT>
-__device__ __forceinline__ bool window_all(const Proj &P, const Trans &T, const float (&x)[PPT],
+__device__ __forceinline__ Where window_all(const Proj &P, const Trans &T, const float (&x)[PPT],
                                            const float (&y)[PPT], const float (&z)[PPT],
                                            float (&fx)[PPT], float (&fy)[PPT], Box &box)
 {
@@ -880,16 +882,17 @@ __device__ __forceinline__ bool window_all(const Proj &P, const Trans &T, const 
     const uint32_t lane = threadIdx.x & 63u;
     const bool odd = (lane & 16u) != 0;
     const int32_t size = (lane & 32u) ? __float_as_int(P.fh) : __float_as_int(P.fw);
+    if (wave_any((wlo < 0x00800000u) | (whi >= 0x7E800000u)))
+        return kMixed;
     // even rows: minimum >= 0; odd rows: maximum < size, on the complement
-    const bool ok = (wlo >= 0x00800000u) & (whi < 0x7E800000u) & (m >= (odd ? -size : 0));
-    if (wave_any(!ok))
-        return false;
+    if (wave_any(m < (odd ? -size : 0)))
+        return wave_any(m >= (odd ? 0 : size)) ? kOffScreen : kMixed;
     const int32_t px = (int32_t)__int_as_float(odd ? ~m : m);
     box.x0 = (uint32_t)__builtin_amdgcn_readlane(px, 0);
     box.x1 = (uint32_t)__builtin_amdgcn_readlane(px, 16);
     box.y0 = (uint32_t)__builtin_amdgcn_readlane(px, 32);
     box.y1 = (uint32_t)__builtin_amdgcn_readlane(px, 48);
-    return true;
+    return kOnScreen;
 }
 
 // One uniform range of the depth map for a whole chunk: the linear and scale
@@ -963,151 +966,6 @@ __device__ __forceinline__ uint32_t tile_first(const WaveTile &t, uint32_t base,
     uint32_t v = base - ((t.y0 * t.bw + t.x0) << sh);
     asm("" : "+v"(v));
     return v;
-}
-
-// What raster_wave_fast leaves to be flushed: its tile (area 0: nothing), and
-// of the lane's first entry the pixel and the nearest key read before.
-struct MinFlush {
-    WaveTile t;
-    uint32_t p0;
-    uint64_t cur;
-    bool four;
-};
-
-// The flush: one coalesced global atomic per touched pixel whose nearest key
-// it lowers.
-__device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, const uint64_t *w_tile,
-                                                  MinFlush &f)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t base = lds_addr(w_tile);
-    gu64 *gfb = global_ptr(fb);
-    arrive(f.cur);
-    if (f.t.area == 0)
-        return;
-    auto nearest = [&](uint32_t i) -> uint64_t {   // of entry i of the tile
-        if (!f.four)
-            return *lds_ptr(base + 8 * i);
-        const u64x2 a = *lds_ptr2(base + 32 * i), b = *lds_ptr2(base + 32 * i + 16);
-        const uint64_t m = a.x < a.y ? a.x : a.y, n = b.x < b.y ? b.x : b.y;
-        return m < n ? m : n;
-    };
-    if (lane < f.t.area) {
-        const uint64_t v = nearest(lane);
-        if (v < f.cur)
-            __hip_atomic_fetch_min(gfb + f.p0, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    for (uint32_t i = lane + 64; i < f.t.area; i += 64) {
-        const uint64_t v = nearest(i);
-        if (v != ~0ull) {
-            gu64 *dst = gfb + tile_pixel(f.t, i);
-            const uint64_t was = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (v < was)
-                __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    wave_sync();   // the tile is free for the next use
-}
-
-// raster_chunk_wave for a wave whose points are all on screen and, as it turns
-// out, in one range of the depth map and in [near, far): no flag per point, and
-// neither the clamp nor the test for a slow reciprocal.  Returns false, with
-// fb untouched or holding nothing but keys of the wave, when that does not
-// hold.  The nearest keys that the flush compares with are read before the
-// depths are computed, so that their latency passes meanwhile (a key read early
-// is an upper bound of the later one).
-//
-// A tile that fits four times is kept four times, lane i taking copy i & 3:
-// neighbouring lanes hold neighbouring points, and LDS atomics of one address
-// follow each other one per cycle (a depth pass of 100M points over 8 views:
-// 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
-template <int PPT, bool PW>
-__device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
-                                                 uint64_t *__restrict__ fb,
-                                                 const float (&x)[PPT], const float (&y)[PPT],
-                                                 const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                 uint64_t *w_tile, uint32_t words, MinFlush &flush)
-{
-    float fx[PPT], fy[PPT];
-    Box box;
-    if (!window_all<PPT>(P, T, x, y, z, fx, fy, box))
-        return false;
-    const uint32_t lane = threadIdx.x & 63u;
-    const WaveTile t = wave_tile(P, box);
-    gu64 *gfb = global_ptr(fb);
-    const Range1 R = uniform_range<PW>(P, depth_of(P, T.td, x[0], y[0], z[0]));
-    bool in = true;
-    auto key_of = [&](int j) {
-        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
-        in = in & (d >= R.lo) & (d < R.hi);
-        const double f = floor((d - R.o) * R.s);
-        uint64_t q52 = (uint64_t)__double_as_longlong(f + 0x1p52);
-        if (PW)
-            q52 += R.base;
-        return make_key(q52, c[j]);
-    };
-    if (t.area <= words) {
-        const uint32_t base = lds_addr(w_tile);
-        const uint32_t p0 = tile_pixel(t, lane);
-        uint64_t cur = 0ull;
-        if (lane < t.area)
-            cur = __hip_atomic_load(gfb + p0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool four = 4 * t.area <= words;
-        const uint32_t sh = four ? 5u : 3u;
-        const uint32_t bytes = t.area << sh;
-        u64x2 none;
-        none.x = none.y = ~0ull;
-        if (16 * lane < bytes)
-            *lds_ptr2(base + 16 * lane) = none;
-        for (uint32_t i = 1024 + 16 * lane; i < bytes; i += 1024)
-            *lds_ptr2(base + i) = none;
-        wave_sync();
-        const uint32_t first = tile_first(t, base + (four ? 8 * (lane & 3u) : 0u), sh);
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-            __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)), key_of(j),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (j % 2)
-                __builtin_amdgcn_sched_barrier(0);
-        }
-        wave_sync();
-        flush = MinFlush{t, p0, cur, four};
-        if (wave_any(!in)) {
-            arrive(flush.cur);
-            return false;
-        }
-        flush.t.area = t.area;
-        return true;
-    }
-    flush.t.area = 0;
-    // spread too far for the tile: groups of four points, their early-out reads
-    // in flight while their keys are computed.  A point out of range takes no
-    // part here, and then the whole chunk is redone by the caller (a minimum may
-    // be taken twice).
-    constexpr int G = 4;
-    bool all = true;
-#pragma unroll
-    for (int g = 0; g < PPT; g += G) {
-        uint32_t pix[G];
-        uint64_t cur[G];
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            pix[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.width) +
-                     (uint32_t)(int32_t)fx[g + k];
-            cur[k] = __hip_atomic_load(gfb + pix[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            in = true;
-            const uint64_t key = key_of(g + k);
-            all = all & in;
-            if (in & (key < cur[k]))
-                __hip_atomic_fetch_min(gfb + pix[k], key, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    return !wave_any(!all);
 }
 
 // Box of the on-screen points of a wave.
@@ -1211,13 +1069,162 @@ __device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
     wave_sync();   // the tile is free for the next use
 }
 
+// What raster_chunk_wave leaves to be flushed: its tile (area 0: nothing), and
+// of the lane's first entry the pixel and the nearest key read before.
+struct MinFlush {
+    WaveTile t;
+    uint32_t p0;
+    uint64_t cur;
+    bool four;
+};
+
+// The flush: one coalesced global atomic per touched pixel whose nearest key
+// it lowers.
+__device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, const uint64_t *w_tile,
+                                                  MinFlush &f)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t base = lds_addr(w_tile);
+    gu64 *gfb = global_ptr(fb);
+    arrive(f.cur);
+    if (f.t.area == 0)
+        return;
+    auto nearest = [&](uint32_t i) -> uint64_t {   // of entry i of the tile
+        if (!f.four)
+            return *lds_ptr(base + 8 * i);
+        const u64x2 a = *lds_ptr2(base + 32 * i), b = *lds_ptr2(base + 32 * i + 16);
+        const uint64_t m = a.x < a.y ? a.x : a.y, n = b.x < b.y ? b.x : b.y;
+        return m < n ? m : n;
+    };
+    if (lane < f.t.area) {
+        const uint64_t v = nearest(lane);
+        if (v < f.cur)
+            __hip_atomic_fetch_min(gfb + f.p0, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (uint32_t i = lane + 64; i < f.t.area; i += 64) {
+        const uint64_t v = nearest(i);
+        if (v != ~0ull) {
+            gu64 *dst = gfb + tile_pixel(f.t, i);
+            const uint64_t was = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v < was)
+                __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    wave_sync();   // the tile is free for the next use
+}
+
 // Depth pass over one chunk with a private LDS tile per wave: like
 // raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
 // in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
 // Same result bits as raster_chunk, for any tile size.  Integer depth maps.
-// raster_wave_flush must follow with the same `flush`.  again() puts the points
-// back into x .. c: where it loads them anew, raster_wave_fast need not hold
-// them in registers until it is sure not to give up.
+// raster_wave_flush must follow with the same `flush`.
+//
+// A wave whose points are all on screen and, as it turns out, in one range of
+// the depth map and in [near, far) needs no flag per point, and neither the
+// clamp nor the test for a slow reciprocal; every other one takes
+// raster_wave_any, for which again() puts the points back into x .. c: where it
+// loads them anew (they are in the L2 then), they need not be held in registers
+// till it is known (16 points a thread: 122 registers, 158 with them).
+//
+// The nearest keys that the flush compares with are read before the depths are
+// computed, so that their latency passes meanwhile (a key read early is an upper
+// bound of the later one).
+//
+// A tile that fits four times is kept four times, lane i taking copy i & 3:
+// neighbouring lanes hold neighbouring points, and LDS atomics of one address
+// follow each other one per cycle (a depth pass of 100M points over 8 views:
+// 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
+template <int PPT, bool PW>
+__device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
+                                                 uint64_t *__restrict__ fb,
+                                                 const float (&x)[PPT], const float (&y)[PPT],
+                                                 const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                 uint64_t *w_tile, uint32_t words, MinFlush &flush)
+{
+    float fx[PPT], fy[PPT];
+    Box box;
+    flush.t.area = 0;
+    flush.cur = 0;
+    const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
+    if (where != kOnScreen)
+        return where == kOffScreen;
+    const uint32_t lane = threadIdx.x & 63u;
+    const WaveTile t = wave_tile(P, box);
+    gu64 *gfb = global_ptr(fb);
+    const Range1 R = uniform_range<PW>(P, depth_of(P, T.td, x[0], y[0], z[0]));
+    bool in = true;
+    auto key_of = [&](int j) {
+        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
+        in = in & (d >= R.lo) & (d < R.hi);
+        const double f = floor((d - R.o) * R.s);
+        uint64_t q52 = (uint64_t)__double_as_longlong(f + 0x1p52);
+        if (PW)
+            q52 += R.base;
+        return make_key(q52, c[j]);
+    };
+    if (t.area <= words) {
+        const uint32_t base = lds_addr(w_tile);
+        const uint32_t p0 = tile_pixel(t, lane);
+        uint64_t cur = 0ull;
+        if (lane < t.area)
+            cur = __hip_atomic_load(gfb + p0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool four = 4 * t.area <= words;
+        const uint32_t sh = four ? 5u : 3u;
+        const uint32_t bytes = t.area << sh;
+        u64x2 none;
+        none.x = none.y = ~0ull;
+        if (16 * lane < bytes)
+            *lds_ptr2(base + 16 * lane) = none;
+        for (uint32_t i = 1024 + 16 * lane; i < bytes; i += 1024)
+            *lds_ptr2(base + i) = none;
+        wave_sync();
+        const uint32_t first = tile_first(t, base + (four ? 8 * (lane & 3u) : 0u), sh);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)), key_of(j),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (j % 2)
+                __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+        flush = MinFlush{t, p0, cur, four};
+        if (wave_any(!in)) {
+            arrive(flush.cur);
+            flush.t.area = 0;
+            return false;
+        }
+        return true;
+    }
+    // spread too far for the tile: groups of four points, their early-out reads
+    // in flight while their keys are computed.  A point out of range takes no
+    // part here, and then the whole chunk is redone by the caller (a minimum may
+    // be taken twice).
+    constexpr int G = 4;
+    bool all = true;
+#pragma unroll
+    for (int g = 0; g < PPT; g += G) {
+        uint32_t pix[G];
+        uint64_t cur[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            pix[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.width) +
+                     (uint32_t)(int32_t)fx[g + k];
+            cur[k] = __hip_atomic_load(gfb + pix[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            in = true;
+            const uint64_t key = key_of(g + k);
+            all = all & in;
+            if (in & (key < cur[k]))
+                __hip_atomic_fetch_min(gfb + pix[k], key, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return !wave_any(!all);
+}
+
 template <int PPT, bool PW, typename Again>
 __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                                   uint64_t *__restrict__ fb,
@@ -1229,8 +1236,6 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
     if (raster_wave_fast<PPT, PW>(P, T, fb, x, y, z, c, w_tile, words, flush))
         return;
     again();
-    flush.t.area = 0;
-    flush.cur = 0;
     raster_wave_any<PPT, PW>(P, T, fb, x, y, z, c, w_tile, words);
 }
 
@@ -1440,189 +1445,6 @@ __device__ __forceinline__ void accum_chunk(const Proj &P, uint32_t eps_num, uin
     }
 }
 
-// What accum_wave_fast leaves to be flushed: its tile (area 0: nothing) and the
-// pixels of the lane's first entries.
-template <int PPT>
-struct SumFlush {
-    static constexpr int kPre = PPT / 2;   // entries per lane whose depths are read ahead
-    WaveTile t;
-    uint32_t pix[kPre];
-    bool four;
-};
-
-template <int PPT>
-__device__ __forceinline__ void accum_wave_flush(uint64_t *__restrict__ acc, const uint64_t *w_tile,
-                                                 const SumFlush<PPT> &f)
-{
-    if (f.t.area == 0)
-        return;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t base = lds_addr(w_tile), sh = f.four ? 5u : 4u;
-    gu64 *gacc = global_ptr(acc);
-    auto flush = [&](uint32_t i, uint32_t p) {
-        uint64_t a0 = 0, a1 = 0;
-        auto add = [&](uint64_t w) {
-            a0 += (w & 0xFFFFull) | (((w >> 16) & 0xFFFFull) << 32);
-            a1 += ((w >> 32) & 0xFFFFull) | ((w >> 48) << 32);
-        };
-        const u64x2 a = *lds_ptr2(base + (i << sh));
-        if (f.four) {   // pairs hold at most 256 points
-            const u64x2 b = *lds_ptr2(base + (i << sh) + 16);
-            add(a.x + a.y);
-            add(b.x + b.y);
-        } else {
-            add(a.x);
-            add(a.y);
-        }
-        if (a1 != 0ull) {   // count > 0
-            gu64 *dst = gacc + 2 * (uint64_t)p;
-            __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    };
-#pragma unroll
-    for (int k = 0; k < SumFlush<PPT>::kPre; ++k) {
-        if (k > 0 && f.t.area <= 64u * k)
-            break;
-        if (lane + 64 * k < f.t.area)
-            flush(lane + 64 * k, f.pix[k]);
-    }
-    for (uint32_t i = lane + 64 * SumFlush<PPT>::kPre; i < f.t.area; i += 64)
-        flush(i, tile_pixel(f.t, i));
-    wave_sync();   // the tile is free for the next use
-}
-
-// accum_chunk_wave for a wave whose points are all on screen and in one range
-// of a linear or scale map, as raster_wave_fast.  Returns false, with acc
-// untouched, when that does not hold, when the rectangle does not fit the tile,
-// or when the window's products are not exact in double precision (see below).
-//
-// The window test is one comparison per point against a threshold per pixel:
-// den * (q - qmin) <= num * S with S = qmin + z0 holds exactly for the integers
-// q <= qmin + floor(num * S / den).  num * S stays below 2^50 for the eps and z0
-// accepted here, so that the product, the remainder of the estimated quotient
-// and with it the corrected floor are exact.  The thresholds lie in LDS beside
-// the sums: the nearest depths of the rectangle are read in coalesced rows
-// while the depths are computed, instead of one by one.
-//
-// Sums: R | G << 16 | B << 32 | count << 48 in copies of the tile, four where
-// they fit, else two (neighbouring lanes hold neighbouring points, and the LDS
-// adds of one address follow each other one per cycle).  One of two copies, or a
-// pair of the four, takes the points of 32 lanes of at most 8 points:
-// 256 * 255 < 2^16, so no field carries before the fields are unpacked.
-template <int PPT, bool PW>
-__device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, const Eps &eps,
-                                                const uint64_t *__restrict__ fb,
-                                                const float (&x)[PPT], const float (&y)[PPT],
-                                                const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                uint64_t *w_tile, uint32_t words,
-                                                SumFlush<PPT> &flush)
-{
-    static_assert(PPT <= 8, "16-bit fields");
-    if ((PW && P.nr != 0) || eps.num > 256u || eps.den > 4096u || P.z0 > (1ull << 41))
-        return false;
-    float fx[PPT], fy[PPT];
-    Box box;
-    if (!window_all<PPT>(P, T, x, y, z, fx, fy, box))
-        return false;
-    const uint32_t lane = threadIdx.x & 63u;
-    const WaveTile t = wave_tile(P, box);
-    const gu64 *gfb = (const gu64 *)global_ptr(fb);
-    const double num = (double)eps.num, den = (double)eps.den;
-    bool in = true;
-    auto depth_q = [&](int j) {   // q as a double
-        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
-        in = in & (d >= P.dlo[0]) & (d < P.dhi[0]);
-        return floor((d - P.o) * P.s);
-    };
-    if (3 * t.area > words)
-        return false;
-    constexpr int kPre = SumFlush<PPT>::kPre;
-    const uint32_t base = lds_addr(w_tile);
-    const bool four = 5 * t.area <= words;
-    const uint32_t sh = four ? 5u : 4u;
-    const uint32_t thr = base + (t.area << sh);   // the thresholds' LDS address
-    uint32_t pix[kPre] = {};
-    uint64_t near[kPre];
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-        if (k > 0 && t.area <= 64u * k)
-            break;
-        pix[k] = tile_pixel(t, lane + 64 * k);
-        near[k] = lane + 64 * k < t.area ? gfb[pix[k]] : 0ull;
-    }
-    u64x2 zero;
-    zero.x = zero.y = 0ull;
-    for (uint32_t i = 16 * lane; i < (t.area << sh); i += 1024)
-        *lds_ptr2(base + i) = zero;
-    double q[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        q[j] = depth_q(j);
-        if (j % 2)
-            __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int j = 0; j < PPT; ++j)   // not before the depths are there
-        asm volatile("" : "+v"(near[0]) : "v"(q[j]));
-#pragma unroll
-    for (int k = 1; k < kPre; ++k)
-        if (t.area > 64u * k)
-            arrive(near[k]);
-    if (wave_any(!in))
-        return false;
-    auto threshold = [&](uint64_t key) {
-        const double dm = int52_to_double(key >> 24);
-        const double r = num * (dm + P.z0d);
-        const double f = floor(r * eps.inv_den);
-        const double rem = __builtin_fma(-f, den, r);
-        return dm + (rem < 0.0 ? f - 1.0 : rem >= den ? f + 1.0 : f);
-    };
-    typedef __attribute__((address_space(3))) double lf64;
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-        if (k > 0 && t.area <= 64u * k)
-            break;
-        if (lane + 64 * k < t.area)
-            *(lf64 *)(uintptr_t)(thr + 8 * (lane + 64 * k)) = threshold(near[k]);
-    }
-    for (uint32_t i = lane + 64 * kPre; i < t.area; i += 64)
-        *(lf64 *)(uintptr_t)(thr + 8 * i) = threshold(gfb[tile_pixel(t, i)]);
-    wave_sync();
-    const uint32_t sub = lane & (four ? 3u : 1u);
-    const uint32_t first = tile_first(t, base + 8 * sub, sh);
-    const uint32_t tfirst = tile_first(t, thr, 3);
-    constexpr int G = 4;   // thresholds in flight
-#pragma unroll
-    for (int g = 0; g < PPT; g += G) {
-        uint32_t e[G];
-        double most[G];
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            e[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.bw) +
-                   (uint32_t)(int32_t)fx[g + k];
-            most[k] = *(lf64 *)(uintptr_t)((e[k] << 3) + tfirst);
-        }
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            if (q[g + k] <= most[k]) {
-                const uint32_t lo = __builtin_amdgcn_perm(1u, c[g + k], 0x0c010c00u);   // R, G
-                const uint32_t hi = __builtin_amdgcn_perm(1u, c[g + k], 0x0c040c02u);   // B, 1
-                __hip_atomic_fetch_add(lds_ptr((e[k] << sh) + first),
-                                       ((uint64_t)hi << 32) | lo, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
-    }
-    wave_sync();
-    flush.t = t;
-    flush.four = four;
-#pragma unroll
-    for (int k = 0; k < kPre; ++k)
-        flush.pix[k] = pix[k];
-    return true;
-}
-
 // accum_chunk_wave for any wave: each point with its own flags, as
 // raster_wave_any.  A wave of at most 512 points (PPT <= 8) adds one packed word
 // per fragment, R | G << 17 | B << 34 | count << 51: no field of a sum over the
@@ -1718,9 +1540,194 @@ __device__ __forceinline__ void accum_wave_any(const Proj &P, const Trans &T, co
     wave_sync();   // the tile is free for the next use
 }
 
+// What accum_chunk_wave leaves to be flushed: its tile (area 0: nothing) and the
+// pixels of the lane's first entries.
+template <int PPT>
+struct SumFlush {
+    static constexpr int kPre = PPT / 2;   // entries per lane whose depths are read ahead
+    WaveTile t;
+    uint32_t pix[kPre];
+    bool four;
+};
+
+template <int PPT>
+__device__ __forceinline__ void accum_wave_flush(uint64_t *__restrict__ acc, const uint64_t *w_tile,
+                                                 const SumFlush<PPT> &f)
+{
+    if (f.t.area == 0)
+        return;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t base = lds_addr(w_tile), sh = f.four ? 5u : 4u;
+    gu64 *gacc = global_ptr(acc);
+    auto flush = [&](uint32_t i, uint32_t p) {
+        uint64_t a0 = 0, a1 = 0;
+        auto add = [&](uint64_t w) {
+            a0 += (w & 0xFFFFull) | (((w >> 16) & 0xFFFFull) << 32);
+            a1 += ((w >> 32) & 0xFFFFull) | ((w >> 48) << 32);
+        };
+        const u64x2 a = *lds_ptr2(base + (i << sh));
+        if (f.four) {   // pairs hold at most 256 points
+            const u64x2 b = *lds_ptr2(base + (i << sh) + 16);
+            add(a.x + a.y);
+            add(b.x + b.y);
+        } else {
+            add(a.x);
+            add(a.y);
+        }
+        if (a1 != 0ull) {   // count > 0
+            gu64 *dst = gacc + 2 * (uint64_t)p;
+            __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < SumFlush<PPT>::kPre; ++k) {
+        if (k > 0 && f.t.area <= 64u * k)
+            break;
+        if (lane + 64 * k < f.t.area)
+            flush(lane + 64 * k, f.pix[k]);
+    }
+    for (uint32_t i = lane + 64 * SumFlush<PPT>::kPre; i < f.t.area; i += 64)
+        flush(i, tile_pixel(f.t, i));
+    wave_sync();   // the tile is free for the next use
+}
+
 // Accumulate pass over one chunk with a private LDS tile per wave of `words`
-// words (see raster_chunk_wave).  Same result bits as accum_chunk.
-// accum_wave_flush must follow with the same `flush`; again() as there.
+// words.  Same result bits as accum_chunk.  accum_wave_flush must follow with
+// the same `flush`; again() as for raster_chunk_wave.
+//
+// As there, a wave whose points are all on screen and in range needs no flag
+// per point; every other one takes accum_wave_any, and so do waves whose
+// rectangle does not fit the tile, piecewise maps, and windows whose products
+// are not exact in double precision (see below).
+//
+// The window test is one comparison per point against a threshold per pixel:
+// den * (q - qmin) <= num * S with S = qmin + z0 holds exactly for the integers
+// q <= qmin + floor(num * S / den).  num * S stays below 2^50 for the eps and z0
+// accepted here, so that the product, the remainder of the estimated quotient
+// and with it the corrected floor are exact.  The thresholds lie in LDS beside
+// the sums: the nearest depths of the rectangle are read in coalesced rows
+// while the depths are computed, instead of one by one.
+//
+// Sums: R | G << 16 | B << 32 | count << 48 in copies of the tile, four where
+// they fit, else two (neighbouring lanes hold neighbouring points, and the LDS
+// adds of one address follow each other one per cycle).  One of two copies, or a
+// pair of the four, takes the points of 32 lanes of at most 8 points:
+// 256 * 255 < 2^16, so no field carries before the fields are unpacked.
+template <int PPT, bool PW>
+__device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, const Eps &eps,
+                                                const uint64_t *__restrict__ fb,
+                                                const float (&x)[PPT], const float (&y)[PPT],
+                                                const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                uint64_t *w_tile, uint32_t words,
+                                                SumFlush<PPT> &flush)
+{
+    flush.t.area = 0;
+    if ((PW && P.nr != 0) || eps.num > 256u || eps.den > 4096u || P.z0 > (1ull << 41))
+        return false;
+    float fx[PPT], fy[PPT];
+    Box box;
+    const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
+    if (where == kOffScreen)
+        return true;
+    if (where == kMixed || 3 * (box.x1 - box.x0 + 1) * (box.y1 - box.y0 + 1) > words)
+        return false;
+    const uint32_t lane = threadIdx.x & 63u;
+    const WaveTile t = wave_tile(P, box);
+    const gu64 *gfb = (const gu64 *)global_ptr(fb);
+    const double num = (double)eps.num, den = (double)eps.den;
+    bool in = true;
+    auto depth_q = [&](int j) {   // q as a double
+        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
+        in = in & (d >= P.dlo[0]) & (d < P.dhi[0]);
+        return floor((d - P.o) * P.s);
+    };
+    constexpr int kPre = SumFlush<PPT>::kPre;
+    const uint32_t base = lds_addr(w_tile);
+    const bool four = 5 * t.area <= words;
+    const uint32_t sh = four ? 5u : 4u;
+    const uint32_t thr = base + (t.area << sh);   // the thresholds' LDS address
+    uint32_t pix[kPre] = {};
+    uint64_t near[kPre];
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+        if (k > 0 && t.area <= 64u * k)
+            break;
+        pix[k] = tile_pixel(t, lane + 64 * k);
+        near[k] = lane + 64 * k < t.area ? gfb[pix[k]] : 0ull;
+    }
+    u64x2 zero;
+    zero.x = zero.y = 0ull;
+    for (uint32_t i = 16 * lane; i < (t.area << sh); i += 1024)
+        *lds_ptr2(base + i) = zero;
+    double q[PPT];
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+        q[j] = depth_q(j);
+        if (j % 2)
+            __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < PPT; ++j)   // not before the depths are there
+        asm volatile("" : "+v"(near[0]) : "v"(q[j]));
+#pragma unroll
+    for (int k = 1; k < kPre; ++k)
+        if (t.area > 64u * k)
+            arrive(near[k]);
+    if (wave_any(!in))
+        return false;
+    auto threshold = [&](uint64_t key) {
+        const double dm = int52_to_double(key >> 24);
+        const double r = num * (dm + P.z0d);
+        const double f = floor(r * eps.inv_den);
+        const double rem = __builtin_fma(-f, den, r);
+        return dm + (rem < 0.0 ? f - 1.0 : rem >= den ? f + 1.0 : f);
+    };
+    typedef __attribute__((address_space(3))) double lf64;
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+        if (k > 0 && t.area <= 64u * k)
+            break;
+        if (lane + 64 * k < t.area)
+            *(lf64 *)(uintptr_t)(thr + 8 * (lane + 64 * k)) = threshold(near[k]);
+    }
+    for (uint32_t i = lane + 64 * kPre; i < t.area; i += 64)
+        *(lf64 *)(uintptr_t)(thr + 8 * i) = threshold(gfb[tile_pixel(t, i)]);
+    wave_sync();
+    const uint32_t sub = lane & (four ? 3u : 1u);
+    const uint32_t first = tile_first(t, base + 8 * sub, sh);
+    const uint32_t tfirst = tile_first(t, thr, 3);
+    constexpr int G = 4;   // thresholds in flight
+#pragma unroll
+    for (int g = 0; g < PPT; g += G) {
+        uint32_t e[G];
+        double most[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            e[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.bw) +
+                   (uint32_t)(int32_t)fx[g + k];
+            most[k] = *(lf64 *)(uintptr_t)((e[k] << 3) + tfirst);
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            if (q[g + k] <= most[k]) {
+                const uint32_t lo = __builtin_amdgcn_perm(1u, c[g + k], 0x0c010c00u);   // R, G
+                const uint32_t hi = __builtin_amdgcn_perm(1u, c[g + k], 0x0c040c02u);   // B, 1
+                __hip_atomic_fetch_add(lds_ptr((e[k] << sh) + first),
+                                       ((uint64_t)hi << 32) | lo, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    }
+    wave_sync();
+    flush.t = t;
+    flush.four = four;
+#pragma unroll
+    for (int k = 0; k < kPre; ++k)
+        flush.pix[k] = pix[k];
+    return true;
+}
+
 template <int PPT, bool PW, typename Again>
 __device__ __forceinline__ void accum_chunk_wave(const Proj &P, const Trans &T, const Eps &eps,
                                                  const uint64_t *__restrict__ fb,
@@ -1730,12 +1737,12 @@ __device__ __forceinline__ void accum_chunk_wave(const Proj &P, const Trans &T, 
                                                  uint32_t words, SumFlush<PPT> &flush,
                                                  const Again &again)
 {
-    if constexpr (PPT <= 8) {
+    flush.t.area = 0;
+    if constexpr (PPT <= 8) {   // the sums' 16-bit fields
         if (accum_wave_fast<PPT, PW>(P, T, eps, fb, x, y, z, c, w_tile, words, flush))
             return;
         again();
     }
-    flush.t.area = 0;
     accum_wave_any<PPT, PW>(P, T, eps, fb, acc, x, y, z, c, w_tile, words);
 }
 

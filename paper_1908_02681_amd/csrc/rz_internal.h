@@ -48,9 +48,18 @@ struct Tune {
     int xcd_remap = 0;     // give each XCD a contiguous range of chunks
     int bin = 2;           // 0 none, 1 workgroup LDS tile, 2 per-wave LDS tile,
                            // 3 the small per-wave tile
+    int by_size = 1;       // library default: small clouds take kSmallTune
 };
 
-constexpr Tune kHqTune = {64, 8, 1, 0, 3};
+constexpr Tune kHqTune = {64, 8, 1, 0, 3, 1};
+// Clouds of fewer points than this: four times the waves, each done sooner.  At
+// the default shapes they are one or two rounds of 4096 waves of 1024 points (5120
+// of 512 in the splat pass), so that a pass lasts as long as its slowest waves.
+// Frames of the terrain at 1920x1080, default shape / this one: 0.5M points 25.1 /
+// 21.5 us (splat 64.9 / 56.3), 2M 29.7 / 27.1 (73.3 / 66.4), 5M 36.1 / 31.5 (81.9 /
+// 77.3), 10M 47.4 / 44.6 (101.7 / 100.6), 20M 71.9 / 72.4 (149.0 / 152.9).
+constexpr int64_t kSmallCloud = 8 << 20;
+constexpr Tune kSmallTune = {256, 4, 1, 0, 3, 1};
 
 // The splat window's eps = num / den, with 1 / den rounded once.
 struct Eps {

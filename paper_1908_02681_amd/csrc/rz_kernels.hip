@@ -273,12 +273,13 @@ hipError_t raster_min_zk(const Pts &p, const Proj &P, uint64_t *fb, const Tune &
 
 }  // namespace
 
-hipError_t launch_raster_min(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t,
+hipError_t launch_raster_min(const Pts &p, const Proj &P, uint64_t *fb, const Tune &tune,
                              hipStream_t s)
 {
     Range r("rz depth pass");
     if (p.n == 0)
         return hipSuccess;
+    const Tune &t = tune.by_size && p.n < kSmallCloud && P.zkind == 0 ? kSmallTune : tune;
     if (P.zkind != 0) {
         // float depth encodings: the per-wave tile kernel (either tile
         // size) at 16 points per thread, the general point kernel for every
@@ -297,11 +298,12 @@ hipError_t launch_raster_min(const Pts &p, const Proj &P, uint64_t *fb, const Tu
 }
 
 hipError_t launch_hq_accum(const Pts &p, const Proj &P, uint32_t num, uint32_t den,
-                           const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
+                           const uint64_t *fb, uint64_t *acc, const Tune &tune, hipStream_t s)
 {
     Range r("rz splat accumulate pass");
     if (p.n == 0)
         return hipSuccess;
+    const Tune &t = tune.by_size && p.n < kSmallCloud ? kSmallTune : tune;
     const Eps eps{num, den, 1.0 / (double)den};
     switch (t.ppt) {
     case 4: return hq_accum_dispatch<4>(p, P, eps, fb, acc, t, s);
