@@ -832,9 +832,10 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
 
 // Window positions of a wave's points: kOnScreen, with their pixel rectangle,
 // when every point of the wave has a w in [2^-126, 2^126) and an on-screen window
-// position; kOffScreen when all lie beyond one edge of the screen; kMixed (and
-// the rest meaningless) otherwise.  The first two are nearly all chunks of an
-// ordered cloud, and need no flag per point.  The tests run on bit patterns, where the order of
+// position; kOffScreen when all lie beyond one edge of the screen; kEdge, with
+// the on-screen part of their rectangle, when only w is known to be fine; kMixed
+// (and the rest meaningless) otherwise.  The first two are nearly all chunks of
+// an ordered cloud, and need no flag per point.  The tests run on bit patterns, where the order of
 // non-negative floats is that of the integers and every other value (negative,
 // NaN, infinite) falls outside: w through an unsigned minimum and maximum, x
 // and y through signed ones.
@@ -844,7 +845,7 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
 // the even rows and the complemented maxima into the odd ones, and one 16-lane
 // reduction finishes all four: 11 instructions where four 64-lane reductions
 // take 24.
-enum Where { kOnScreen, kOffScreen, kMixed };
+enum Where { kOnScreen, kOffScreen, kEdge, kMixed };
 
 template <int PPT>
 __device__ __forceinline__ Where window_all(const Proj &P, const Trans &T, const float (&x)[PPT],
@@ -885,13 +886,18 @@ __device__ __forceinline__ Where window_all(const Proj &P, const Trans &T, const
     if (wave_any((wlo < 0x00800000u) | (whi >= 0x7E800000u)))
         return kMixed;
     // even rows: minimum >= 0; odd rows: maximum < size, on the complement
-    if (wave_any(m < (odd ? -size : 0)))
-        return wave_any(m >= (odd ? 0 : size)) ? kOffScreen : kMixed;
-    const int32_t px = (int32_t)__int_as_float(odd ? ~m : m);
+    const bool inside = m >= (odd ? -size : 0);
+    if (wave_any(m >= (odd ? 0 : size)))   // a minimum >= size or a maximum < 0
+        return kOffScreen;
+    // the minima and maxima as pixels, cut at the screen's edge
+    const float edge = odd ? __int_as_float(size) - 1.0f : 0.0f;
+    const int32_t px = (int32_t)(inside ? __int_as_float(odd ? ~m : m) : edge);
     box.x0 = (uint32_t)__builtin_amdgcn_readlane(px, 0);
     box.x1 = (uint32_t)__builtin_amdgcn_readlane(px, 16);
     box.y0 = (uint32_t)__builtin_amdgcn_readlane(px, 32);
     box.y1 = (uint32_t)__builtin_amdgcn_readlane(px, 48);
+    if (wave_any(!inside))
+        return kEdge;
     return kOnScreen;
 }
 
@@ -1146,8 +1152,10 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
     flush.t.area = 0;
     flush.cur = 0;
     const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
-    if (where != kOnScreen)
-        return where == kOffScreen;
+    if (where == kOffScreen)
+        return true;
+    if (where == kMixed)
+        return false;
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
     gu64 *gfb = global_ptr(fb);
@@ -1163,6 +1171,8 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
         return make_key(q52, c[j]);
     };
     if (t.area <= words) {
+        if (where == kEdge)
+            return false;
         const uint32_t base = lds_addr(w_tile);
         const uint32_t p0 = tile_pixel(t, lane);
         uint64_t cur = 0ull;
@@ -1196,27 +1206,30 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
         return true;
     }
     // spread too far for the tile: groups of four points, their early-out reads
-    // in flight while their keys are computed.  A point out of range takes no
-    // part here, and then the whole chunk is redone by the caller (a minimum may
-    // be taken twice).
+    // in flight while their keys are computed; here points off screen are no
+    // reason to leave.  A point out of range takes no part, and then the whole
+    // chunk is redone by the caller (a minimum may be taken twice).
     constexpr int G = 4;
     bool all = true;
 #pragma unroll
     for (int g = 0; g < PPT; g += G) {
         uint32_t pix[G];
         uint64_t cur[G];
+        bool vis[G];
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            pix[k] = __umul24((uint32_t)(int32_t)fy[g + k], t.width) +
-                     (uint32_t)(int32_t)fx[g + k];
+            const float px = fx[g + k], py = fy[g + k];
+            vis[k] = (px >= 0.0f) & (px < P.fw) & (py >= 0.0f) & (py < P.fh);
+            pix[k] = __umul24((uint32_t)(int32_t)(vis[k] ? py : 0.0f), t.width) +
+                     (uint32_t)(int32_t)(vis[k] ? px : 0.0f);
             cur[k] = __hip_atomic_load(gfb + pix[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
 #pragma unroll
         for (int k = 0; k < G; ++k) {
             in = true;
             const uint64_t key = key_of(g + k);
-            all = all & in;
-            if (in & (key < cur[k]))
+            all = all & (in | !vis[k]);
+            if (in & vis[k] & (key < cur[k]))
                 __hip_atomic_fetch_min(gfb + pix[k], key, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -1630,7 +1643,7 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
     const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
     if (where == kOffScreen)
         return true;
-    if (where == kMixed || 3 * (box.x1 - box.x0 + 1) * (box.y1 - box.y0 + 1) > words)
+    if (where != kOnScreen || 3 * (box.x1 - box.x0 + 1) * (box.y1 - box.y0 + 1) > words)
         return false;
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
