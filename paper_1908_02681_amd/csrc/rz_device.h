@@ -400,6 +400,18 @@ __device__ __forceinline__ bool fragment_zk(const Proj &P, const Trans &T, float
     return vis & in_range & clip;
 }
 
+// The fragment of the kernels templated on the depth encoding: ZK = 0 for
+// the integer maps, else RZ_DEPTH_GL24 or RZ_DEPTH_F32REV.
+template <bool PW, int ZK>
+__device__ __forceinline__ bool fragment_enc(const Proj &P, const Trans &T, float x, float y,
+                                             float z, uint32_t &px, uint32_t &py, uint64_t &q)
+{
+    if constexpr (ZK == 0)
+        return fragment<PW>(P, T, x, y, z, px, py, q);
+    else
+        return fragment_zk<ZK>(P, T, x, y, z, px, py, q);
+}
+
 // Workgroup -> chunk of points.  Workgroups are dealt round-robin to the 8
 // XCDs; with the remap, XCD k works through the k-th eighth of the chunks,
 // so spatially coherent (e.g. Morton-ordered) ranges share one L2.
@@ -931,6 +943,51 @@ __device__ __forceinline__ uint64_t make_key(uint64_t q52, uint32_t c)
     return ((uint64_t)kh << 32) | kl;
 }
 
+// Keys of the points of one chunk, all of them with a w in [2^-126, 2^126).
+// `in` is cleared by a point for which the key is not valid: one outside
+// [near, far), outside the chunk's range of the depth map, or clipped by the
+// 24-bit window depth.
+template <bool PW, int ZK>
+struct ChunkKey {
+    const Proj &P;
+    const Trans &T;
+    Range1 R;
+
+    // x, y, z: a point of the chunk, whose range serves for all
+    __device__ __forceinline__ ChunkKey(const Proj &p, const Trans &t, float x, float y, float z)
+        : P(p), T(t), R(uniform_range<PW>(p, PW ? depth_of(p, t.td, x, y, z) : 0.0))
+    {
+    }
+
+    __device__ __forceinline__ uint64_t operator()(float x, float y, float z, uint32_t c,
+                                                   bool &in) const
+    {
+        const double d = depth_of(P, T.td, x, y, z);
+        in = in & (d >= R.lo) & (d < R.hi);
+        if constexpr (ZK == 0) {
+            const double f = floor((d - R.o) * R.s);
+            uint64_t q52 = (uint64_t)__double_as_longlong(f + 0x1p52);
+            if (PW)
+                q52 += R.base;
+            return make_key(q52, c);
+        }
+        float cw = __builtin_fmaf(P.m[8], x, T.tw);
+        cw = __builtin_fmaf(P.m[9], y, cw);
+        cw = __builtin_fmaf(P.m[10], z, cw);
+        if constexpr (ZK == RZ_DEPTH_F32REV)
+            return make_key(0xFFFFFFFFull - (uint64_t)__float_as_uint(P.nearf / cw), c);
+        float cz = __builtin_fmaf(P.mz[0], x, P.mz[3]);
+        cz = __builtin_fmaf(P.mz[1], y, cz);
+        cz = __builtin_fmaf(P.mz[2], z, cz);
+        const float nz = cz * recip_newton(cw);
+        const bool clip = (nz >= -1.0f) & (nz <= 1.0f);
+        in = in & clip;
+        const float zw = (nz + 1.0f) * 0.5f;
+        const float t = zw * 16777215.0f;
+        return make_key((uint64_t)(uint32_t)floor((double)(clip ? t : 0.0f) + 0.5), c);
+    }
+};
+
 // The screen rectangle of a wave's fragments as a tile in LDS.
 struct WaveTile {
     uint32_t x0, y0, bw, area;
@@ -1002,7 +1059,7 @@ __device__ __forceinline__ Box wave_screen_box(const Proj &P, const Trans &T, co
 // array of keys or pixels is held: these waves are few (those across the
 // screen's edge or a range of the depth map), and the registers of this path
 // are those of the whole kernel.
-template <int PPT, bool PW>
+template <int PPT, bool PW, int ZK>
 __device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
                                                 uint64_t *__restrict__ fb, const float (&x)[PPT],
                                                 const float (&y)[PPT], const float (&z)[PPT],
@@ -1035,7 +1092,7 @@ __device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
             own(xx), own(yy), own(zz);
             uint32_t px = 0, py = 0;
             uint64_t q = 0;
-            live[k] = fragment<PW>(P, T, xx, yy, zz, px, py, q);
+            live[k] = fragment_enc<PW, ZK>(P, T, xx, yy, zz, px, py, q);
             key[k] = (q << 24) | ((uint64_t)c[g + k] & kRgbMask);
             at[k] = tiled ? ((__umul24(py, t.bw) + px) << 3) + first
                           : __umul24(py, t.width) + px;
@@ -1122,7 +1179,7 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
 // Depth pass over one chunk with a private LDS tile per wave: like
 // raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
 // in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
-// Same result bits as raster_chunk, for any tile size.  Integer depth maps.
+// Same result bits as raster_chunk, for any tile size.
 // raster_wave_flush must follow with the same `flush`.
 //
 // A wave whose points are all on screen and, as it turns out, in one range of
@@ -1140,7 +1197,7 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
 // neighbouring lanes hold neighbouring points, and LDS atomics of one address
 // follow each other one per cycle (a depth pass of 100M points over 8 views:
 // 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
-template <int PPT, bool PW>
+template <int PPT, bool PW, int ZK>
 __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
                                                  uint64_t *__restrict__ fb,
                                                  const float (&x)[PPT], const float (&y)[PPT],
@@ -1159,17 +1216,8 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
     gu64 *gfb = global_ptr(fb);
-    const Range1 R = uniform_range<PW>(P, depth_of(P, T.td, x[0], y[0], z[0]));
+    const ChunkKey<PW, ZK> key_of(P, T, x[0], y[0], z[0]);
     bool in = true;
-    auto key_of = [&](int j) {
-        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
-        in = in & (d >= R.lo) & (d < R.hi);
-        const double f = floor((d - R.o) * R.s);
-        uint64_t q52 = (uint64_t)__double_as_longlong(f + 0x1p52);
-        if (PW)
-            q52 += R.base;
-        return make_key(q52, c[j]);
-    };
     if (t.area <= words) {
         if (where == kEdge)
             return false;
@@ -1191,7 +1239,7 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
         const uint32_t first = tile_first(t, base + (four ? 8 * (lane & 3u) : 0u), sh);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-            __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)), key_of(j),
+            __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)), key_of(x[j], y[j], z[j], c[j], in),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (j % 2)
                 __builtin_amdgcn_sched_barrier(0);
@@ -1227,7 +1275,7 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
 #pragma unroll
         for (int k = 0; k < G; ++k) {
             in = true;
-            const uint64_t key = key_of(g + k);
+            const uint64_t key = key_of(x[g + k], y[g + k], z[g + k], c[g + k], in);
             all = all & (in | !vis[k]);
             if (in & vis[k] & (key < cur[k]))
                 __hip_atomic_fetch_min(gfb + pix[k], key, __ATOMIC_RELAXED,
@@ -1238,7 +1286,7 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
     return !wave_any(!all);
 }
 
-template <int PPT, bool PW, typename Again>
+template <int PPT, bool PW, int ZK = 0, typename Again>
 __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                                   uint64_t *__restrict__ fb,
                                                   const float (&x)[PPT], const float (&y)[PPT],
@@ -1246,102 +1294,10 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                                   uint64_t *w_tile, uint32_t words,
                                                   MinFlush &flush, const Again &again)
 {
-    if (raster_wave_fast<PPT, PW>(P, T, fb, x, y, z, c, w_tile, words, flush))
+    if (raster_wave_fast<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, flush))
         return;
     again();
-    raster_wave_any<PPT, PW>(P, T, fb, x, y, z, c, w_tile, words);
-}
-
-// The same for the float depth encodings (ZK), the flush included.
-template <int PPT, int ZK>
-__device__ __forceinline__ void raster_chunk_wave_zk(const Proj &P, const Trans &T,
-                                                  uint64_t *__restrict__ fb,
-                                                  const float (&x)[PPT], const float (&y)[PPT],
-                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                     uint64_t *w_tile, uint32_t words)
-{
-    uint32_t px[PPT], py[PPT], pix[PPT];
-    uint64_t key[PPT];
-    bool live[PPT];
-    #pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        uint64_t q = 0;
-        uint32_t a = 0, b = 0;
-        live[j] = fragment_zk<ZK>(P, T, x[j], y[j], z[j], a, b, q);
-        px[j] = a;
-        py[j] = b;
-        key[j] = (q << 24) | ((uint64_t)c[j] & kRgbMask);
-    }
-    const Box box = wave_box_live_min<PPT>(px, py, live);
-    const uint32_t lane = threadIdx.x & 63u;
-    bool tiled = false;
-    uint32_t bw = 0, bh = 0;
-    if (box.x0 <= box.x1) {
-        bw = box.x1 - box.x0 + 1;
-        bh = box.y1 - box.y0 + 1;
-        tiled = (uint64_t)bw * bh <= words;
-    }
-    if (tiled) {
-        // the box bounds every live fragment of the wave, so all of them
-        // land in the tile: entry (py - y0) * bw + (px - x0), computed
-        // modulo 2^32 as py * bw + px - org
-        const uint32_t area = bw * bh;
-        const uint32_t org = box.y0 * bw + box.x0;
-        for (uint32_t i = lane; i < area; i += 64)
-            w_tile[i] = ~0ull;
-        wave_sync();
-#pragma unroll
-        for (int j = 0; j < PPT; ++j)
-            if (live[j])
-                __hip_atomic_fetch_min(&w_tile[__umul24(py[j], bw) + px[j] - org], key[j],
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        wave_sync();
-        const float inv_bw = 1.0f / (float)bw;
-        for (uint32_t i = lane; i < area; i += 64) {
-            const uint64_t v = w_tile[i];
-            if (v != ~0ull) {
-                uint32_t r, col;
-                tile_rc(i, bw, inv_bw, r, col);
-                uint64_t *dst = fb + (__umul24(box.y0 + r, (uint32_t)P.width) + box.x0 + col);
-                const uint64_t cur = __hip_atomic_load(dst, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                if (v < cur)
-                    __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        wave_sync();   // the tile is free for the next use
-        return;
-    }
-    // the wave's fragments spread too far for the tile (or there are none):
-    // runs of one pixel are merged in registers (LDS atomics need no such
-    // help), then each remaining fragment takes an early-out read and a
-    // global atomic
-#pragma unroll
-    for (int j = 0; j < PPT; ++j)
-        pix[j] = __umul24(py[j], (uint32_t)P.width) + px[j];   // both below 2^15
-#pragma unroll
-    for (int j = 1; j < PPT; ++j) {
-        const bool same = live[j] && live[j - 1] && pix[j] == pix[j - 1];
-        const uint64_t lo = key[j] < key[j - 1] ? key[j] : key[j - 1];
-        key[j] = same ? lo : key[j];
-        live[j - 1] = live[j - 1] && !same;
-    }
-    bool any_live = false;
-#pragma unroll
-    for (int j = 0; j < PPT; ++j)
-        any_live = any_live || live[j];
-    if (wave_any(any_live)) {
-        uint64_t cur[PPT];
-#pragma unroll
-        for (int j = 0; j < PPT; ++j)
-            cur[j] = __hip_atomic_load(fb + (live[j] ? pix[j] : 0u), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int j = 0; j < PPT; ++j)
-            if (live[j] && key[j] < cur[j])
-                __hip_atomic_fetch_min(fb + pix[j], key[j], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-    }
+    raster_wave_any<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words);
 }
 
 // Accumulation pass of high-quality splatting over one chunk (section 2.2).

@@ -51,20 +51,22 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
 
 // Depth pass for the float depth encodings (RZ_DEPTH_GL24, RZ_DEPTH_F32REV)
 // at one pixel per point: the per-wave tile kernel with the encoding's key.
-template <int ZK>
+template <int PPT, int ZK>
 __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *__restrict__ fb,
                                                        int64_t nchunks, uint32_t words)
 {
-    constexpr int PPT = 16;
     extern __shared__ uint64_t s_waves[];
     const int64_t chunk = blockIdx.x;
     if (chunk >= nchunks)
         return;
     float x[PPT], y[PPT], z[PPT];
     uint32_t c[PPT];
-    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
-    raster_chunk_wave_zk<PPT, ZK>(P, lane_trans(P), fb, x, y, z, c,
-                                  s_waves + (threadIdx.x >> 6) * words, words);
+    uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
+    auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
+    load();
+    MinFlush flush;
+    raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load);
+    raster_wave_flush(fb, w_tile, flush);
 }
 
 // Accumulation pass of section 2.2 for one view.
@@ -260,15 +262,27 @@ hipError_t hq_accum_dispatch(const Pts &p, const Proj &P, const Eps &eps,
                 : hq_accum_bin<PPT, false>(p, P, eps, fb, acc, t, s);
 }
 
-template <int ZK>
+template <int PPT, int ZK>
 hipError_t raster_min_zk(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t, hipStream_t s)
 {
-    const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * 16);
+    const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * PPT);
     const size_t lds = wave_lds(t.bin, t.block, false);
     const uint32_t words = wave_tile_words(t.bin, false);
-    hipLaunchKernelGGL((k_raster_min_zk<ZK>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
+    hipLaunchKernelGGL((k_raster_min_zk<PPT, ZK>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
                        fb, nchunks, words);
     return hipGetLastError();
+}
+
+template <int ZK>
+hipError_t raster_min_zk_dispatch(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t,
+                                  hipStream_t s)
+{
+    switch (t.ppt) {
+    case 4: return raster_min_zk<4, ZK>(p, P, fb, t, s);
+    case 8: return raster_min_zk<8, ZK>(p, P, fb, t, s);
+    case 16: return raster_min_zk<16, ZK>(p, P, fb, t, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -279,15 +293,18 @@ hipError_t launch_raster_min(const Pts &p, const Proj &P, uint64_t *fb, const Tu
     Range r("rz depth pass");
     if (p.n == 0)
         return hipSuccess;
-    const Tune &t = tune.by_size && p.n < kSmallCloud && P.zkind == 0 ? kSmallTune : tune;
+    // (the float encodings' kernel holds 141 registers at 16 points a thread, and
+    // the small shape serves them longer: 20M points 71.0 us against 72.9, 50M
+    // 159 against 148)
+    const int64_t small = P.zkind != 0 ? 3 * kSmallCloud : kSmallCloud;
+    const Tune &t = tune.by_size && p.n < small ? kSmallTune : tune;
     if (P.zkind != 0) {
-        // float depth encodings: the per-wave tile kernel (either tile
-        // size) at 16 points per thread, the general point kernel for every
-        // other launch shape
-        if ((t.bin != kBinWave && t.bin != kBinWaveSmall) || t.ppt != 16 || t.xcd_remap)
+        // float depth encodings: the per-wave tile kernel (either tile size),
+        // the general point kernel for every other launch shape
+        if ((t.bin != kBinWave && t.bin != kBinWaveSmall) || t.xcd_remap)
             return launch_raster_points(p, P, 1, fb, s);
-        return P.zkind == RZ_DEPTH_GL24 ? raster_min_zk<RZ_DEPTH_GL24>(p, P, fb, t, s)
-                                        : raster_min_zk<RZ_DEPTH_F32REV>(p, P, fb, t, s);
+        return P.zkind == RZ_DEPTH_GL24 ? raster_min_zk_dispatch<RZ_DEPTH_GL24>(p, P, fb, t, s)
+                                        : raster_min_zk_dispatch<RZ_DEPTH_F32REV>(p, P, fb, t, s);
     }
     switch (t.ppt) {
     case 4: return raster_min_dispatch<4>(p, P, fb, t, s);
