@@ -170,6 +170,26 @@ __device__ __forceinline__ bool in_window_live(const Proj &P, uint32_t eps_num, 
     return ok;
 }
 
+// The window as a threshold per pixel, for the linear and scale maps:
+// den * (q - qmin) <= num * S with S = qmin + z0 holds exactly for the integers
+// q <= qmin + floor(num * S / den).  num * S stays below 2^50 for the eps and z0
+// of window_exact, so that the product, the remainder of the estimated quotient
+// and with it the corrected floor are exact.
+__device__ __forceinline__ bool window_exact(const Proj &P, const Eps &eps)
+{
+    return eps.num <= 256u && eps.den <= 4096u && P.z0 <= (1ull << 41);
+}
+
+__device__ __forceinline__ double window_threshold(const Proj &P, const Eps &eps, uint64_t key)
+{
+    const double den = (double)eps.den;
+    const double dm = int52_to_double(key >> 24);
+    const double r = (double)eps.num * (dm + P.z0d);
+    const double f = floor(r * eps.inv_den);
+    const double rem = __builtin_fma(-f, den, r);
+    return dm + (rem < 0.0 ? f - 1.0 : rem >= den ? f + 1.0 : f);
+}
+
 // The IEEE quotient 1 / w for w > 0, without the full division sequence:
 // one Newton-Raphson correction of the hardware estimate, r + r * (1 - w r)
 // with both steps fused (Markstein's method).  Run over every positive
@@ -1570,12 +1590,8 @@ __device__ __forceinline__ void accum_wave_flush(uint64_t *__restrict__ acc, con
 // rectangle does not fit the tile, piecewise maps, and windows whose products
 // are not exact in double precision (see below).
 //
-// The window test is one comparison per point against a threshold per pixel:
-// den * (q - qmin) <= num * S with S = qmin + z0 holds exactly for the integers
-// q <= qmin + floor(num * S / den).  num * S stays below 2^50 for the eps and z0
-// accepted here, so that the product, the remainder of the estimated quotient
-// and with it the corrected floor are exact.  The thresholds lie in LDS beside
-// the sums: the nearest depths of the rectangle are read in coalesced rows
+// The window test is one comparison per point against a threshold per pixel
+// (window_threshold).  The thresholds lie in LDS beside the sums: the nearest depths of the rectangle are read in coalesced rows
 // while the depths are computed, instead of one by one.
 //
 // Sums: R | G << 16 | B << 32 | count << 48 in copies of the tile, four where
@@ -1592,7 +1608,7 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
                                                 SumFlush<PPT> &flush)
 {
     flush.t.area = 0;
-    if ((PW && P.nr != 0) || eps.num > 256u || eps.den > 4096u || P.z0 > (1ull << 41))
+    if ((PW && P.nr != 0) || !window_exact(P, eps))
         return false;
     float fx[PPT], fy[PPT];
     Box box;
@@ -1604,7 +1620,6 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
     const gu64 *gfb = (const gu64 *)global_ptr(fb);
-    const double num = (double)eps.num, den = (double)eps.den;
     bool in = true;
     auto depth_q = [&](int j) {   // q as a double
         const double d = depth_of(P, T.td, x[j], y[j], z[j]);
@@ -1645,23 +1660,16 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
             arrive(near[k]);
     if (wave_any(!in))
         return false;
-    auto threshold = [&](uint64_t key) {
-        const double dm = int52_to_double(key >> 24);
-        const double r = num * (dm + P.z0d);
-        const double f = floor(r * eps.inv_den);
-        const double rem = __builtin_fma(-f, den, r);
-        return dm + (rem < 0.0 ? f - 1.0 : rem >= den ? f + 1.0 : f);
-    };
     typedef __attribute__((address_space(3))) double lf64;
 #pragma unroll
     for (int k = 0; k < kPre; ++k) {
         if (k > 0 && t.area <= 64u * k)
             break;
         if (lane + 64 * k < t.area)
-            *(lf64 *)(uintptr_t)(thr + 8 * (lane + 64 * k)) = threshold(near[k]);
+            *(lf64 *)(uintptr_t)(thr + 8 * (lane + 64 * k)) = window_threshold(P, eps, near[k]);
     }
     for (uint32_t i = lane + 64 * kPre; i < t.area; i += 64)
-        *(lf64 *)(uintptr_t)(thr + 8 * i) = threshold(gfb[tile_pixel(t, i)]);
+        *(lf64 *)(uintptr_t)(thr + 8 * i) = window_threshold(P, eps, gfb[tile_pixel(t, i)]);
     wave_sync();
     const uint32_t sub = lane & (four ? 3u : 1u);
     const uint32_t first = tile_first(t, base + 8 * sub, sh);

@@ -139,3 +139,36 @@ def test_wave_windows(rz, oracle, depth, eps):
     assert np.array_equal(rz.unpack_acc(acc), sums)
     _, _, img, _ = rz.rasterize_hq_splat(pts, v, depth=depth, eps=eps)
     assert np.array_equal(rz.to_u32(img), himg)
+
+
+@pytest.mark.parametrize("wh", [(1, 1), (5, 4), (8, 8), (13, 13), (14, 13), (16, 15), (22, 22),
+                                (31, 32), (33, 32), (120, 90)])
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7, 16])
+def test_point_squares(rz, oracle, wh, k):
+    """Squares of k x k pixels over rectangles of centres on both sides of every
+    limit of the wave's LDS (copies, row minima, row sums), in the middle of the
+    screen and against its corners: keys, sums and images."""
+    for i, (kw, depth) in enumerate([(dict(), (0, 0.0)), (dict(ox=0, oy=0), (1, 1000.0)),
+                                     (dict(ox=400 - wh[0], oy=300 - wh[1]), (0, 0.0)),
+                                     (dict(outside=3, behind=2), (0, 0.0)), (dict(pile=True), (0, 0.0)),
+                                     (dict(), (2, ((0.0, 1e9), (2.015, 1e6), (10.0, 1e3))))]):
+        c, v = rectangle_scene(*wh, n=700, seed=i, **kw)
+        args = (c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width, v.height, *depth)
+        pts = rz.Points.from_cloud(c)
+        keys, img = oracle.render_atomicmin(*args, bg=7, point_size=k)
+        fb, _, _, _ = rz.rasterize_points(pts, v, depth, point_size=k, background=7, keep_keys=True)
+        assert np.array_equal(rz.to_u64(fb), keys), (wh, k, kw, depth)
+        hk, sums, himg = oracle.render_hq(*args, bg=7, point_size=k)
+        fb, acc, _, _ = rz.rasterize_points(pts, v, depth, hq=True, point_size=k, background=7,
+                                            keep_keys=True)
+        assert np.array_equal(rz.to_u64(fb), hk)
+        assert np.array_equal(rz.unpack_acc(acc), sums), (wh, k, kw, depth)
+        _, _, got, st = rz.rasterize_points(pts, v, depth, hq=True, point_size=k, background=7)
+        assert np.array_equal(rz.to_u32(got), himg) and int(st.item()) == 0
+    for kind in (3, 4):   # the float encodings: depth pass
+        c, v = rectangle_scene(*wh, n=700, seed=9)
+        keys, _ = oracle.render_atomicmin(c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width,
+                                          v.height, kind, 0.0, point_size=k)
+        fb, _, _, _ = rz.rasterize_points(rz.Points.from_cloud(c), v, (kind, 0.0), point_size=k,
+                                          keep_keys=True)
+        assert np.array_equal(rz.to_u64(fb), keys)
