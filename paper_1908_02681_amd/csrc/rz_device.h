@@ -38,8 +38,7 @@ constexpr int kMaxWaves = 512 / 64;
 constexpr uint32_t kTileMin = 4096;          // workgroup tile of the depth pass: 32 KiB
 constexpr uint32_t kTileHq = 2048;           // workgroup tile of the accumulate pass: 32 KiB
 constexpr uint32_t kWaveTileWords = 1024;    // per-wave tile: 8 KiB of LDS
-constexpr uint32_t kWaveTileMin = kWaveTileWords;        // pixels (one key each)
-constexpr uint32_t kWaveTileHq = kWaveTileWords / 2;     // pixels (two sums each)
+constexpr uint32_t kWaveTileMin = kWaveTileWords;   // pixels (one key each)
 // The small per-wave tile (2 KiB): a quarter of the LDS per wave, so that
 // LDS no longer caps the waves per SIMD of kernels with few registers
 // (measured: the multi-view kernels at 4 points per thread).
@@ -358,40 +357,10 @@ __device__ __forceinline__ bool fragment(const Proj &P, float x, float y, float 
     return fragment<PW>(P, scalar_trans(P), x, y, z, px, py, q);
 }
 
-// fragment() for every depth encoding: the integer maps, the 24-bit window
-// depth of the perspective matrix (RZ_DEPTH_GL24) and the complemented
-// reversed float depth (RZ_DEPTH_F32REV).
-__device__ __forceinline__ bool fragment_any(const Proj &P, float x, float y, float z,
-                                             uint32_t &px, uint32_t &py, uint64_t &q)
-{
-    if (P.zkind == 0)
-        return fragment<true>(P, x, y, z, px, py, q);
-    float cw, iw;
-    if (!project(P, scalar_trans(P), x, y, z, px, py, cw, iw))
-        return false;
-    const double d = depth_of(P, x, y, z);
-    if (!(d >= P.near_ && d < P.far_))
-        return false;
-    if (P.zkind == RZ_DEPTH_F32REV) {
-        const float zr = P.nearf / cw;
-        q = 0xFFFFFFFFull - (uint64_t)__float_as_uint(zr);
-        return true;
-    }
-    float cz = __builtin_fmaf(P.mz[0], x, P.mz[3]);
-    cz = __builtin_fmaf(P.mz[1], y, cz);
-    cz = __builtin_fmaf(P.mz[2], z, cz);
-    const float nz = cz * iw;
-    if (!(nz >= -1.0f && nz <= 1.0f))
-        return false;
-    const float zw = (nz + 1.0f) * 0.5f;
-    const float t = zw * 16777215.0f;
-    q = (uint64_t)(uint32_t)floor((double)t + 0.5);
-    return true;
-}
-
-// fragment_any() for one float encoding, straight-line like fragment(): the
-// same arithmetic, with selects in place of the early returns, and the
-// 24-bit code converted only from a value inside the window.
+// fragment() for one of the float encodings, the 24-bit window depth of the
+// perspective matrix (RZ_DEPTH_GL24) or the complemented reversed float depth
+// (RZ_DEPTH_F32REV): straight-line, and the 24-bit code is converted only from a
+// value inside the window.
 template <int ZK>
 __device__ __forceinline__ bool fragment_zk(const Proj &P, const Trans &T, float x, float y,
                                             float z, uint32_t &px, uint32_t &py, uint64_t &q)
@@ -482,29 +451,7 @@ __device__ __forceinline__ void load_full(const Pts &p, int64_t base, float (&x)
     }
 }
 
-template <int PPT>
-__device__ __forceinline__ void load_ragged(const Pts &p, int64_t base, float (&x)[PPT],
-                                            float (&y)[PPT], float (&z)[PPT],
-                                            uint32_t (&c)[PPT], bool (&in)[PPT])
-{
-    const int64_t stride = 4 * (int64_t)blockDim.x;
-    const int64_t first = base + 4 * (int64_t)threadIdx.x;
-#pragma unroll
-    for (int g = 0; g < PPT / 4; ++g) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t i = first + g * stride + k;
-            const bool ok = i < p.n;
-            in[4 * g + k] = ok;
-            x[4 * g + k] = ok ? p.x[i] : 0.0f;
-            y[4 * g + k] = ok ? p.y[i] : 0.0f;
-            z[4 * g + k] = ok ? p.z[i] : 0.0f;
-            c[4 * g + k] = ok ? p.rgb[i] : 0u;
-        }
-    }
-}
-
-// The same loads for kernels that carry no per-point bounds flags: points
+// The loads of any chunk, for kernels that carry no per-point bounds flags: points
 // past the end read as NaN, which every projection culls (a NaN coordinate
 // makes clip w NaN, and w > 0 fails), so the chunk code is the same for the
 // last chunk as for all others.
@@ -531,21 +478,6 @@ __device__ __forceinline__ void load_points_nan(const Pts &p, int64_t base, floa
             z[4 * g + k] = ok ? p.z[i] : nan;
             c[4 * g + k] = ok ? p.rgb[i] : 0u;
         }
-    }
-}
-
-template <int PPT>
-__device__ __forceinline__ void load_points(const Pts &p, int64_t base, float (&x)[PPT],
-                                            float (&y)[PPT], float (&z)[PPT],
-                                            uint32_t (&c)[PPT], bool (&in)[PPT])
-{
-    if (chunk_full<PPT>(p, base)) {
-        load_full<PPT>(p, base, x, y, z, c);
-#pragma unroll
-        for (int j = 0; j < PPT; ++j)
-            in[j] = true;
-    } else {
-        load_ragged<PPT>(p, base, x, y, z, c, in);
     }
 }
 
@@ -783,33 +715,6 @@ __device__ __forceinline__ Box wave_box(const uint32_t (&px)[PPT], const uint32_
         hy = max(hy, max(d0, d1));
     }
     // no live lane: lx = ~0 > hx = 0, an empty box
-    return Box{wave_min(lx), wave_min(ly), wave_max(hx), wave_max(hy)};
-}
-
-// wave_box() for the wave kernels, one select fewer per coordinate: a point
-// that is off screen has pixel 0 (project()), which cannot raise a maximum,
-// so the maxima are taken over all points; the minima only over the live
-// ones.  Points on screen but outside [near, far) may widen the rectangle,
-// which then still bounds every live fragment.
-template <int PPT>
-__device__ __forceinline__ Box wave_box_live_min(const uint32_t (&px)[PPT],
-                                                 const uint32_t (&py)[PPT],
-                                                 const bool (&live)[PPT])
-{
-    static_assert(PPT % 2 == 0, "points are taken in pairs");
-    uint32_t lx = 0xFFFFFFFFu, ly = 0xFFFFFFFFu, hx = 0u, hy = 0u;
-#pragma unroll
-    for (int j = 0; j < PPT; j += 2) {   // pairs: three-operand min and max
-        const uint32_t a0 = live[j] ? px[j] : 0xFFFFFFFFu,
-                       a1 = live[j + 1] ? px[j + 1] : 0xFFFFFFFFu;
-        const uint32_t b0 = live[j] ? py[j] : 0xFFFFFFFFu,
-                       b1 = live[j + 1] ? py[j + 1] : 0xFFFFFFFFu;
-        lx = min(lx, min(a0, a1));
-        ly = min(ly, min(b0, b1));
-        hx = max(hx, max(px[j], px[j + 1]));
-        hy = max(hy, max(py[j], py[j + 1]));
-    }
-    // no live lane: lx = ~0 > hx, an empty box
     return Box{wave_min(lx), wave_min(ly), wave_max(hx), wave_max(hy)};
 }
 

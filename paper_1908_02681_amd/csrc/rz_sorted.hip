@@ -10,12 +10,12 @@
 //                      workgroups) and the bucket's total
 //      k_sort_scan     bucket starts and the chunk work list of E
 //   C  k_sort_scatter  the same ranges again, with the whole fragment (depth
-//                      in double precision).  Per step of 4096 points the
+//                      in double precision).  Per step of 8192 points the
 //                      workgroup sorts its entries by bucket in LDS (a
 //                      counting sort), then writes each bucket's run at its
 //                      own cursor in that bucket: consecutive lanes write
 //                      consecutive entries.  Entry = key (u64) + pixel in
-//                      the tile (u16).  (8192 points per step)
+//                      the tile (u16).
 //   D  k_sort_raster   an equal share of the entries per workgroup; per run
 //                      of one bucket in it: LDS minimum over the tile, then
 //                      one coalesced early-out atomic per touched pixel
