@@ -55,6 +55,15 @@ struct MvResolve {
     int32_t hq;
 };
 
+// Clouds of at least this many points read the nearest keys of a flush through the
+// XCD's L2 (read_nearest): a wave flushes eight views one after the other, and
+// what it waits for in each is that read.  64 views of 100M points 16.0 ms without,
+// 14.5 ms with (a launch of 8 depth passes 1.34 / 1.17 ms); 40 views of 10M 1.434 /
+// 1.403 ms, of 6M 1.127 / 1.126, of 3M 0.971 / 0.983: there the lines a wave meets
+// are still being filled, and an older key costs an atomic.  One-view passes gain
+// nothing (50M points 140.3 / 140.7 us) and read the current keys.
+constexpr int64_t kCachedReads = 8 << 20;
+
 // Depth passes of views[0 .. nv) over one chunk: the points are loaded
 // once and stay in registers while each view is rasterized in turn.
 template <int PPT, bool XCD, int BIN, bool PW>
@@ -81,6 +90,7 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         own(x[j]), own(y[j]), own(z[j]), own(c[j]);
+    const bool l2 = p.n >= kCachedReads;
     for (int32_t k = 0; k < nv; ++k) {
         const Proj P = views[k].P;
         const Trans T = lane_trans(P);
@@ -91,8 +101,8 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(
             uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
             MinFlush flush;
             raster_chunk_wave<PPT, PW>(P, T, views[k].fb, x, y, z, c, w_tile, words, flush,
-                                       [] {});
-            raster_wave_flush(views[k].fb, w_tile, flush);
+                                       [] {}, l2);
+            raster_wave_flush(views[k].fb, w_tile, flush, l2);
         } else {
             if (BIN == kBinBlock && k > 0)
                 __syncthreads();   // previous view's tile fully flushed

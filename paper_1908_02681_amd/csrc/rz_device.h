@@ -1066,10 +1066,20 @@ struct MinFlush {
     bool four;
 };
 
+// The nearest key of a pixel, for an early out.  With `l2` the read may be served
+// by the XCD's L2, where a neighbouring chunk left the line; the key may be older
+// then, but like any early one it is an upper bound (at its start a launch sees
+// at least what the launches before it wrote).
+__device__ __forceinline__ uint64_t read_nearest(const gu64 *p, bool l2)
+{
+    return l2 ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+              : __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The flush: one coalesced global atomic per touched pixel whose nearest key
 // it lowers.
 __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, const uint64_t *w_tile,
-                                                  MinFlush &f)
+                                                  MinFlush &f, bool l2 = false)
 {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t base = lds_addr(w_tile);
@@ -1093,7 +1103,7 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
         const uint64_t v = nearest(i);
         if (v != ~0ull) {
             gu64 *dst = gfb + tile_pixel(f.t, i);
-            const uint64_t was = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t was = read_nearest(dst, l2);
             if (v < was)
                 __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -1127,7 +1137,8 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
                                                  uint64_t *__restrict__ fb,
                                                  const float (&x)[PPT], const float (&y)[PPT],
                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                 uint64_t *w_tile, uint32_t words, MinFlush &flush)
+                                                 uint64_t *w_tile, uint32_t words, MinFlush &flush,
+                                                 bool l2)
 {
     float fx[PPT], fy[PPT];
     Box box;
@@ -1150,7 +1161,7 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
         const uint32_t p0 = tile_pixel(t, lane);
         uint64_t cur = 0ull;
         if (lane < t.area)
-            cur = __hip_atomic_load(gfb + p0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            cur = read_nearest(gfb + p0, l2);
         const bool four = 4 * t.area <= words;
         const uint32_t sh = four ? 5u : 3u;
         const uint32_t bytes = t.area << sh;
@@ -1217,9 +1228,10 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                                   const float (&x)[PPT], const float (&y)[PPT],
                                                   const float (&z)[PPT], const uint32_t (&c)[PPT],
                                                   uint64_t *w_tile, uint32_t words,
-                                                  MinFlush &flush, const Again &again)
+                                                  MinFlush &flush, const Again &again,
+                                                  bool l2 = false)
 {
-    if (raster_wave_fast<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, flush))
+    if (raster_wave_fast<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, flush, l2))
         return;
     again();
     raster_wave_any<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words);

@@ -172,3 +172,28 @@ def test_point_squares(rz, oracle, wh, k):
         fb, _, _, _ = rz.rasterize_points(rz.Points.from_cloud(c), v, (kind, 0.0), point_size=k,
                                           keep_keys=True)
         assert np.array_equal(rz.to_u64(fb), keys)
+
+
+@pytest.mark.parametrize("n", [(8 << 20) - 1, 8 << 20])
+def test_batch_reads_after_clears(rz, oracle, n):
+    """A batch at the size from which its flushes read nearest keys through the
+    L2: replays over the same framebuffers after the cloud moved away, so that a
+    key of an earlier run, were it read, would hide the points."""
+    import torch
+    c = gen.terrain(n, 5, extent=100.0, amplitude=10.0, wavelength=40.0)
+    views = gen.orbit_views(2, 11, [(200, 150), (97, 61)], extent=100.0, rmin=60.0, rmax=120.0,
+                            near=0.5, far=400.0)
+    pts = rz.Points.from_cloud(c)
+    b = rz.Batch(pts, views, [rz.RZ_MODE_ATOMICMIN, rz.RZ_MODE_HQ], launch=(256, 4, 1, 0, 3),
+                 use_graph=True)
+    scratch = torch.ones(1 << 20, device="cuda")
+    for y in (c.y, c.y - np.float32(7.0), c.y - np.float32(3.0)):
+        pts.y.copy_(torch.from_numpy(y))
+        wants = [f(c.x, y, c.z, c.rgb, v.vp, v.near, v.far, v.width, v.height)[-1]
+                 for f, v in zip((oracle.render_atomicmin, oracle.render_hq), views)]
+        for _ in range(2):
+            b.run()
+            scratch.mul_(1.5)
+            torch.cuda.synchronize()
+            for got, want in zip(b.images(), wants):
+                assert np.array_equal(got, want)
