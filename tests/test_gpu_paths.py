@@ -197,3 +197,23 @@ def test_batch_reads_after_clears(rz, oracle, n):
             torch.cuda.synchronize()
             for got, want in zip(b.images(), wants):
                 assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("k,hq", [(2, False), (3, True), (7, True)])
+def test_point_squares_after_clears(rz, oracle, k, hq):
+    """Frames of a cloud that moves away, into one framebuffer that each frame
+    leaves cleared: a key of an earlier frame, were it read, would hide points."""
+    import torch
+    c = gen.terrain(300_000, 5, extent=100.0, amplitude=10.0, wavelength=40.0)
+    v = gen.orbit_views(1, 11, [(200, 150)], extent=100.0, rmin=60.0, rmax=120.0, near=0.5,
+                        far=400.0)[0]
+    pts = rz.Points.from_cloud(c)
+    fb, acc = rz.new_framebuffer(v, 0, hq=hq)
+    for down in (0.0, 7.0, 3.0, 9.0):
+        y = c.y - np.float32(down)
+        pts.y.copy_(torch.from_numpy(y))
+        render = oracle.render_hq if hq else oracle.render_atomicmin
+        want = render(c.x, y, c.z, c.rgb, v.vp, v.near, v.far, v.width, v.height,
+                      point_size=k)[-1]
+        img = rz.rasterize_points(pts, v, hq=hq, point_size=k, fb=fb, acc=acc)[2]
+        assert np.array_equal(rz.to_u32(img), want)
