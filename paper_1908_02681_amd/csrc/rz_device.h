@@ -979,6 +979,16 @@ __device__ __forceinline__ Box wave_screen_box(const Proj &P, const Trans &T, co
     return Box{wave_min(lx), wave_min(ly), wave_max(hx), wave_max(hy)};
 }
 
+// The nearest key of a pixel, for an early out.  With `l2` the read may be served
+// by the XCD's L2, where a neighbouring chunk left the line; the key may be older
+// then, but like any early one it is an upper bound (at its start a launch sees
+// at least what the launches before it wrote).
+__device__ __forceinline__ uint64_t read_nearest(const gu64 *p, bool l2)
+{
+    return l2 ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+              : __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // raster_chunk_wave for any wave: each point with its own flags.  The points
 // are projected once for the rectangle and again for their keys, so that no
 // array of keys or pixels is held: these waves are few (those across the
@@ -989,7 +999,7 @@ __device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
                                                 uint64_t *__restrict__ fb, const float (&x)[PPT],
                                                 const float (&y)[PPT], const float (&z)[PPT],
                                                 const uint32_t (&c)[PPT], uint64_t *w_tile,
-                                                uint32_t words)
+                                                uint32_t words, bool early)
 {
     const Box box = wave_screen_box<PPT>(P, T, x, y, z);
     if (box.x0 > box.x1)
@@ -1032,8 +1042,7 @@ __device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
         } else {
 #pragma unroll
             for (int k = 0; k < G; ++k)   // a discarded fragment reads pixel 0
-                was[k] = __hip_atomic_load(gfb + (live[k] ? at[k] : 0u), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
+                was[k] = early ? read_nearest(gfb + (live[k] ? at[k] : 0u), false) : ~0ull;
 #pragma unroll
             for (int k = 0; k < G; ++k)
                 if (live[k] && key[k] < was[k])
@@ -1065,16 +1074,6 @@ struct MinFlush {
     uint64_t cur;
     bool four;
 };
-
-// The nearest key of a pixel, for an early out.  With `l2` the read may be served
-// by the XCD's L2, where a neighbouring chunk left the line; the key may be older
-// then, but like any early one it is an upper bound (at its start a launch sees
-// at least what the launches before it wrote).
-__device__ __forceinline__ uint64_t read_nearest(const gu64 *p, bool l2)
-{
-    return l2 ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
-              : __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // The flush: one coalesced global atomic per touched pixel whose nearest key
 // it lowers.
@@ -1115,7 +1114,8 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
 // raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
 // in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
 // Same result bits as raster_chunk, for any tile size.
-// raster_wave_flush must follow with the same `flush`.
+// raster_wave_flush must follow with the same `flush`.  Without `early`, fragments
+// of a wave that does not fit its tile go to the framebuffer unread.
 //
 // A wave whose points are all on screen and, as it turns out, in one range of
 // the depth map and in [near, far) needs no flag per point, and neither the
@@ -1138,7 +1138,7 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
                                                  const float (&x)[PPT], const float (&y)[PPT],
                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
                                                  uint64_t *w_tile, uint32_t words, MinFlush &flush,
-                                                 bool l2)
+                                                 bool l2, bool early)
 {
     float fx[PPT], fy[PPT];
     Box box;
@@ -1206,7 +1206,7 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
             vis[k] = (px >= 0.0f) & (px < P.fw) & (py >= 0.0f) & (py < P.fh);
             pix[k] = __umul24((uint32_t)(int32_t)(vis[k] ? py : 0.0f), t.width) +
                      (uint32_t)(int32_t)(vis[k] ? px : 0.0f);
-            cur[k] = __hip_atomic_load(gfb + pix[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            cur[k] = early ? read_nearest(gfb + pix[k], false) : ~0ull;
         }
 #pragma unroll
         for (int k = 0; k < G; ++k) {
@@ -1229,12 +1229,12 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                                   const float (&z)[PPT], const uint32_t (&c)[PPT],
                                                   uint64_t *w_tile, uint32_t words,
                                                   MinFlush &flush, const Again &again,
-                                                  bool l2 = false)
+                                                  bool l2 = false, bool early = true)
 {
-    if (raster_wave_fast<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, flush, l2))
+    if (raster_wave_fast<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, flush, l2, early))
         return;
     again();
-    raster_wave_any<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words);
+    raster_wave_any<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, early);
 }
 
 // Accumulation pass of high-quality splatting over one chunk (section 2.2).

@@ -49,6 +49,7 @@ struct Tune {
     int bin = 2;           // 0 none, 1 workgroup LDS tile, 2 per-wave LDS tile,
                            // 3 the small per-wave tile
     int by_size = 1;       // library default: small clouds take kSmallTune
+    int read_first = 1;    // per-wave tiles: early-out reads also beside the tile
 };
 
 constexpr Tune kHqTune = {64, 8, 1, 0, 3, 1};
@@ -60,6 +61,15 @@ constexpr Tune kHqTune = {64, 8, 1, 0, 3, 1};
 // 77.3), 10M 47.4 / 44.6 (101.7 / 100.6), 20M 71.9 / 72.4 (149.0 / 152.9).
 constexpr int64_t kSmallCloud = 8 << 20;
 constexpr Tune kSmallTune = {256, 4, 1, 0, 3, 1};
+// Clouds of fewer points than this do not fill the device, and a fragment beside
+// a tile (a cloud in no spatial order) costs the latencies of its early-out read and
+// of its atomic in turn, whatever the screen: they go without the read.  Frames,
+// with the read / without: spheres at 1024x768 0.2M points 19.3 / 17.0 us, 0.4M 29.5 /
+// 26.6, 0.8M 50.9 / 42.0, 1M 59.5 / 56.9, 1.3M 69.7 / 72.4, 2M 87.7 / 108.7; shuffled
+// terrain at 2560x1440 0.4M 37.0 / 31.7, 1M 62.8 / 56.7, 2M 98.1 / 95.5, at 320x200
+// 0.4M 48.0 / 34.3, 1M 106.5 / 78.1, 1.6M 123 / 123, 2M 131 / 151.
+constexpr int64_t kUnreadCloud = 1 << 20;
+constexpr Tune kUnreadTune = {256, 4, 1, 0, 3, 1, 0};
 
 // The splat window's eps = num / den, with 1 / den rounded once.
 struct Eps {

@@ -42,7 +42,8 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
         in[j] = true;
     if (BIN == kBinWave) {
         MinFlush flush;
-        raster_chunk_wave<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load);
+        raster_chunk_wave<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load,
+                                   false, EARLY);
         raster_wave_flush(fb, w_tile, flush);
     } else {
         raster_chunk<PPT, EARLY, BIN == kBinBlock, PW>(P, fb, x, y, z, c, in, s_tile, s_box);
@@ -51,7 +52,7 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
 
 // Depth pass for the float depth encodings (RZ_DEPTH_GL24, RZ_DEPTH_F32REV)
 // at one pixel per point: the per-wave tile kernel with the encoding's key.
-template <int PPT, int ZK>
+template <int PPT, int ZK, bool EARLY>
 __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *__restrict__ fb,
                                                        int64_t nchunks, uint32_t words)
 {
@@ -65,7 +66,8 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
     auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
     load();
     MinFlush flush;
-    raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load);
+    raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load,
+                                      false, EARLY);
     raster_wave_flush(fb, w_tile, flush);
 }
 
@@ -226,7 +228,10 @@ hipError_t raster_min_bin(const Pts &p, const Proj &P, uint64_t *fb, const Tune 
     switch (t.bin) {
     case kBinBlock: return raster_min_ppt<PPT, true, kBinBlock, PW>(p, P, fb, t, s);
     case kBinWave:
-    case kBinWaveSmall: return raster_min_ppt<PPT, true, kBinWave, PW>(p, P, fb, t, s);
+    case kBinWaveSmall:
+        if (PPT == 4 && !t.read_first)   // kUnreadTune
+            return raster_min_ppt<4, false, kBinWave, PW>(p, P, fb, t, s);
+        return raster_min_ppt<PPT, true, kBinWave, PW>(p, P, fb, t, s);
     default:
         return t.early_out ? raster_min_ppt<PPT, true, kBinNone, PW>(p, P, fb, t, s)
                            : raster_min_ppt<PPT, false, kBinNone, PW>(p, P, fb, t, s);
@@ -262,13 +267,13 @@ hipError_t hq_accum_dispatch(const Pts &p, const Proj &P, const Eps &eps,
                 : hq_accum_bin<PPT, false>(p, P, eps, fb, acc, t, s);
 }
 
-template <int PPT, int ZK>
+template <int PPT, int ZK, bool EARLY = true>
 hipError_t raster_min_zk(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t, hipStream_t s)
 {
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * PPT);
     const size_t lds = wave_lds(t.bin, t.block, false);
     const uint32_t words = wave_tile_words(t.bin, false);
-    hipLaunchKernelGGL((k_raster_min_zk<PPT, ZK>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
+    hipLaunchKernelGGL((k_raster_min_zk<PPT, ZK, EARLY>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
                        fb, nchunks, words);
     return hipGetLastError();
 }
@@ -278,7 +283,9 @@ hipError_t raster_min_zk_dispatch(const Pts &p, const Proj &P, uint64_t *fb, con
                                   hipStream_t s)
 {
     switch (t.ppt) {
-    case 4: return raster_min_zk<4, ZK>(p, P, fb, t, s);
+    case 4:
+        return t.read_first ? raster_min_zk<4, ZK>(p, P, fb, t, s)
+                            : raster_min_zk<4, ZK, false>(p, P, fb, t, s);
     case 8: return raster_min_zk<8, ZK>(p, P, fb, t, s);
     case 16: return raster_min_zk<16, ZK>(p, P, fb, t, s);
     default: return hipErrorInvalidValue;
@@ -297,7 +304,9 @@ hipError_t launch_raster_min(const Pts &p, const Proj &P, uint64_t *fb, const Tu
     // the small shape serves them longer: 20M points 71.0 us against 72.9, 50M
     // 159 against 148)
     const int64_t small = P.zkind != 0 ? 3 * kSmallCloud : kSmallCloud;
-    const Tune &t = tune.by_size && p.n < small ? kSmallTune : tune;
+    const Tune &t = !tune.by_size || p.n >= small ? tune
+                    : p.n < kUnreadCloud          ? kUnreadTune
+                                                  : kSmallTune;
     if (P.zkind != 0) {
         // float depth encodings: the per-wave tile kernel (either tile size),
         // the general point kernel for every other launch shape

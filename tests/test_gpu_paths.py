@@ -217,3 +217,20 @@ def test_point_squares_after_clears(rz, oracle, k, hq):
                       point_size=k)[-1]
         img = rz.rasterize_points(pts, v, hq=hq, point_size=k, fb=fb, acc=acc)[2]
         assert np.array_equal(rz.to_u32(img), want)
+
+
+@pytest.mark.parametrize("n", [1, 65, (1 << 20) - 1, 1 << 20])
+@pytest.mark.parametrize("depth", [(0, 0.0), (3, 0.0), (2, ((0.0, 1e9), (2.015, 1e6), (10.0, 1e3)))])
+def test_small_unordered_clouds(rz, oracle, n, depth):
+    """Shuffled clouds on both sides of the size from which fragments beside a tile
+    read the framebuffer first, partly off screen, into a framebuffer with keys."""
+    c = gen.shuffle(gen.terrain(n, 3, extent=60.0, amplitude=5.0, wavelength=20.0), 4)
+    v = gen.terrain_view(120, 90, extent=50.0, distance=45.0, near=0.5, far=400.0)
+    pts = rz.Points.from_cloud(c)
+    keys, img = oracle.render_atomicmin(c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width,
+                                        v.height, *depth)
+    draw = rz.rasterize_points if depth[0] == 3 else rz.rasterize_atomicmin
+    fb, _ = rz.new_framebuffer(v, 0)
+    for _ in range(2):   # the second time into the first one's keys
+        draw(pts, v, depth, fb=fb, keep_keys=True)
+        assert np.array_equal(rz.to_u64(fb), keys)
