@@ -1371,7 +1371,7 @@ __device__ __forceinline__ void accum_wave_any(const Proj &P, const Trans &T, co
         return;
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
-    const bool tiled = (t.area << kSh) <= 8 * words;
+    const bool tiled = tile_fits(t.area, words, kSh);
     const uint32_t base = lds_addr(w_tile);
     const gu64 *gfb = (const gu64 *)global_ptr(fb);
     gu64 *gacc = global_ptr(acc);

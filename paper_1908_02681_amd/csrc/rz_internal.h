@@ -77,6 +77,14 @@ struct Eps {
     double inv_den;
 };
 
+// Whether a rectangle of `area` pixels fits a tile of `words` 8-byte words at
+// 1 << sh bytes per pixel (sh >= 3).  A rectangle of a 32768 x 32768 screen has up
+// to 2^30 pixels: 32 bits hold its area, but not its bytes.
+__host__ __device__ constexpr bool tile_fits(uint32_t area, uint32_t words, uint32_t sh)
+{
+    return area <= words >> (sh - 3);
+}
+
 constexpr uint64_t kDepthOnes = 0xFFFFFFFFFF000000ull;
 constexpr uint64_t kRgbMask = 0xFFFFFFull;
 constexpr uint64_t kHqCountMax = 16843009ull;   // floor((2^32 - 1) / 255)
