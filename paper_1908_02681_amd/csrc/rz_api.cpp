@@ -177,7 +177,9 @@ int make_proj(const rz_view *v, const rz_depth_map *dm, Proj *P)
     auto top = [&](double d) { return floor((d - o) * s); };
     for (int32_t k = 0; k < 8; ++k)
         P->dlo[k] = P->dhi[k] = v->near_;
-    if (P->nr == 0) {
+    if (P->zkind != 0) {   // no integer depth, nothing to clamp
+        P->dhi[0] = v->far_;
+    } else if (P->nr == 0) {
         double hi = v->far_;
         if (top(hi) > kQRange - 1.0)
             hi = v->far_ - (v->far_ - v->near_) * 0x1p-20;

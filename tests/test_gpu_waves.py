@@ -69,3 +69,21 @@ def test_splat_waves_across_large_screens(rz, oracle, size, shape):
     torch.cuda.empty_cache()
     assert np.array_equal(got, np.array([want[i] for i in idx], got.dtype))
     assert written == len(idx)
+
+
+@pytest.mark.parametrize("kind", [3, 4])
+@pytest.mark.parametrize("k", [1, 3])
+def test_float_encodings_with_far_at_infinity(rz, oracle, kind, k):
+    """A far plane beyond any depth that a 40-bit map could hold: keys of the float
+    encodings, ordered and in no order."""
+    c = gen.terrain(60_000, 52, extent=100.0, amplitude=10.0, wavelength=40.0)
+    t = gen.orbit_views(1, 13, [(160, 120)], extent=100.0, rmin=60.0, rmax=120.0, near=0.5,
+                        far=400.0)[0]
+    v = gen.View(t.vp, t.near, 1e30, t.width, t.height)
+    for cloud in (c, gen.shuffle(c, 3)):
+        want, _ = oracle.render_atomicmin(cloud.x, cloud.y, cloud.z, cloud.rgb, v.vp, v.near, v.far,
+                                          v.width, v.height, kind, point_size=k)
+        assert (want != np.uint64(oracle.clear_value(0))).mean() > 0.1
+        fb, _, _, _ = rz.rasterize_points(rz.Points.from_cloud(cloud), v, (kind, 0.0), point_size=k,
+                                          keep_keys=True)
+        assert np.array_equal(rz.to_u64(fb), want)
