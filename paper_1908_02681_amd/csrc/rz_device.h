@@ -769,10 +769,11 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
 
 // Window positions of a wave's points: kOnScreen, with their pixel rectangle,
 // when every point of the wave has a w in [2^-126, 2^126) and an on-screen window
-// position; kOffScreen when all lie beyond one edge of the screen; kEdge, with
-// the on-screen part of their rectangle, when only w is known to be fine; kMixed
-// (and the rest meaningless) otherwise.  The first two are nearly all chunks of
-// an ordered cloud, and need no flag per point.  The tests run on bit patterns, where the order of
+// position; kOffScreen when all lie beyond one edge of the screen or behind the
+// camera (w negative or -0, which is never drawn); kEdge, with the on-screen part
+// of their rectangle, when only w is known to be fine; kMixed (and the rest
+// meaningless) otherwise.  The first two are nearly all chunks of an ordered cloud,
+// and need no flag per point.  The tests run on bit patterns, where the order of
 // non-negative floats is that of the integers and every other value (negative,
 // NaN, infinite) falls outside: w through an unsigned minimum and maximum, x
 // and y through signed ones.
@@ -820,8 +821,8 @@ __device__ __forceinline__ Where window_all(const Proj &P, const Trans &T, const
     const uint32_t lane = threadIdx.x & 63u;
     const bool odd = (lane & 16u) != 0;
     const int32_t size = (lane & 32u) ? __float_as_int(P.fh) : __float_as_int(P.fw);
-    if (wave_any((wlo < 0x00800000u) | (whi >= 0x7E800000u)))
-        return kMixed;
+    if (wave_any((wlo < 0x00800000u) | (whi >= 0x7E800000u)))   // some w <= 0: all of them?
+        return wave_any(wlo < 0x80000000u) ? kMixed : kOffScreen;
     // even rows: minimum >= 0; odd rows: maximum < size, on the complement
     const bool inside = m >= (odd ? -size : 0);
     if (wave_any(m >= (odd ? 0 : size)))   // a minimum >= size or a maximum < 0

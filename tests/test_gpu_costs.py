@@ -1,0 +1,66 @@
+"""What a call costs beside another of the same size, in time: frames whose waves leave
+the kernels' common path against frames whose waves do not.  The limits are ratios of
+two times taken in turn on one device; each lies well between what the kernels give
+and what they gave with the fault that the test stands for, both beside it."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1908_02681_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rz():
+    from paper_1908_02681_amd import rz as m
+    m.load()
+    return m
+
+
+@pytest.fixture(scope="module")
+def terrain(rz):
+    return rz.Points.from_cloud(gen.terrain(30_000_000, 42))
+
+
+def frame(rz, pts, view, hq=False, depth=(0, 0.0), eps=(1, 100), size=1):
+    import torch
+    fb, acc = rz.new_framebuffer(view, 0, hq=hq)
+    img = torch.empty(view.width * view.height, dtype=torch.int32, device="cuda")
+    kw = {"depth": depth, "fb": fb, "img": img}
+    if hq:
+        kw.update(acc=acc, eps=eps, status=torch.zeros(1, dtype=torch.int32, device="cuda"))
+    return lambda: rz.rasterize_points(pts, view, hq=hq, point_size=size, **kw)
+
+
+def ratio(label, run, base):
+    """Time of `run` by that of `base`: the least of eight times of ten calls each."""
+    import torch
+    best = [1e30, 1e30]
+    for _ in range(8):
+        for i, f in enumerate((run, base)):
+            f()
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                f()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 100)
+    print(f"[cost] {label}: {best[0]:.1f} us by {best[1]:.1f} us = {best[0] / best[1]:.2f}",
+          flush=True)
+    sys.stdout.flush()
+    return best[0] / best[1]
+
+
+HD = gen.terrain_view(1920, 1080)
+
+
+@pytest.mark.parametrize("hq", [False, True])
+def test_clouds_behind_the_camera(rz, terrain, hq):
+    """Every wave behind the camera: no more than the cloud's reads."""
+    away = gen.make_view((500.0, -300.0, 300.0), (500.0, -900.0, 300.0), (0, 0, 1), 60.0, 1920, 1080,
+                         0.5, 4000.0)
+    r = ratio(f"behind hq={hq}", frame(rz, terrain, away, hq), frame(rz, terrain, HD, hq))
+    assert r < 1.15   # 0.8; 1.55 with waves rasterized twice

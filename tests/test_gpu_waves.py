@@ -87,3 +87,52 @@ def test_float_encodings_with_far_at_infinity(rz, oracle, kind, k):
         fb, _, _, _ = rz.rasterize_points(rz.Points.from_cloud(cloud), v, (kind, 0.0), point_size=k,
                                           keep_keys=True)
         assert np.array_equal(rz.to_u64(fb), want)
+
+
+def render_all(rz, oracle, c, v, depth=(0, 0.0), eps=(1, 100), shape=None, sizes=(1, 2, 3)):
+    """Keys, splat sums and batch images of one scene against the oracle's."""
+    args = (c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width, v.height, *depth)
+    pts = rz.Points.from_cloud(c)
+    rz.reset_launch() if shape is None else rz.set_launch(*shape)
+    try:
+        for k in sizes:
+            keys, img = oracle.render_atomicmin(*args, point_size=k)
+            fb, _, _, _ = rz.rasterize_points(pts, v, depth, point_size=k, keep_keys=True)
+            assert np.array_equal(rz.to_u64(fb), keys), (k, "keys")
+            _, sums, himg = oracle.render_hq(*args, eps=eps, point_size=k)
+            _, acc, _, _ = rz.rasterize_points(pts, v, depth, True, eps, k, keep_keys=True)
+            assert np.array_equal(rz.unpack_acc(acc), sums), (k, "sums")
+            if k == 1:
+                b = rz.Batch(pts, [v, v, v], [0, 1, 0], depth=depth, eps=eps, launch=shape)
+                b.run()
+                got = b.images()
+                assert np.array_equal(got[0], img) and np.array_equal(got[2], img)
+                assert np.array_equal(got[1], himg)
+    finally:
+        rz.reset_launch()
+
+
+SHAPES = [None, (64, 8, 1, 0, 3), (64, 16, 1, 0, 2)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("what", ["behind", "at zero", "a few in front", "a few at zero", "nan"])
+def test_waves_behind_the_camera(rz, oracle, what, shape):
+    """Whole waves with w < 0, w = -0 and w NaN beside waves in front, and waves of which a
+    few points are in front of the camera or in its plane (w = 0)."""
+    n = 6000
+    c, v = rectangle_scene(40, 30, n, 8)
+    part = np.arange(n // 4, 3 * n // 4)
+    if what == "nan":
+        c.z[part] = np.nan
+    else:
+        c.x[part], c.y[part], c.z[part] = -c.x[part], -c.y[part], -c.z[part]
+    if what == "at zero":
+        c.x[part], c.y[part], c.z[part] = -np.abs(c.x[part]), -np.abs(c.y[part]), -0.0
+        v.vp[3, 3] = -0.0   # w = -0 for them
+    if what == "a few in front":
+        some = part[::57]
+        c.x[some], c.y[some], c.z[some] = -c.x[some], -c.y[some], -c.z[some]
+    if what == "a few at zero":
+        c.z[part[::57]] = 0.0
+    render_all(rz, oracle, c, v, shape=shape)
