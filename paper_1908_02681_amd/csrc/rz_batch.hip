@@ -100,8 +100,7 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(
         if (BIN == kBinWave) {
             uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
             MinFlush flush;
-            raster_chunk_wave<PPT, PW>(P, T, views[k].fb, x, y, z, c, w_tile, words, flush,
-                                       [] {}, l2);
+            raster_chunk_wave<PPT, PW>(P, T, views[k].fb, x, y, z, c, w_tile, words, flush, l2);
             raster_wave_flush(views[k].fb, w_tile, flush, l2);
         } else {
             if (BIN == kBinBlock && k > 0)

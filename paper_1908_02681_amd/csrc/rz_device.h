@@ -35,6 +35,7 @@ namespace dev {
 constexpr double kQMax = 1099511627774.0;   // 2^40 - 2
 constexpr int kXcds = 8;                     // XCDs of an MI355X
 constexpr int kMaxWaves = 512 / 64;
+constexpr uint32_t kMaxPixel = 32767;        // of a row or column: screens have at most 2^15
 constexpr uint32_t kTileMin = 4096;          // workgroup tile of the depth pass: 32 KiB
 constexpr uint32_t kTileHq = 2048;           // workgroup tile of the accumulate pass: 32 KiB
 constexpr uint32_t kWaveTileWords = 1024;    // per-wave tile: 8 KiB of LDS
@@ -357,36 +358,50 @@ __device__ __forceinline__ bool fragment(const Proj &P, float x, float y, float 
     return fragment<PW>(P, scalar_trans(P), x, y, z, px, py, q);
 }
 
-// fragment() for one of the float encodings, the 24-bit window depth of the
-// perspective matrix (RZ_DEPTH_GL24) or the complemented reversed float depth
-// (RZ_DEPTH_F32REV): straight-line, and the 24-bit code is converted only from a
-// value inside the window.
+// Depth of one point in any of the encodings, without the assumptions of a chunk
+// (ChunkKey): clears `in` for a point outside [near, far) or clipped by the 24-bit
+// window depth of the perspective matrix (RZ_DEPTH_GL24), whose depth is then
+// meaningless.  ZK = 0 for the integer maps; cw and iw = 1 / cw are read by the
+// float encodings only (RZ_DEPTH_F32REV: the complemented reversed float depth).
+// Straight-line, and the 24-bit code is converted only from a value inside the window.
+template <bool PW, int ZK>
+__device__ __forceinline__ uint64_t depth_enc(const Proj &P, const Trans &T, float x, float y,
+                                              float z, float cw, float iw, bool &in)
+{
+    const double d = depth_of(P, T, x, y, z);
+    const bool in_range = (d >= P.near_) & (d < P.far_);
+    in = in & in_range;
+    if constexpr (ZK == 0) {
+        if (PW && P.nr != 0)
+            return piecewise_q(P, in_range ? d : P.near_);
+        return to_u64(fmin(floor((d - P.o) * P.s), kQMax));   // d < near gives garbage, unused
+    }
+    if constexpr (ZK == RZ_DEPTH_F32REV)
+        return 0xFFFFFFFFull - (uint64_t)__float_as_uint(P.nearf / cw);
+    float cz = __builtin_fmaf(P.mz[0], x, P.mz[3]);
+    cz = __builtin_fmaf(P.mz[1], y, cz);
+    cz = __builtin_fmaf(P.mz[2], z, cz);
+    const float nz = cz * iw;
+    const bool clip = (nz >= -1.0f) & (nz <= 1.0f);
+    in = in & clip;
+    const float zw = (nz + 1.0f) * 0.5f;
+    const float t = zw * 16777215.0f;
+    return (uint64_t)(uint32_t)floor((double)(clip ? t : 0.0f) + 0.5);
+}
+
+// The fragment of one point in a float encoding (ZK).
 template <int ZK>
 __device__ __forceinline__ bool fragment_zk(const Proj &P, const Trans &T, float x, float y,
                                             float z, uint32_t &px, uint32_t &py, uint64_t &q)
 {
     static_assert(ZK == RZ_DEPTH_GL24 || ZK == RZ_DEPTH_F32REV, "float encodings only");
     float cw, iw;
-    const bool vis = project(P, T, x, y, z, px, py, cw, iw);
+    bool in = project(P, T, x, y, z, px, py, cw, iw);
     q = 0;
-    if (!wave_any(vis))
+    if (!wave_any(in))
         return false;
-    const double d = depth_of(P, T, x, y, z);
-    const bool in_range = (d >= P.near_) & (d < P.far_);
-    if (ZK == RZ_DEPTH_F32REV) {
-        const float zr = P.nearf / cw;
-        q = 0xFFFFFFFFull - (uint64_t)__float_as_uint(zr);
-        return vis & in_range;
-    }
-    float cz = __builtin_fmaf(P.mz[0], x, P.mz[3]);
-    cz = __builtin_fmaf(P.mz[1], y, cz);
-    cz = __builtin_fmaf(P.mz[2], z, cz);
-    const float nz = cz * iw;
-    const bool clip = (nz >= -1.0f) & (nz <= 1.0f);
-    const float zw = (nz + 1.0f) * 0.5f;
-    const float t = zw * 16777215.0f;
-    q = (uint64_t)(uint32_t)floor((double)(clip ? t : 0.0f) + 0.5);
-    return vis & in_range & clip;
+    q = depth_enc<false, ZK>(P, T, x, y, z, cw, iw, in);
+    return in;
 }
 
 // The fragment of the kernels templated on the depth encoding: ZK = 0 for
@@ -722,6 +737,7 @@ __device__ __forceinline__ Box wave_box(const uint32_t (&px)[PPT], const uint32_
 // derived from v over to here in further registers.
 __device__ __forceinline__ void own(float &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void own(uint32_t &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void own(int32_t &v) { asm volatile("" : "+v"(v)); }
 
 // The loads of v end here, whether v is used or not: a register with a load
 // pending would make whatever takes it next wait for every memory operation
@@ -767,6 +783,35 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
     return v;
 }
 
+// Minima of x and y and the complements of their maxima over a wave, in the rows of
+// 16 lanes: x's minimum, x's maximum, y's minimum, y's maximum.  The four reductions
+// share their steps: two half-wave swaps leave x (rows 0, 1) beside y (rows 2, 3), a
+// row swap puts the minima into the even rows and the complemented maxima into the
+// odd ones, and one 16-lane reduction finishes all four: 11 instructions where four
+// 64-lane reductions take 24.
+__device__ __forceinline__ int32_t wave_bounds(int32_t xlo, int32_t xhi, int32_t ylo, int32_t yhi)
+{
+    // rows 0 and 1: x, rows 2 and 3: y
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)xlo, (uint32_t)ylo, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)~xhi, (uint32_t)~yhi, false, false);
+    const int32_t l2 = min((int32_t)lo[0], (int32_t)lo[1]);
+    const int32_t h2 = min((int32_t)hi[0], (int32_t)hi[1]);
+    // rows 0 and 2: the minima, rows 1 and 3: the complements of the maxima
+    const auto lh = __builtin_amdgcn_permlane16_swap((uint32_t)l2, (uint32_t)h2, false, false);
+    return row_min(min((int32_t)lh[0], (int32_t)lh[1]));
+}
+
+// The rectangle of which wave_bounds() left the sides `v` in its rows.
+__device__ __forceinline__ Box bounds_box(int32_t v)
+{
+    Box box;
+    box.x0 = (uint32_t)__builtin_amdgcn_readlane(v, 0);
+    box.x1 = (uint32_t)__builtin_amdgcn_readlane(v, 16);
+    box.y0 = (uint32_t)__builtin_amdgcn_readlane(v, 32);
+    box.y1 = (uint32_t)__builtin_amdgcn_readlane(v, 48);
+    return box;
+}
+
 // Window positions of a wave's points: kOnScreen, with their pixel rectangle,
 // when every point of the wave has a w in [2^-126, 2^126) and an on-screen window
 // position; kOffScreen when all lie beyond one edge of the screen or behind the
@@ -777,12 +822,6 @@ __device__ __forceinline__ int32_t row_min(int32_t v)
 // non-negative floats is that of the integers and every other value (negative,
 // NaN, infinite) falls outside: w through an unsigned minimum and maximum, x
 // and y through signed ones.
-//
-// The four reductions over the lanes share their steps: two half-wave swaps
-// leave x (rows 0, 1) beside y (rows 2, 3), a row swap puts the minima into
-// the even rows and the complemented maxima into the odd ones, and one 16-lane
-// reduction finishes all four: 11 instructions where four 64-lane reductions
-// take 24.
 enum Where { kOnScreen, kOffScreen, kEdge, kMixed };
 
 template <int PPT>
@@ -810,14 +849,7 @@ __device__ __forceinline__ Where window_all(const Proj &P, const Trans &T, const
         if (j % 4)
             __builtin_amdgcn_sched_barrier(0);
     }
-    // rows 0 and 1: x, rows 2 and 3: y
-    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)xlo, (uint32_t)ylo, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)~xhi, (uint32_t)~yhi, false, false);
-    const int32_t l2 = min((int32_t)lo[0], (int32_t)lo[1]);
-    const int32_t h2 = min((int32_t)hi[0], (int32_t)hi[1]);
-    // rows 0 and 2: the minima, rows 1 and 3: the complements of the maxima
-    const auto lh = __builtin_amdgcn_permlane16_swap((uint32_t)l2, (uint32_t)h2, false, false);
-    const int32_t m = row_min(min((int32_t)lh[0], (int32_t)lh[1]));
+    const int32_t m = wave_bounds(xlo, xhi, ylo, yhi);
     const uint32_t lane = threadIdx.x & 63u;
     const bool odd = (lane & 16u) != 0;
     const int32_t size = (lane & 32u) ? __float_as_int(P.fh) : __float_as_int(P.fw);
@@ -830,13 +862,79 @@ __device__ __forceinline__ Where window_all(const Proj &P, const Trans &T, const
     // the minima and maxima as pixels, cut at the screen's edge
     const float edge = odd ? __int_as_float(size) - 1.0f : 0.0f;
     const int32_t px = (int32_t)(inside ? __int_as_float(odd ? ~m : m) : edge);
-    box.x0 = (uint32_t)__builtin_amdgcn_readlane(px, 0);
-    box.x1 = (uint32_t)__builtin_amdgcn_readlane(px, 16);
-    box.y0 = (uint32_t)__builtin_amdgcn_readlane(px, 32);
-    box.y1 = (uint32_t)__builtin_amdgcn_readlane(px, 48);
+    box = bounds_box(px);
     if (wave_any(!inside))
         return kEdge;
     return kOnScreen;
+}
+
+// A window position on screen.
+__device__ __forceinline__ bool on_screen(const Proj &P, float fx, float fy)
+{
+    return (fx >= 0.0f) & (fx < P.fw) & (fy >= 0.0f) & (fy < P.fh);
+}
+
+// Clip w of one point, with no register shared with the projection's.
+__device__ __forceinline__ float clip_w(const Proj &P, const Trans &T, float x, float y, float z)
+{
+    own(x), own(y), own(z);
+    float cw = __builtin_fmaf(P.m[8], x, T.tw);
+    cw = __builtin_fmaf(P.m[9], y, cw);
+    return __builtin_fmaf(P.m[10], z, cw);
+}
+
+// Whether point j of a wave is on screen, from its window position: in a wave with
+// points of w <= 0 or NaN (mixed, wave-uniform) by the sign of w too.
+template <int PPT>
+__device__ __forceinline__ bool point_visible(const Proj &P, const Trans &T, bool mixed, int j,
+                                              const float (&x)[PPT], const float (&y)[PPT],
+                                              const float (&z)[PPT], float wx, float wy)
+{
+    bool vis = on_screen(P, wx, wy);
+    if (mixed)
+        vis = vis & (clip_w(P, T, x[j], y[j], z[j]) > 0.0f);
+    return vis;
+}
+
+// Some point of a wave has a positive w outside [2^-126, 2^126), so that its window
+// position is not the one by the IEEE quotient.
+template <int PPT>
+__device__ __forceinline__ bool any_slow_w(const Proj &P, const Trans &T, const float (&x)[PPT],
+                                           const float (&y)[PPT], const float (&z)[PPT])
+{
+    bool slow = false;
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+        const float cw = clip_w(P, T, x[j], y[j], z[j]);
+        slow = slow | ((cw > 0.0f) & ((cw < 0x1p-126f) | (cw >= 0x1p126f)));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return wave_any(slow);
+}
+
+// Box of the on-screen points of a wave; without one, x1 lies beyond kMaxPixel.
+template <int PPT>
+__device__ __forceinline__ Box window_box(const Proj &P, const Trans &T, bool mixed,
+                                          const float (&x)[PPT], const float (&y)[PPT],
+                                          const float (&z)[PPT], const float (&fx)[PPT],
+                                          const float (&fy)[PPT])
+{
+    int32_t xlo = 0x7FFFFFFF, ylo = 0x7FFFFFFF, xhi = -1, yhi = -1;
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+        float wx = fx[j], wy = fy[j];
+        own(wx), own(wy);
+        const bool vis = point_visible<PPT>(P, T, mixed, j, x, y, z, wx, wy);
+        const int32_t px = (int32_t)(vis ? wx : 0.0f), py = (int32_t)(vis ? wy : 0.0f);
+        xlo = min(xlo, vis ? px : 0x7FFFFFFF);
+        ylo = min(ylo, vis ? py : 0x7FFFFFFF);
+        xhi = max(xhi, vis ? px : -1);
+        yhi = max(yhi, vis ? py : -1);
+        // this point's work ends here, and with it its registers
+        own(xlo), own(ylo), own(xhi), own(yhi);
+    }
+    const int32_t m = wave_bounds(xlo, xhi, ylo, yhi);
+    return bounds_box((threadIdx.x & 16u) != 0 ? ~m : m);
 }
 
 // One uniform range of the depth map for a whole chunk: the linear and scale
@@ -990,83 +1088,6 @@ __device__ __forceinline__ uint64_t read_nearest(const gu64 *p, bool l2)
               : __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// raster_chunk_wave for any wave: each point with its own flags.  The points
-// are projected once for the rectangle and again for their keys, so that no
-// array of keys or pixels is held: these waves are few (those across the
-// screen's edge or a range of the depth map), and the registers of this path
-// are those of the whole kernel.
-template <int PPT, bool PW, int ZK>
-__device__ __forceinline__ void raster_wave_any(const Proj &P, const Trans &T,
-                                                uint64_t *__restrict__ fb, const float (&x)[PPT],
-                                                const float (&y)[PPT], const float (&z)[PPT],
-                                                const uint32_t (&c)[PPT], uint64_t *w_tile,
-                                                uint32_t words, bool early)
-{
-    const Box box = wave_screen_box<PPT>(P, T, x, y, z);
-    if (box.x0 > box.x1)
-        return;
-    const uint32_t lane = threadIdx.x & 63u;
-    const WaveTile t = wave_tile(P, box);
-    const bool tiled = t.area <= words;
-    const uint32_t base = lds_addr(w_tile);
-    gu64 *gfb = global_ptr(fb);
-    if (tiled) {
-        for (uint32_t i = lane; i < t.area; i += 64)
-            *lds_ptr(base + 8 * i) = ~0ull;
-        wave_sync();
-    }
-    const uint32_t first = tile_first(t, base, 3);
-    constexpr int G = 4;   // early-out reads in flight
-#pragma unroll
-    for (int g = 0; g < PPT; g += G) {
-        uint32_t at[G];   // LDS entry or pixel
-        uint64_t key[G], was[G];
-        bool live[G];
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            float xx = x[g + k], yy = y[g + k], zz = z[g + k];
-            own(xx), own(yy), own(zz);
-            uint32_t px = 0, py = 0;
-            uint64_t q = 0;
-            live[k] = fragment_enc<PW, ZK>(P, T, xx, yy, zz, px, py, q);
-            key[k] = (q << 24) | ((uint64_t)c[g + k] & kRgbMask);
-            at[k] = tiled ? ((__umul24(py, t.bw) + px) << 3) + first
-                          : __umul24(py, t.width) + px;
-            own(at[k]);
-        }
-        if (tiled) {
-#pragma unroll
-            for (int k = 0; k < G; ++k)
-                if (live[k])
-                    __hip_atomic_fetch_min(lds_ptr(at[k]), key[k], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-        } else {
-#pragma unroll
-            for (int k = 0; k < G; ++k)   // a discarded fragment reads pixel 0
-                was[k] = early ? read_nearest(gfb + (live[k] ? at[k] : 0u), false) : ~0ull;
-#pragma unroll
-            for (int k = 0; k < G; ++k)
-                if (live[k] && key[k] < was[k])
-                    __hip_atomic_fetch_min(gfb + at[k], key[k], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (!tiled)
-        return;
-    wave_sync();
-    for (uint32_t i = lane; i < t.area; i += 64) {
-        const uint64_t v = *lds_ptr(base + 8 * i);
-        if (v != ~0ull) {
-            gu64 *dst = gfb + tile_pixel(t, i);
-            const uint64_t was = __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (v < was)
-                __hip_atomic_fetch_min(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    wave_sync();   // the tile is free for the next use
-}
-
 // What raster_chunk_wave leaves to be flushed: its tile (area 0: nothing), and
 // of the lane's first entry the pixel and the nearest key read before.
 struct MinFlush {
@@ -1111,6 +1132,22 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
     wave_sync();   // the tile is free for the next use
 }
 
+// Key of a point of any wave; clears `in` for a point that takes no part.
+template <bool PW, int ZK>
+__device__ __forceinline__ uint64_t key_any(const Proj &P, const Trans &T, float x, float y,
+                                            float z, uint32_t c, bool &in)
+{
+    own(x), own(y), own(z);   // nothing of ChunkKey's is kept for here
+    float cw = 0.0f, iw = 0.0f;
+    if constexpr (ZK != 0) {
+        cw = clip_w(P, T, x, y, z);
+        if constexpr (ZK == RZ_DEPTH_GL24)
+            iw = recip_rn(cw);
+    }
+    const uint64_t q = depth_enc<PW, ZK>(P, T, x, y, z, cw, iw, in);
+    return (q << 24) | ((uint64_t)c & kRgbMask);
+}
+
 // Depth pass over one chunk with a private LDS tile per wave: like
 // raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
 // in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
@@ -1120,10 +1157,9 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
 //
 // A wave whose points are all on screen and, as it turns out, in one range of
 // the depth map and in [near, far) needs no flag per point, and neither the
-// clamp nor the test for a slow reciprocal; every other one takes
-// raster_wave_any, for which again() puts the points back into x .. c: where it
-// loads them anew (they are in the L2 then), they need not be held in registers
-// till it is known (16 points a thread: 122 registers, 158 with them).
+// clamp nor the test for a slow reciprocal.  Every other wave goes on from the same
+// window positions with flags per point (key_any), so that no point is loaded or
+// projected again.
 //
 // The nearest keys that the flush compares with are read before the depths are
 // computed, so that their latency passes meanwhile (a key read early is an upper
@@ -1133,13 +1169,14 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
 // neighbouring lanes hold neighbouring points, and LDS atomics of one address
 // follow each other one per cycle (a depth pass of 100M points over 8 views:
 // 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
-template <int PPT, bool PW, int ZK>
-__device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
-                                                 uint64_t *__restrict__ fb,
-                                                 const float (&x)[PPT], const float (&y)[PPT],
-                                                 const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                 uint64_t *w_tile, uint32_t words, MinFlush &flush,
-                                                 bool l2, bool early)
+template <int PPT, bool PW, int ZK = 0>
+__device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
+                                                  uint64_t *__restrict__ fb,
+                                                  const float (&x)[PPT], const float (&y)[PPT],
+                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                  uint64_t *w_tile, uint32_t words,
+                                                  MinFlush &flush, bool l2 = false,
+                                                  bool early = true)
 {
     float fx[PPT], fy[PPT];
     Box box;
@@ -1147,17 +1184,33 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
     flush.cur = 0;
     const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
     if (where == kOffScreen)
-        return true;
-    if (where == kMixed)
-        return false;
+        return;
+    gu64 *gfb = global_ptr(fb);
+    const bool mixed = where == kMixed;
+    if (mixed && any_slow_w<PPT>(P, T, x, y, z)) {   // no wave in practice
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            float xx = x[j], yy = y[j], zz = z[j];
+            own(xx), own(yy), own(zz);
+            uint32_t px, py;
+            uint64_t q;
+            if (fragment_enc<PW, ZK>(P, T, xx, yy, zz, px, py, q))
+                __hip_atomic_fetch_min(gfb + (__umul24(py, (uint32_t)P.width) + px),
+                                       (q << 24) | ((uint64_t)c[j] & kRgbMask), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
+    }
+    if (where != kOnScreen) {
+        box = window_box<PPT>(P, T, mixed, x, y, z, fx, fy);
+        if (box.x1 > kMaxPixel)   // no point on screen
+            return;
+    }
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
-    gu64 *gfb = global_ptr(fb);
     const ChunkKey<PW, ZK> key_of(P, T, x[0], y[0], z[0]);
-    bool in = true;
     if (t.area <= words) {
-        if (where == kEdge)
-            return false;
         const uint32_t base = lds_addr(w_tile);
         const uint32_t p0 = tile_pixel(t, lane);
         uint64_t cur = 0ull;
@@ -1166,76 +1219,91 @@ __device__ __forceinline__ bool raster_wave_fast(const Proj &P, const Trans &T,
         const bool four = 4 * t.area <= words;
         const uint32_t sh = four ? 5u : 3u;
         const uint32_t bytes = t.area << sh;
-        u64x2 none;
-        none.x = none.y = ~0ull;
-        if (16 * lane < bytes)
-            *lds_ptr2(base + 16 * lane) = none;
-        for (uint32_t i = 1024 + 16 * lane; i < bytes; i += 1024)
-            *lds_ptr2(base + i) = none;
-        wave_sync();
         const uint32_t first = tile_first(t, base + (four ? 8 * (lane & 3u) : 0u), sh);
+        auto clear = [&] {
+            u64x2 none;
+            none.x = none.y = ~0ull;
+            if (16 * lane < bytes)
+                *lds_ptr2(base + 16 * lane) = none;
+            for (uint32_t i = 1024 + 16 * lane; i < bytes; i += 1024)
+                *lds_ptr2(base + i) = none;
+            wave_sync();
+        };
+        clear();
+        bool in = where == kOnScreen;
+        if (where == kOnScreen) {
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-            __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)), key_of(x[j], y[j], z[j], c[j], in),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (j % 2)
+            for (int j = 0; j < PPT; ++j) {
+                __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)),
+                                       key_of(x[j], y[j], z[j], c[j], in), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (j % 2)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
+            wave_sync();
+        }
+        if (wave_any(!in)) {   // flags per point
+            clear();
+#pragma unroll
+            for (int j = 0; j < PPT; ++j) {
+                float px = fx[j], py = fy[j];
+                own(px), own(py);
+                bool live = point_visible<PPT>(P, T, mixed, j, x, y, z, px, py);
+                const uint64_t key = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live);
+                if (live)
+                    __hip_atomic_fetch_min(lds_ptr(tile_entry(t, px, py, sh, first)), key,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 __builtin_amdgcn_sched_barrier(0);
+            }
+            wave_sync();
         }
-        wave_sync();
         flush = MinFlush{t, p0, cur, four};
-        if (wave_any(!in)) {
-            arrive(flush.cur);
-            flush.t.area = 0;
-            return false;
-        }
-        return true;
+        return;
     }
     // spread too far for the tile: groups of four points, their early-out reads
-    // in flight while their keys are computed; here points off screen are no
-    // reason to leave.  A point out of range takes no part, and then the whole
-    // chunk is redone by the caller (a minimum may be taken twice).
+    // in flight while their keys are computed.  A point out of range takes the
+    // general key, and from then on all do.
     constexpr int G = 4;
-    bool all = true;
+    bool general = false;
 #pragma unroll
     for (int g = 0; g < PPT; g += G) {
         uint32_t pix[G];
-        uint64_t cur[G];
-        bool vis[G];
+        uint64_t key[G], cur[G];
+        bool vis[G], live[G];
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            const float px = fx[g + k], py = fy[g + k];
-            vis[k] = (px >= 0.0f) & (px < P.fw) & (py >= 0.0f) & (py < P.fh);
-            pix[k] = __umul24((uint32_t)(int32_t)(vis[k] ? py : 0.0f), t.width) +
-                     (uint32_t)(int32_t)(vis[k] ? px : 0.0f);
+            float wx = fx[g + k], wy = fy[g + k];
+            own(wx), own(wy);
+            vis[k] = point_visible<PPT>(P, T, mixed, g + k, x, y, z, wx, wy);
+            pix[k] = __umul24((uint32_t)(int32_t)(vis[k] ? wy : 0.0f), t.width) +
+                     (uint32_t)(int32_t)(vis[k] ? wx : 0.0f);
             cur[k] = early ? read_nearest(gfb + pix[k], false) : ~0ull;
         }
+        if (!general) {
+            bool all = true;
 #pragma unroll
-        for (int k = 0; k < G; ++k) {
-            in = true;
-            const uint64_t key = key_of(x[g + k], y[g + k], z[g + k], c[g + k], in);
-            all = all & (in | !vis[k]);
-            if (in & vis[k] & (key < cur[k]))
-                __hip_atomic_fetch_min(gfb + pix[k], key, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+            for (int k = 0; k < G; ++k) {
+                live[k] = true;
+                key[k] = key_of(x[g + k], y[g + k], z[g + k], c[g + k], live[k]);
+                all = all & (live[k] | !vis[k]);
+                live[k] = live[k] & vis[k];
+            }
+            general = wave_any(!all);
         }
+        if (general) {
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                live[k] = vis[k];
+                key[k] = key_any<PW, ZK>(P, T, x[g + k], y[g + k], z[g + k], c[g + k], live[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (live[k] & (key[k] < cur[k]))
+                __hip_atomic_fetch_min(gfb + pix[k], key[k], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_sched_barrier(0);
     }
-    return !wave_any(!all);
-}
-
-template <int PPT, bool PW, int ZK = 0, typename Again>
-__device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
-                                                  uint64_t *__restrict__ fb,
-                                                  const float (&x)[PPT], const float (&y)[PPT],
-                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                  uint64_t *w_tile, uint32_t words,
-                                                  MinFlush &flush, const Again &again,
-                                                  bool l2 = false, bool early = true)
-{
-    if (raster_wave_fast<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, flush, l2, early))
-        return;
-    again();
-    raster_wave_any<PPT, PW, ZK>(P, T, fb, x, y, z, c, w_tile, words, early);
 }
 
 // Accumulation pass of high-quality splatting over one chunk (section 2.2).
@@ -1352,8 +1420,9 @@ __device__ __forceinline__ void accum_chunk(const Proj &P, uint32_t eps_num, uin
     }
 }
 
-// accum_chunk_wave for any wave: each point with its own flags, as
-// raster_wave_any.  A wave of at most 512 points (PPT <= 8) adds one packed word
+// accum_chunk_wave for any wave: each point with its own flags.  The points are
+// projected once for the rectangle and again for their depths, so that no array of
+// them is held.  A wave of at most 512 points (PPT <= 8) adds one packed word
 // per fragment, R | G << 17 | B << 34 | count << 51: no field of a sum over the
 // wave can carry into the next (512 * 255 < 2^17, 512 < 2^13); larger waves keep
 // the accumulator's own two words.

@@ -35,15 +35,14 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
     bool in[PPT];
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
     // no per-point bounds flags: points past the end load as NaN and are culled
-    auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
-    load();
+    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
     if (BIN == kBinWave) {
         MinFlush flush;
-        raster_chunk_wave<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load,
-                                   false, EARLY);
+        raster_chunk_wave<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, false,
+                                   EARLY);
         raster_wave_flush(fb, w_tile, flush);
     } else {
         raster_chunk<PPT, EARLY, BIN == kBinBlock, PW>(P, fb, x, y, z, c, in, s_tile, s_box);
@@ -63,11 +62,10 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
     float x[PPT], y[PPT], z[PPT];
     uint32_t c[PPT];
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
-    auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
-    load();
+    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
     MinFlush flush;
-    raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, load,
-                                      false, EARLY);
+    raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, false,
+                                      EARLY);
     raster_wave_flush(fb, w_tile, flush);
 }
 

@@ -64,3 +64,10 @@ def test_clouds_behind_the_camera(rz, terrain, hq):
                          0.5, 4000.0)
     r = ratio(f"behind hq={hq}", frame(rz, terrain, away, hq), frame(rz, terrain, HD, hq))
     assert r < 1.15   # 0.8; 1.55 with waves rasterized twice
+
+
+def test_clouds_mostly_beyond_the_depth_range(rz, terrain):
+    """Most waves on screen with no point in [near, far)."""
+    cut = gen.terrain_view(1920, 1080, near=900.0, far=1100.0)
+    r = ratio("depth cut", frame(rz, terrain, cut), frame(rz, terrain, HD))
+    assert r < 1.2   # 0.95; 1.5 with waves rasterized twice

@@ -136,3 +136,50 @@ def test_waves_behind_the_camera(rz, oracle, what, shape):
     if what == "a few at zero":
         c.z[part[::57]] = 0.0
     render_all(rz, oracle, c, v, shape=shape)
+
+
+PIECES = [(0, 0.0), (2, ((0.0, 1e9), (2.015, 1e6), (10.0, 1e3))), (3, 0.0), (4, 0.0)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("depth", PIECES)
+@pytest.mark.parametrize("wh", [(9, 7), (41, 25), (300, 200)])
+def test_waves_across_depth_ranges(rz, oracle, wh, depth, shape):
+    """Waves of which some points lie before near, beyond far or in another range of the
+    depth map, over rectangles inside the tile (four copies and one) and beside it,
+    partly off screen too."""
+    for i, (ox, oy) in enumerate([(37, 21), (-3, -2)]):
+        c, v = rectangle_scene(*wh, n=3001, seed=20 + i, ox=ox, oy=oy, outside=300)
+        v.near, v.far = 2.005, 2.05   # z is 2 to 2.03 or about 2.5
+        args = (c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width, v.height, *depth)
+        pts = rz.Points.from_cloud(c)
+        keys, img = oracle.render_atomicmin(*args)
+        rz.reset_launch() if shape is None else rz.set_launch(*shape)
+        try:
+            fb, _ = rz.rasterize_atomicmin(pts, v, depth, keep_keys=True)
+        finally:
+            rz.reset_launch()
+        assert np.array_equal(rz.to_u64(fb), keys), (ox, oy)
+        if depth[0] < 3:
+            b = rz.Batch(pts, [v, v], [0, 0], depth=depth, launch=shape)
+            b.run()
+            assert all(np.array_equal(g, img) for g in b.images())
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_waves_of_extreme_w(rz, oracle, shape):
+    """Points whose w is denormal or at least 2^126, where the reciprocal takes the IEEE
+    quotient, among ordinary ones and alone."""
+    n = 4000
+    c, v = rectangle_scene(30, 20, n, 12)
+    v.near, v.far = 1e-41, 1e39
+    scale = np.ones(n)
+    scale[100:1100:7] = 1e38 / 2
+    scale[1500:2200] = 1e38 / 2
+    scale[2300:3000:5] = 3e-39
+    scale[3200:3900] = 3e-39
+    for a in (c.x, c.y, c.z):
+        a[:] = (a.astype(np.float64) * scale).astype(np.float32)
+    pix, _ = oracle.fragments(c.x, c.y, c.z, v.vp, v.near, v.far, v.width, v.height)
+    assert (pix[1500:2200] >= 0).any() and (pix[3200:3900] >= 0).any()
+    render_all(rz, oracle, c, v, shape=shape)
