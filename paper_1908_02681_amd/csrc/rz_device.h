@@ -883,48 +883,42 @@ __device__ __forceinline__ float clip_w(const Proj &P, const Trans &T, float x, 
     return __builtin_fmaf(P.m[10], z, cw);
 }
 
-// Whether point j of a wave is on screen, from its window position: in a wave with
-// points of w <= 0 or NaN (mixed, wave-uniform) by the sign of w too.
+// After kMixed: bit j of `behind` set where the lane's point j has w <= 0 or NaN, so
+// that its window position means nothing.  True when some point of the wave has a
+// positive w outside [2^-126, 2^126): its position is not the one by the IEEE quotient.
 template <int PPT>
-__device__ __forceinline__ bool point_visible(const Proj &P, const Trans &T, bool mixed, int j,
-                                              const float (&x)[PPT], const float (&y)[PPT],
-                                              const float (&z)[PPT], float wx, float wy)
-{
-    bool vis = on_screen(P, wx, wy);
-    if (mixed)
-        vis = vis & (clip_w(P, T, x[j], y[j], z[j]) > 0.0f);
-    return vis;
-}
-
-// Some point of a wave has a positive w outside [2^-126, 2^126), so that its window
-// position is not the one by the IEEE quotient.
-template <int PPT>
-__device__ __forceinline__ bool any_slow_w(const Proj &P, const Trans &T, const float (&x)[PPT],
-                                           const float (&y)[PPT], const float (&z)[PPT])
+__device__ __forceinline__ bool sort_w(const Proj &P, const Trans &T, const float (&x)[PPT],
+                                       const float (&y)[PPT], const float (&z)[PPT],
+                                       uint32_t &behind)
 {
     bool slow = false;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const float cw = clip_w(P, T, x[j], y[j], z[j]);
         slow = slow | ((cw > 0.0f) & ((cw < 0x1p-126f) | (cw >= 0x1p126f)));
+        behind |= cw > 0.0f ? 0u : 1u << j;
         __builtin_amdgcn_sched_barrier(0);
     }
     return wave_any(slow);
 }
 
+// Whether a lane's point j is on screen, by its window position and `behind`.
+__device__ __forceinline__ bool visible(const Proj &P, float fx, float fy, uint32_t behind, int j)
+{
+    return on_screen(P, fx, fy) & ((behind & (1u << j)) == 0u);
+}
+
 // Box of the on-screen points of a wave; without one, x1 lies beyond kMaxPixel.
 template <int PPT>
-__device__ __forceinline__ Box window_box(const Proj &P, const Trans &T, bool mixed,
-                                          const float (&x)[PPT], const float (&y)[PPT],
-                                          const float (&z)[PPT], const float (&fx)[PPT],
-                                          const float (&fy)[PPT])
+__device__ __forceinline__ Box window_box(const Proj &P, const float (&fx)[PPT],
+                                          const float (&fy)[PPT], uint32_t behind)
 {
     int32_t xlo = 0x7FFFFFFF, ylo = 0x7FFFFFFF, xhi = -1, yhi = -1;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         float wx = fx[j], wy = fy[j];
         own(wx), own(wy);
-        const bool vis = point_visible<PPT>(P, T, mixed, j, x, y, z, wx, wy);
+        const bool vis = visible(P, wx, wy, behind, j);
         const int32_t px = (int32_t)(vis ? wx : 0.0f), py = (int32_t)(vis ? wy : 0.0f);
         xlo = min(xlo, vis ? px : 0x7FFFFFFF);
         ylo = min(ylo, vis ? py : 0x7FFFFFFF);
@@ -1186,8 +1180,8 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
     if (where == kOffScreen)
         return;
     gu64 *gfb = global_ptr(fb);
-    const bool mixed = where == kMixed;
-    if (mixed && any_slow_w<PPT>(P, T, x, y, z)) {   // no wave in practice
+    uint32_t behind = 0u;
+    if (where == kMixed && sort_w<PPT>(P, T, x, y, z, behind)) {   // no wave in practice
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             float xx = x[j], yy = y[j], zz = z[j];
@@ -1203,7 +1197,7 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
         return;
     }
     if (where != kOnScreen) {
-        box = window_box<PPT>(P, T, mixed, x, y, z, fx, fy);
+        box = window_box<PPT>(P, fx, fy, behind);
         if (box.x1 > kMaxPixel)   // no point on screen
             return;
     }
@@ -1248,7 +1242,7 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
             for (int j = 0; j < PPT; ++j) {
                 float px = fx[j], py = fy[j];
                 own(px), own(py);
-                bool live = point_visible<PPT>(P, T, mixed, j, x, y, z, px, py);
+                bool live = visible(P, px, py, behind, j);
                 const uint64_t key = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live);
                 if (live)
                     __hip_atomic_fetch_min(lds_ptr(tile_entry(t, px, py, sh, first)), key,
@@ -1260,47 +1254,75 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
         flush = MinFlush{t, p0, cur, four};
         return;
     }
-    // spread too far for the tile: groups of four points, their early-out reads
-    // in flight while their keys are computed.  A point out of range takes the
-    // general key, and from then on all do.
-    constexpr int G = 4;
-    bool general = false;
-#pragma unroll
-    for (int g = 0; g < PPT; g += G) {
-        uint32_t pix[G];
-        uint64_t key[G], cur[G];
-        bool vis[G], live[G];
+    // spread too far for the tile: groups of four points.  Consecutive points of a
+    // thread in one pixel send one atomic, and a group's early-out reads are sent before
+    // the atomics of the group before it, which they would have to wait for otherwise
+    // (one counter covers all memory operations of a wave, in order).
+    constexpr int G = 4, N = PPT / G;
+    uint32_t pix[2][G];
+    uint64_t key[2][G], cur[2][G];
+    bool live[2][G];
+    bool general = !PW;   // keys of points in any range
+    auto read = [&](int g) {
+        const int b = g & 1;
+        bool vis[G], run = false;
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            float wx = fx[g + k], wy = fy[g + k];
+            const int j = G * g + k;
+            float wx = fx[j], wy = fy[j];
             own(wx), own(wy);
-            vis[k] = point_visible<PPT>(P, T, mixed, g + k, x, y, z, wx, wy);
-            pix[k] = __umul24((uint32_t)(int32_t)(vis[k] ? wy : 0.0f), t.width) +
-                     (uint32_t)(int32_t)(vis[k] ? wx : 0.0f);
-            cur[k] = early ? read_nearest(gfb + pix[k], false) : ~0ull;
+            vis[k] = visible(P, wx, wy, behind, j);
+            pix[b][k] = __umul24((uint32_t)(int32_t)(vis[k] ? wy : 0.0f), t.width) +
+                        (uint32_t)(int32_t)(vis[k] ? wx : 0.0f);
         }
         if (!general) {
             bool all = true;
 #pragma unroll
             for (int k = 0; k < G; ++k) {
-                live[k] = true;
-                key[k] = key_of(x[g + k], y[g + k], z[g + k], c[g + k], live[k]);
-                all = all & (live[k] | !vis[k]);
-                live[k] = live[k] & vis[k];
+                const int j = G * g + k;
+                live[b][k] = true;
+                key[b][k] = key_of(x[j], y[j], z[j], c[j], live[b][k]);
+                all = all & (live[b][k] | !vis[k]);
+                live[b][k] = live[b][k] & vis[k];
             }
-            general = wave_any(!all);
+            general = wave_any(!all);   // and so for the groups after it
         }
         if (general) {
 #pragma unroll
             for (int k = 0; k < G; ++k) {
-                live[k] = vis[k];
-                key[k] = key_any<PW, ZK>(P, T, x[g + k], y[g + k], z[g + k], c[g + k], live[k]);
+                const int j = G * g + k;
+                live[b][k] = vis[k];
+                key[b][k] = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live[b][k]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
 #pragma unroll
+        for (int k = 1; k < G; ++k)
+            run = run | (live[b][k] & live[b][k - 1] & (pix[b][k] == pix[b][k - 1]));
+        if (wave_any(run)) {
+#pragma unroll
+            for (int k = 1; k < G; ++k) {
+                const bool same = live[b][k] & live[b][k - 1] & (pix[b][k] == pix[b][k - 1]);
+                const uint64_t lo = key[b][k] < key[b][k - 1] ? key[b][k] : key[b][k - 1];
+                key[b][k] = same ? lo : key[b][k];
+                live[b][k - 1] = live[b][k - 1] & !same;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k)   // a point that takes no part reads pixel 0
+            cur[b][k] = early ? read_nearest(gfb + (live[b][k] ? pix[b][k] : 0u), false) : ~0ull;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    read(0);
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+        const int b = g & 1;
+        if (g + 1 < N)
+            read(g + 1);
+#pragma unroll
         for (int k = 0; k < G; ++k)
-            if (live[k] & (key[k] < cur[k]))
-                __hip_atomic_fetch_min(gfb + pix[k], key[k], __ATOMIC_RELAXED,
+            if (live[b][k] & (key[b][k] < cur[b][k]))
+                __hip_atomic_fetch_min(gfb + pix[b][k], key[b][k], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_sched_barrier(0);
     }

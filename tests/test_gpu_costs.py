@@ -71,3 +71,22 @@ def test_clouds_mostly_beyond_the_depth_range(rz, terrain):
     cut = gen.terrain_view(1920, 1080, near=900.0, far=1100.0)
     r = ratio("depth cut", frame(rz, terrain, cut), frame(rz, terrain, HD))
     assert r < 1.2   # 0.95; 1.5 with waves rasterized twice
+
+
+@pytest.fixture(scope="module")
+def noisy(rz, terrain):
+    """The terrain with a stray point in every 256: no wave's rectangle is small."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    at = torch.arange(100, terrain.n, 256, device="cuda")
+    src = torch.randint(0, terrain.n, (at.numel(),), generator=g, device="cuda")
+    planes = [a.clone() for a in (terrain.x, terrain.y, terrain.z, terrain.rgb)]
+    for a in planes:
+        a[at] = a[src]
+    return rz.Points(*planes)
+
+
+def test_runs_beside_the_tile(rz, terrain, noisy):
+    """Consecutive points of a thread in one pixel send one atomic."""
+    r = ratio("noise", frame(rz, noisy, HD), frame(rz, terrain, HD))
+    assert r < 5.0   # 3.5; 7.9 with an atomic per point

@@ -183,3 +183,19 @@ def test_waves_of_extreme_w(rz, oracle, shape):
     pix, _ = oracle.fragments(c.x, c.y, c.z, v.vp, v.near, v.far, v.width, v.height)
     assert (pix[1500:2200] >= 0).any() and (pix[3200:3900] >= 0).any()
     render_all(rz, oracle, c, v, shape=shape)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("depth", PIECES[:2])
+def test_runs_of_one_pixel_beside_the_tile(rz, oracle, depth, shape):
+    """Runs of 1 to 6 consecutive points in one pixel, some of them out of range, in waves
+    spread too far for any tile."""
+    n = 5003
+    c, v = rectangle_scene(350, 250, n, 33)
+    v.far = 2.4
+    rng = np.random.default_rng(34)
+    src = np.repeat(np.arange(n), rng.integers(1, 7, n))[:n]
+    deeper = rng.choice([1.0, 1.001, 1.003, 1.3], n, p=[0.3, 0.3, 0.3, 0.1]).astype(np.float32)
+    for a in (c.x, c.y, c.z):
+        a[:] = a[src] * deeper   # along the ray: the same pixel, or beyond far
+    render_all(rz, oracle, c, v, depth=depth, shape=shape, sizes=(1, 2))
