@@ -48,7 +48,9 @@ constexpr uint32_t kWaveTileSmallWords = 256;
 // Tiling modes of the point kernels.  kBinWaveSmall is kBinWave with the
 // small tile: the kernels take the tile size as an argument, so both modes
 // share the kBinWave code.
-enum : int { kBinNone = 0, kBinBlock = 1, kBinWave = 2, kBinWaveSmall = 3 };
+// kBinGroup (not a launch option) is kBinWaveSmall in a workgroup whose waves share
+// their tiles where they cover the same pixels.
+enum : int { kBinNone = 0, kBinBlock = 1, kBinWave = 2, kBinWaveSmall = 3, kBinGroup = 4 };
 
 // Words of one wave's tile in a per-wave tiling mode.  The accumulate pass's
 // small tile has 6 KiB: three words a pixel (two copies of the sums and the
@@ -1091,6 +1093,16 @@ struct MinFlush {
     bool four;
 };
 
+// Nearest key of entry i of a tile at LDS address base, kept once or four times.
+__device__ __forceinline__ uint64_t tile_nearest(uint32_t base, uint32_t i, bool four)
+{
+    if (!four)
+        return *lds_ptr(base + 8 * i);
+    const u64x2 a = *lds_ptr2(base + 32 * i), b = *lds_ptr2(base + 32 * i + 16);
+    const uint64_t m = a.x < a.y ? a.x : a.y, n = b.x < b.y ? b.x : b.y;
+    return m < n ? m : n;
+}
+
 // The flush: one coalesced global atomic per touched pixel whose nearest key
 // it lowers.
 __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, const uint64_t *w_tile,
@@ -1102,20 +1114,13 @@ __device__ __forceinline__ void raster_wave_flush(uint64_t *__restrict__ fb, con
     arrive(f.cur);
     if (f.t.area == 0)
         return;
-    auto nearest = [&](uint32_t i) -> uint64_t {   // of entry i of the tile
-        if (!f.four)
-            return *lds_ptr(base + 8 * i);
-        const u64x2 a = *lds_ptr2(base + 32 * i), b = *lds_ptr2(base + 32 * i + 16);
-        const uint64_t m = a.x < a.y ? a.x : a.y, n = b.x < b.y ? b.x : b.y;
-        return m < n ? m : n;
-    };
     if (lane < f.t.area) {
-        const uint64_t v = nearest(lane);
+        const uint64_t v = tile_nearest(base, lane, f.four);
         if (v < f.cur)
             __hip_atomic_fetch_min(gfb + f.p0, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     for (uint32_t i = lane + 64; i < f.t.area; i += 64) {
-        const uint64_t v = nearest(i);
+        const uint64_t v = tile_nearest(base, i, f.four);
         if (v != ~0ull) {
             gu64 *dst = gfb + tile_pixel(f.t, i);
             const uint64_t was = read_nearest(dst, l2);
@@ -1142,46 +1147,29 @@ __device__ __forceinline__ uint64_t key_any(const Proj &P, const Trans &T, float
     return (q << 24) | ((uint64_t)c & kRgbMask);
 }
 
-// Depth pass over one chunk with a private LDS tile per wave: like
-// raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
-// in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
-// Same result bits as raster_chunk, for any tile size.
-// raster_wave_flush must follow with the same `flush`.  Without `early`, fragments
-// of a wave that does not fit its tile go to the framebuffer unread.
-//
-// A wave whose points are all on screen and, as it turns out, in one range of
-// the depth map and in [near, far) needs no flag per point, and neither the
-// clamp nor the test for a slow reciprocal.  Every other wave goes on from the same
-// window positions with flags per point (key_any), so that no point is loaded or
-// projected again.
-//
-// The nearest keys that the flush compares with are read before the depths are
-// computed, so that their latency passes meanwhile (a key read early is an upper
-// bound of the later one).
-//
-// A tile that fits four times is kept four times, lane i taking copy i & 3:
-// neighbouring lanes hold neighbouring points, and LDS atomics of one address
-// follow each other one per cycle (a depth pass of 100M points over 8 views:
-// 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
-template <int PPT, bool PW, int ZK = 0>
-__device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
-                                                  uint64_t *__restrict__ fb,
-                                                  const float (&x)[PPT], const float (&y)[PPT],
-                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                  uint64_t *w_tile, uint32_t words,
-                                                  MinFlush &flush, bool l2 = false,
-                                                  bool early = true)
+// A wave's points on screen: the first half of its depth pass.
+template <int PPT>
+struct WaveView {
+    float fx[PPT], fy[PPT];   // window positions
+    Box box;                  // of the on-screen points
+    Where where;
+    uint32_t behind;          // as sort_w leaves it
+};
+
+// False when the wave has nothing left to do: no point on screen, or points whose w
+// needs the IEEE quotient, which go to the framebuffer one by one here.
+template <int PPT, bool PW, int ZK>
+__device__ __forceinline__ bool wave_view(const Proj &P, const Trans &T, uint64_t *__restrict__ fb,
+                                          const float (&x)[PPT], const float (&y)[PPT],
+                                          const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                          WaveView<PPT> &v)
 {
-    float fx[PPT], fy[PPT];
-    Box box;
-    flush.t.area = 0;
-    flush.cur = 0;
-    const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
-    if (where == kOffScreen)
-        return;
-    gu64 *gfb = global_ptr(fb);
-    uint32_t behind = 0u;
-    if (where == kMixed && sort_w<PPT>(P, T, x, y, z, behind)) {   // no wave in practice
+    v.behind = 0u;
+    v.where = window_all<PPT>(P, T, x, y, z, v.fx, v.fy, v.box);
+    if (v.where == kOffScreen)
+        return false;
+    if (v.where == kMixed && sort_w<PPT>(P, T, x, y, z, v.behind)) {   // no wave in practice
+        gu64 *gfb = global_ptr(fb);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             float xx = x[j], yy = y[j], zz = z[j];
@@ -1194,15 +1182,26 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                        __HIP_MEMORY_SCOPE_AGENT);
             __builtin_amdgcn_sched_barrier(0);
         }
-        return;
+        return false;
     }
-    if (where != kOnScreen) {
-        box = window_box<PPT>(P, fx, fy, behind);
-        if (box.x1 > kMaxPixel)   // no point on screen
-            return;
+    if (v.where != kOnScreen) {
+        v.box = window_box<PPT>(P, v.fx, v.fy, v.behind);
+        return v.box.x1 <= kMaxPixel;   // some point on screen
     }
+    return true;
+}
+
+// The second half, with the wave's own tile (raster_chunk_wave).
+template <int PPT, bool PW, int ZK>
+__device__ __forceinline__ void raster_view(const Proj &P, const Trans &T, uint64_t *__restrict__ fb,
+                                            const float (&x)[PPT], const float (&y)[PPT],
+                                            const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                            const WaveView<PPT> &v, uint64_t *w_tile,
+                                            uint32_t words, MinFlush &flush, bool l2, bool early)
+{
+    gu64 *gfb = global_ptr(fb);
     const uint32_t lane = threadIdx.x & 63u;
-    const WaveTile t = wave_tile(P, box);
+    const WaveTile t = wave_tile(P, v.box);
     const ChunkKey<PW, ZK> key_of(P, T, x[0], y[0], z[0]);
     if (t.area <= words) {
         const uint32_t base = lds_addr(w_tile);
@@ -1224,11 +1223,11 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
             wave_sync();
         };
         clear();
-        bool in = where == kOnScreen;
-        if (where == kOnScreen) {
+        bool in = v.where == kOnScreen;
+        if (v.where == kOnScreen) {
 #pragma unroll
             for (int j = 0; j < PPT; ++j) {
-                __hip_atomic_fetch_min(lds_ptr(tile_entry(t, fx[j], fy[j], sh, first)),
+                __hip_atomic_fetch_min(lds_ptr(tile_entry(t, v.fx[j], v.fy[j], sh, first)),
                                        key_of(x[j], y[j], z[j], c[j], in), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (j % 2)
@@ -1240,9 +1239,9 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
             clear();
 #pragma unroll
             for (int j = 0; j < PPT; ++j) {
-                float px = fx[j], py = fy[j];
+                float px = v.fx[j], py = v.fy[j];
                 own(px), own(py);
-                bool live = visible(P, px, py, behind, j);
+                bool live = visible(P, px, py, v.behind, j);
                 const uint64_t key = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live);
                 if (live)
                     __hip_atomic_fetch_min(lds_ptr(tile_entry(t, px, py, sh, first)), key,
@@ -1269,9 +1268,9 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
 #pragma unroll
         for (int k = 0; k < G; ++k) {
             const int j = G * g + k;
-            float wx = fx[j], wy = fy[j];
+            float wx = v.fx[j], wy = v.fy[j];
             own(wx), own(wy);
-            vis[k] = visible(P, wx, wy, behind, j);
+            vis[k] = visible(P, wx, wy, v.behind, j);
             pix[b][k] = __umul24((uint32_t)(int32_t)(vis[k] ? wy : 0.0f), t.width) +
                         (uint32_t)(int32_t)(vis[k] ? wx : 0.0f);
         }
@@ -1325,6 +1324,127 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                 __hip_atomic_fetch_min(gfb + pix[b][k], key[b][k], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Depth pass over one chunk with a private LDS tile per wave: like
+// raster_chunk with BIN, but every wave gathers its own 64 * PPT fragments
+// in its own slice of `words` keys (w_tile), so no workgroup barrier is needed.
+// Same result bits as raster_chunk, for any tile size.
+// raster_wave_flush must follow with the same `flush`.  Without `early`, fragments
+// of a wave that does not fit its tile go to the framebuffer unread.
+//
+// A wave whose points are all on screen and, as it turns out, in one range of
+// the depth map and in [near, far) needs no flag per point, and neither the
+// clamp nor the test for a slow reciprocal.  Every other wave goes on from the same
+// window positions with flags per point (key_any), so that no point is loaded or
+// projected again.
+//
+// The nearest keys that the flush compares with are read before the depths are
+// computed, so that their latency passes meanwhile (a key read early is an upper
+// bound of the later one).
+//
+// A tile that fits four times is kept four times, lane i taking copy i & 3:
+// neighbouring lanes hold neighbouring points, and LDS atomics of one address
+// follow each other one per cycle (a depth pass of 100M points over 8 views:
+// 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
+template <int PPT, bool PW, int ZK = 0>
+__device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
+                                                  uint64_t *__restrict__ fb,
+                                                  const float (&x)[PPT], const float (&y)[PPT],
+                                                  const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                  uint64_t *w_tile, uint32_t words,
+                                                  MinFlush &flush, bool l2 = false,
+                                                  bool early = true)
+{
+    WaveView<PPT> v;
+    flush.t.area = 0;
+    flush.cur = 0;
+    if (wave_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v))
+        raster_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, w_tile, words, flush, l2, early);
+}
+
+// raster_chunk_wave for the waves of one workgroup (at most kMaxWaves of them), with
+// one tile in place of theirs where they cover the same pixels: the rectangle of all
+// takes at most half of theirs together and fits their tiles' words.  That is an
+// unordered cloud on few pixels, where every wave has an atomic for every pixel, and
+// atomics of one pixel follow each other (about 27 ns each): the smaller the waves,
+// the more of them.  Frames of 700k points on spheres in random order, waves of 256
+// points alone / with this / waves of 1024 points: on 24 x 24 pixels 80.9 / 24.8 / 32.3
+// us, on 32 x 32 204 / 29.8 / 30.1, at 1280x720 from so far away that they cover about
+// 27 x 27 pixels 151 / 36.6 / 39.4; 2M points there 408 / 60.0 / 60.8.  The barrier costs
+// an ordered cloud nothing that shows (the terrain at 1920x1080: 1M points 23.7 / 24.0,
+// 4M 27.4 / 27.7, 7M 35.8 / 35.4).  s_tiles: `words` keys of each wave, one wave after
+// the other.
+template <int PPT, bool PW, int ZK = 0>
+__device__ __forceinline__ void raster_chunk_group(const Proj &P, const Trans &T,
+                                                   uint64_t *__restrict__ fb,
+                                                   const float (&x)[PPT], const float (&y)[PPT],
+                                                   const float (&z)[PPT], const uint32_t (&c)[PPT],
+                                                   uint64_t *s_tiles, uint32_t words,
+                                                   uint32_t (*s_box)[4], MinFlush &flush,
+                                                   bool early)
+{
+    WaveView<PPT> v;
+    flush.t.area = 0;
+    flush.cur = 0;
+    const bool some = wave_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v);
+    const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    if ((threadIdx.x & 63u) == 0) {
+        s_box[wave][0] = some ? v.box.x0 : ~0u;
+        s_box[wave][1] = some ? v.box.y0 : ~0u;
+        s_box[wave][2] = some ? v.box.x1 : 0u;
+        s_box[wave][3] = some ? v.box.y1 : 0u;
+    }
+    __syncthreads();
+    Box all{~0u, ~0u, 0u, 0u};
+    uint32_t sum = 0;   // of the waves' areas, those beyond 2^16 pixels counted as that
+    for (uint32_t w = 0; w < waves; ++w) {
+        const Box b{s_box[w][0], s_box[w][1], s_box[w][2], s_box[w][3]};
+        all = Box{min(all.x0, b.x0), min(all.y0, b.y0), max(all.x1, b.x1), max(all.y1, b.y1)};
+        const uint32_t area = (b.x1 - b.x0 + 1) * (b.y1 - b.y0 + 1);
+        sum += b.x0 > b.x1 ? 0u : min(area, 1u << 16);
+    }
+    all = Box{(uint32_t)__builtin_amdgcn_readfirstlane((int)all.x0),
+              (uint32_t)__builtin_amdgcn_readfirstlane((int)all.y0),
+              (uint32_t)__builtin_amdgcn_readfirstlane((int)all.x1),
+              (uint32_t)__builtin_amdgcn_readfirstlane((int)all.y1)};
+    sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)sum);
+    if (sum == 0u)
+        return;
+    const WaveTile t = wave_tile(P, all);
+    if (t.area > words * waves || 2 * t.area > sum) {
+        if (some)
+            raster_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, s_tiles + wave * words, words, flush,
+                                     false, early);
+        return;
+    }
+    const uint32_t base = lds_addr(s_tiles);
+    const bool four = 4 * t.area <= words * waves;
+    const uint32_t sh = four ? 5u : 3u;
+    const uint32_t first = tile_first(t, base + (four ? 8 * (threadIdx.x & 3u) : 0u), sh);
+    for (uint32_t i = threadIdx.x; i < t.area << (sh - 3); i += blockDim.x)
+        *lds_ptr(base + 8 * i) = ~0ull;
+    __syncthreads();
+    if (some) {
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            bool live = visible(P, v.fx[j], v.fy[j], v.behind, j);
+            const uint64_t key = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live);
+            if (live)
+                __hip_atomic_fetch_min(lds_ptr(tile_entry(t, v.fx[j], v.fy[j], sh, first)), key,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    __syncthreads();
+    gu64 *gfb = global_ptr(fb);
+    for (uint32_t i = threadIdx.x; i < t.area; i += blockDim.x) {
+        const uint64_t m = tile_nearest(base, i, four);
+        if (m != ~0ull) {
+            gu64 *dst = gfb + tile_pixel(t, i);
+            if (m < read_nearest(dst, false))
+                __hip_atomic_fetch_min(dst, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 

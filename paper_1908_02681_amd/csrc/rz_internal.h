@@ -58,16 +58,20 @@ constexpr Tune kHqTune = {64, 8, 1, 0, 3, 1};
 // of 512 in the splat pass), so that a pass lasts as long as its slowest waves.
 // Frames of the terrain at 1920x1080, default shape / this one: 0.5M points 25.1 /
 // 21.5 us (splat 64.9 / 56.3), 2M 29.7 / 27.1 (73.3 / 66.4), 5M 36.1 / 31.5 (81.9 /
-// 77.3), 10M 47.4 / 44.6 (101.7 / 100.6), 20M 71.9 / 72.4 (149.0 / 152.9).
+// 77.3), 10M 47.4 / 44.6 (101.7 / 100.6), 20M 71.9 / 72.4 (149.0 / 152.9).  In the
+// depth pass the four waves of a workgroup share a tile where they cover the same
+// pixels (raster_chunk_group).
 constexpr int64_t kSmallCloud = 8 << 20;
 constexpr Tune kSmallTune = {256, 4, 1, 0, 3, 1};
 // Clouds of fewer points than this do not fill the device, and a fragment beside
 // a tile (a cloud in no spatial order) costs the latencies of its early-out read and
-// of its atomic in turn, whatever the screen: they go without the read.  Frames,
-// with the read / without: spheres at 1024x768 0.2M points 19.3 / 17.0 us, 0.4M 29.5 /
-// 26.6, 0.8M 50.9 / 42.0, 1M 59.5 / 56.9, 1.3M 69.7 / 72.4, 2M 87.7 / 108.7; shuffled
-// terrain at 2560x1440 0.4M 37.0 / 31.7, 1M 62.8 / 56.7, 2M 98.1 / 95.5, at 320x200
-// 0.4M 48.0 / 34.3, 1M 106.5 / 78.1, 1.6M 123 / 123, 2M 131 / 151.
+// of its atomic in turn: they go without the read, which would seldom save the atomic,
+// since all waves start at once.  Frames, with the read / without: spheres at 1024x768
+// 0.2M points 19.3 / 17.0 us, 0.4M 29.5 / 26.6, 0.8M 50.9 / 42.0, 1M 59.5 / 56.9, 1.3M
+// 69.7 / 72.4, 2M 87.7 / 108.7; shuffled terrain at 2560x1440 0.4M 37.0 / 31.7, 1M 62.8 /
+// 56.7, 2M 98.1 / 95.5, at 320x200 0.4M 48.0 / 34.3, 1M 106.5 / 78.1, 1.6M 123 / 123, 2M
+// 131 / 151; spheres of 0.7M on 256 x 256 pixels 90.5 / 40.7, 160 x 160 140 / 61, 96 x 96
+// 219 / 75, 64 x 64 255 / 98 (on fewer pixels the waves share a tile).
 constexpr int64_t kUnreadCloud = 1 << 20;
 constexpr Tune kUnreadTune = {256, 4, 1, 0, 3, 1, 0};
 

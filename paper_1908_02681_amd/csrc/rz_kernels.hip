@@ -44,6 +44,11 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
         raster_chunk_wave<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, false,
                                    EARLY);
         raster_wave_flush(fb, w_tile, flush);
+    } else if (BIN == kBinGroup) {
+        MinFlush flush;
+        raster_chunk_group<PPT, PW>(P, lane_trans(P), fb, x, y, z, c, s_waves, words, s_box, flush,
+                                    EARLY);
+        raster_wave_flush(fb, w_tile, flush);
     } else {
         raster_chunk<PPT, EARLY, BIN == kBinBlock, PW>(P, fb, x, y, z, c, in, s_tile, s_box);
     }
@@ -51,10 +56,11 @@ __global__ void __launch_bounds__(512) k_raster_min(Pts p, Proj P, uint64_t *__r
 
 // Depth pass for the float depth encodings (RZ_DEPTH_GL24, RZ_DEPTH_F32REV)
 // at one pixel per point: the per-wave tile kernel with the encoding's key.
-template <int PPT, int ZK, bool EARLY>
+template <int PPT, int ZK, bool EARLY, bool GROUP>
 __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *__restrict__ fb,
                                                        int64_t nchunks, uint32_t words)
 {
+    __shared__ uint32_t s_box[kMaxWaves][4];
     extern __shared__ uint64_t s_waves[];
     const int64_t chunk = blockIdx.x;
     if (chunk >= nchunks)
@@ -64,8 +70,12 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
     load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
     MinFlush flush;
-    raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush, false,
-                                      EARLY);
+    if (GROUP)
+        raster_chunk_group<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, s_waves, words, s_box,
+                                           flush, EARLY);
+    else
+        raster_chunk_wave<PPT, false, ZK>(P, lane_trans(P), fb, x, y, z, c, w_tile, words, flush,
+                                          false, EARLY);
     raster_wave_flush(fb, w_tile, flush);
 }
 
@@ -227,8 +237,9 @@ hipError_t raster_min_bin(const Pts &p, const Proj &P, uint64_t *fb, const Tune 
     case kBinBlock: return raster_min_ppt<PPT, true, kBinBlock, PW>(p, P, fb, t, s);
     case kBinWave:
     case kBinWaveSmall:
-        if (PPT == 4 && !t.read_first)   // kUnreadTune
-            return raster_min_ppt<4, false, kBinWave, PW>(p, P, fb, t, s);
+        if (PPT == 4 && t.by_size)   // kSmallTune, kUnreadTune
+            return t.read_first ? raster_min_ppt<4, true, kBinGroup, PW>(p, P, fb, t, s)
+                                : raster_min_ppt<4, false, kBinGroup, PW>(p, P, fb, t, s);
         return raster_min_ppt<PPT, true, kBinWave, PW>(p, P, fb, t, s);
     default:
         return t.early_out ? raster_min_ppt<PPT, true, kBinNone, PW>(p, P, fb, t, s)
@@ -265,14 +276,14 @@ hipError_t hq_accum_dispatch(const Pts &p, const Proj &P, const Eps &eps,
                 : hq_accum_bin<PPT, false>(p, P, eps, fb, acc, t, s);
 }
 
-template <int PPT, int ZK, bool EARLY = true>
+template <int PPT, int ZK, bool EARLY = true, bool GROUP = false>
 hipError_t raster_min_zk(const Pts &p, const Proj &P, uint64_t *fb, const Tune &t, hipStream_t s)
 {
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * PPT);
     const size_t lds = wave_lds(t.bin, t.block, false);
     const uint32_t words = wave_tile_words(t.bin, false);
-    hipLaunchKernelGGL((k_raster_min_zk<PPT, ZK, EARLY>), dim3((uint32_t)nchunks), dim3(t.block), lds, s, p, P,
-                       fb, nchunks, words);
+    hipLaunchKernelGGL((k_raster_min_zk<PPT, ZK, EARLY, GROUP>), dim3((uint32_t)nchunks),
+                       dim3(t.block), lds, s, p, P, fb, nchunks, words);
     return hipGetLastError();
 }
 
@@ -282,8 +293,10 @@ hipError_t raster_min_zk_dispatch(const Pts &p, const Proj &P, uint64_t *fb, con
 {
     switch (t.ppt) {
     case 4:
-        return t.read_first ? raster_min_zk<4, ZK>(p, P, fb, t, s)
-                            : raster_min_zk<4, ZK, false>(p, P, fb, t, s);
+        if (!t.by_size)
+            return raster_min_zk<4, ZK>(p, P, fb, t, s);
+        return t.read_first ? raster_min_zk<4, ZK, true, true>(p, P, fb, t, s)
+                            : raster_min_zk<4, ZK, false, true>(p, P, fb, t, s);
     case 8: return raster_min_zk<8, ZK>(p, P, fb, t, s);
     case 16: return raster_min_zk<16, ZK>(p, P, fb, t, s);
     default: return hipErrorInvalidValue;

@@ -90,3 +90,20 @@ def test_runs_beside_the_tile(rz, terrain, noisy):
     """Consecutive points of a thread in one pixel send one atomic."""
     r = ratio("noise", frame(rz, noisy, HD), frame(rz, terrain, HD))
     assert r < 5.0   # 3.5; 7.9 with an atomic per point
+
+
+@pytest.mark.parametrize("depth", [(0, 0.0), (4, 0.0)])
+@pytest.mark.parametrize("screen,eye", [((32, 32), 2.5), ((1280, 720), 40.5)])
+def test_small_unordered_clouds_on_few_pixels(rz, screen, eye, depth):
+    """Spheres in random order over fewer pixels than a tile: the default shape beside
+    waves of 1024 points."""
+    pts = rz.Points.from_cloud(gen.spheres(900_000, 3))
+    v = gen.make_view((0.5, 0.5, eye), (0.5, 0.5, 0.5), (0, 1, 0), 60.0, *screen, 0.01, 100.0)
+    f = frame(rz, pts, v, depth=depth)
+
+    def large():
+        rz.set_launch(64, 16, 1, 0, 2)
+        f()
+        rz.reset_launch()
+    r = ratio(f"few pixels {screen} depth {depth[0]}", f, large)
+    assert r < 2.0   # 1.0; 7.5 and 5.0 with each wave's atomics on their own

@@ -199,3 +199,48 @@ def test_runs_of_one_pixel_beside_the_tile(rz, oracle, depth, shape):
     for a in (c.x, c.y, c.z):
         a[:] = a[src] * deeper   # along the ray: the same pixel, or beyond far
     render_all(rz, oracle, c, v, depth=depth, shape=shape, sizes=(1, 2))
+
+
+@pytest.mark.parametrize("depth", PIECES)
+@pytest.mark.parametrize("wh", [(1, 1), (16, 16), (17, 16), (32, 32), (33, 32), (60, 40)])
+def test_waves_that_share_a_tile(rz, oracle, wh, depth):
+    """Small clouds whose workgroups have waves over the same pixels (one tile for all, with
+    four copies and one), beside others: waves off screen, behind the camera, of extreme
+    w and elsewhere on the screen, in every place of the workgroup; into a framebuffer that
+    holds keys already."""
+    n = 16 * 256 + 77
+    c, v = rectangle_scene(*wh, n, 41, outside=200)
+    v.near, v.far = 2.005, 1e39
+    if depth[0] == 0:
+        v.far = 2.6
+    rng = np.random.default_rng(42)
+    for i, what in enumerate(["", "off", "", "behind", "behind", "off", "off", "", "far", "", "",
+                              "far", "huge", "", "off", ""]):
+        w = slice(256 * i, 256 * (i + 1))
+        if what == "off":
+            c.x[w] += 4 * np.abs(c.z[w])
+        elif what == "behind":
+            for a in (c.x, c.y, c.z):
+                a[w] = -a[w]
+        elif what == "far":
+            c.x[w] += (0.5 * c.z[w]).astype(np.float32)
+        elif what == "huge" and depth[0] != 0:
+            for a in (c.x, c.y, c.z):
+                a[256 * i + 5:256 * (i + 1):9] *= np.float32(5e37)
+    v2 = gen.View(v.vp, v.near, v.far, v.width, v.height)
+    if depth[0] == 2:
+        v2.far = 2.6
+    pts = rz.Points.from_cloud(c)
+    keys, _ = oracle.render_atomicmin(c.x, c.y, c.z, c.rgb, v2.vp, v2.near, v2.far, v2.width,
+                                      v2.height, *depth)
+    fb, _ = rz.new_framebuffer(v2, 0)
+    for _ in range(2):
+        rz.rasterize_atomicmin(pts, v2, depth, fb=fb, keep_keys=True)
+        assert np.array_equal(rz.to_u64(fb), keys)
+    some = rng.permutation(n)[:1500]   # fewer, in another order, into the same keys
+    c2 = gen.Cloud(c.x[some], c.y[some], c.z[some], c.rgb[some] ^ np.uint32(0x010101))
+    want = oracle.render_atomicmin(np.r_[c.x, c2.x], np.r_[c.y, c2.y], np.r_[c.z, c2.z],
+                                   np.r_[c.rgb, c2.rgb], v2.vp, v2.near, v2.far, v2.width,
+                                   v2.height, *depth)[0]
+    rz.rasterize_atomicmin(rz.Points.from_cloud(c2), v2, depth, fb=fb, keep_keys=True)
+    assert np.array_equal(rz.to_u64(fb), want)
