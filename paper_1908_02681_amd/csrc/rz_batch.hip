@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 6 : 1) k_mv_hq_accum(Pt
             uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
             SumFlush<PPT> flush;
             accum_chunk_wave<PPT, PW>(P, T, views[k].eps, views[k].fb, views[k].acc, x, y, z, c,
-                                      w_tile, words, flush, [] {});
+                                      w_tile, words, flush);
             accum_wave_flush<PPT>(views[k].acc, w_tile, flush);
         } else {
             if (BIN == kBinBlock && k > 0)

@@ -189,7 +189,8 @@ __device__ __forceinline__ double window_threshold(const Proj &P, const Eps &eps
     const double r = (double)eps.num * (dm + P.z0d);
     const double f = floor(r * eps.inv_den);
     const double rem = __builtin_fma(-f, den, r);
-    return dm + (rem < 0.0 ? f - 1.0 : rem >= den ? f + 1.0 : f);
+    const double off = rem < 0.0 ? -1.0 : rem >= den ? 1.0 : 0.0;
+    return dm + (f + off);
 }
 
 // The IEEE quotient 1 / w for w > 0, without the full division sequence:
@@ -1562,80 +1563,122 @@ __device__ __forceinline__ void accum_chunk(const Proj &P, uint32_t eps_num, uin
     }
 }
 
-// accum_chunk_wave for any wave: each point with its own flags.  The points are
-// projected once for the rectangle and again for their depths, so that no array of
-// them is held.  A wave of at most 512 points (PPT <= 8) adds one packed word
-// per fragment, R | G << 17 | B << 34 | count << 51: no field of a sum over the
-// wave can carry into the next (512 * 255 < 2^17, 512 < 2^13); larger waves keep
-// the accumulator's own two words.
+// Adds the sums a0, a1 to pixel p of the accumulator.
+__device__ __forceinline__ void add_pixel(gu64 *acc, uint32_t p, uint64_t a0, uint64_t a1)
+{
+    gu64 *dst = acc + 2 * (uint64_t)p;
+    __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Splat sums of up to 512 points in one word, R | G << 17 | B << 34 | count << 51: no
+// field can carry into the next (512 * 255 < 2^17, 512 < 2^13).
+__device__ __forceinline__ uint64_t pack_sums(uint32_t c)
+{
+    const uint32_t r = c & 0xFFu, g = (c >> 8) & 0xFFu, b = (c >> 16) & 0xFFu;
+    return ((uint64_t)((b << 2) | (1u << 19)) << 32) | (r | (g << 17));
+}
+
+// The accumulator's two words of them.
+__device__ __forceinline__ uint64_t sums_rg(uint64_t w)
+{
+    return (w & 0x1FFFFull) | (((w >> 17) & 0x1FFFFull) << 32);
+}
+__device__ __forceinline__ uint64_t sums_bn(uint64_t w)
+{
+    return ((w >> 34) & 0x1FFFFull) | ((w >> 51) << 32);
+}
+
+// The second half of a wave's accumulate pass with flags per point: waves that
+// accum_wave_fast does not take.  Consecutive points of a thread in one pixel are summed
+// in registers.  A wave of at most 512 points (PPT <= 8) keeps its sums in its tile as
+// packed words, larger waves as the accumulator's own two words.
 template <int PPT, bool PW>
-__device__ __forceinline__ void accum_wave_any(const Proj &P, const Trans &T, const Eps &eps,
-                                               const uint64_t *__restrict__ fb,
-                                               uint64_t *__restrict__ acc, const float (&x)[PPT],
-                                               const float (&y)[PPT], const float (&z)[PPT],
-                                               const uint32_t (&c)[PPT], uint64_t *w_tile,
-                                               uint32_t words)
+__device__ __forceinline__ void accum_view(const Proj &P, const Trans &T, const Eps &eps,
+                                           const uint64_t *__restrict__ fb,
+                                           uint64_t *__restrict__ acc, const float (&x)[PPT],
+                                           const float (&y)[PPT], const float (&z)[PPT],
+                                           const uint32_t (&c)[PPT], const float (&fx)[PPT],
+                                           const float (&fy)[PPT], uint32_t behind, const Box &box,
+                                           uint64_t *w_tile, uint32_t words)
 {
     constexpr bool kPacked = PPT <= 8;
     constexpr uint32_t kSh = kPacked ? 3u : 4u;   // bytes per pixel, log2
-    const Box box = wave_screen_box<PPT>(P, T, x, y, z);
-    if (box.x0 > box.x1)
-        return;
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
     const bool tiled = tile_fits(t.area, words, kSh);
     const uint32_t base = lds_addr(w_tile);
     const gu64 *gfb = (const gu64 *)global_ptr(fb);
     gu64 *gacc = global_ptr(acc);
-    auto add_pixel = [&](uint32_t p, uint64_t a0, uint64_t a1) {
-        gu64 *dst = gacc + 2 * (uint64_t)p;
-        __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
     if (tiled) {
         for (uint32_t i = lane; i < (t.area << (kSh - 3)); i += 64)
             *lds_ptr(base + 8 * i) = 0ull;
         wave_sync();
     }
     const uint32_t first = tile_first(t, base, kSh);
-    constexpr int G = 4;   // nearest depths in flight
-#pragma unroll
-    for (int g = 0; g < PPT; g += G) {
-        uint32_t px[G], py[G];
-        uint64_t q[G], near[G];
-        bool ok[G];
+    // groups of four points, the nearest depths of the next one in flight
+    constexpr int G = 4, N = PPT / G;
+    uint32_t at[2][G];   // LDS address of the pixel's entry, or the pixel beside a tile
+    uint64_t q[2][G], near[2][G];
+    bool ok[2][G];
+    auto read = [&](int g) {
+        const int b = g & 1;
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            float xx = x[g + k], yy = y[g + k], zz = z[g + k];
+            const int j = G * g + k;
+            float wx = fx[j], wy = fy[j];
+            own(wx), own(wy);
+            ok[b][k] = visible(P, wx, wy, behind, j);
+            const uint32_t px = (uint32_t)(int32_t)(ok[b][k] ? wx : 0.0f);
+            const uint32_t py = (uint32_t)(int32_t)(ok[b][k] ? wy : 0.0f);
+            float xx = x[j], yy = y[j], zz = z[j];
             own(xx), own(yy), own(zz);
-            px[k] = py[k] = 0;
-            q[k] = 0;
-            ok[k] = fragment<PW>(P, T, xx, yy, zz, px[k], py[k], q[k]);
+            q[b][k] = depth_enc<PW, 0>(P, T, xx, yy, zz, 0.0f, 0.0f, ok[b][k]);
+            const uint32_t pix = __umul24(py, t.width) + px;
             // a discarded fragment reads pixel 0
-            near[k] = gfb[ok[k] ? __umul24(py[k], t.width) + px[k] : 0u];
-            if (k % 2)
-                __builtin_amdgcn_sched_barrier(0);
+            near[b][k] = gfb[ok[b][k] ? pix : 0u];
+            at[b][k] = tiled ? ((__umul24(py, t.bw) + px) << kSh) + first : pix;
+            own(at[b][k]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    read(0);
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+        const int b = g & 1;
+        if (g + 1 < N)
+            read(g + 1);
+        uint64_t sum[G];
+        bool in[G], run = false;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            in[k] = in_window_live<PW>(P, eps.num, eps.den, q[b][k], near[b][k] >> 24, ok[b][k]);
+            sum[k] = pack_sums(c[G * g + k]);
+            if (k > 0)
+                run = run | (in[k] & in[k - 1] & (at[b][k] == at[b][k - 1]));
+        }
+        if (wave_any(run)) {
+#pragma unroll
+            for (int k = 1; k < G; ++k) {
+                const bool same = in[k] & in[k - 1] & (at[b][k] == at[b][k - 1]);
+                sum[k] += same ? sum[k - 1] : 0ull;
+                in[k - 1] = in[k - 1] & !same;
+            }
         }
 #pragma unroll
         for (int k = 0; k < G; ++k) {
-            const bool in = in_window_live<PW>(P, eps.num, eps.den, q[k], near[k] >> 24, ok[k]);
-            const uint32_t col = c[g + k];
-            const uint32_t cr = col & 0xFFu, cg = (col >> 8) & 0xFFu, cb = (col >> 16) & 0xFFu;
-            if (in) {
-                lu64 *w = lds_ptr(((__umul24(py[k], t.bw) + px[k]) << kSh) + first);
-                const uint64_t a0 = (uint64_t)cr | ((uint64_t)cg << 32);
-                const uint64_t a1 = (uint64_t)cb | (1ull << 32);
-                if (!tiled) {
-                    add_pixel(__umul24(py[k], t.width) + px[k], a0, a1);
-                } else if (kPacked) {
-                    const uint64_t one = ((uint64_t)((cb << 2) | (1u << 19)) << 32) |
-                                         (cr | (cg << 17));
-                    __hip_atomic_fetch_add(w, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                } else {
-                    __hip_atomic_fetch_add(w, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    __hip_atomic_fetch_add(w + 1, a1, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
+            if (!in[k])
+                continue;
+            if (!tiled) {
+                add_pixel(gacc, at[b][k], sums_rg(sum[k]), sums_bn(sum[k]));
+            } else if (kPacked) {
+                __hip_atomic_fetch_add(lds_ptr(at[b][k]), sum[k], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else {
+                __hip_atomic_fetch_add(lds_ptr(at[b][k]), sums_rg(sum[k]), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(lds_ptr(at[b][k]) + 1, sums_bn(sum[k]), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -1645,15 +1688,10 @@ __device__ __forceinline__ void accum_wave_any(const Proj &P, const Trans &T, co
     wave_sync();
     for (uint32_t i = lane; i < t.area; i += 64) {
         const uint64_t w = *lds_ptr(base + (i << kSh));
-        uint64_t a0 = w, a1;
-        if (kPacked) {
-            a0 = (w & 0x1FFFFull) | (((w >> 17) & 0x1FFFFull) << 32);
-            a1 = ((w >> 34) & 0x1FFFFull) | ((w >> 51) << 32);
-        } else {
-            a1 = *lds_ptr(base + (i << kSh) + 8);
-        }
+        const uint64_t a0 = kPacked ? sums_rg(w) : w;
+        const uint64_t a1 = kPacked ? sums_bn(w) : *lds_ptr(base + (i << kSh) + 8);
         if (a1 != 0ull)   // count > 0
-            add_pixel(tile_pixel(t, i), a0, a1);
+            add_pixel(gacc, tile_pixel(t, i), a0, a1);
     }
     wave_sync();   // the tile is free for the next use
 }
@@ -1693,9 +1731,8 @@ __device__ __forceinline__ void accum_wave_flush(uint64_t *__restrict__ acc, con
             add(a.y);
         }
         if (a1 != 0ull) {   // count > 0
-            gu64 *dst = gacc + 2 * (uint64_t)p;
-            __hip_atomic_fetch_add(dst, a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(dst + 1, a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            own(p);   // its address is not made before
+            add_pixel(gacc, p, a0, a1);
         }
     };
 #pragma unroll
@@ -1710,51 +1747,30 @@ __device__ __forceinline__ void accum_wave_flush(uint64_t *__restrict__ acc, con
     wave_sync();   // the tile is free for the next use
 }
 
-// Accumulate pass over one chunk with a private LDS tile per wave of `words`
-// words.  Same result bits as accum_chunk.  accum_wave_flush must follow with
-// the same `flush`; again() as for raster_chunk_wave.
+// The second half for a wave wholly on screen, under a map and a window of which the
+// threshold of a pixel is known (window_threshold).
 //
-// As there, a wave whose points are all on screen and in range needs no flag
-// per point; every other one takes accum_wave_any, and so do waves whose
-// rectangle does not fit the tile, piecewise maps, and windows whose products
-// are not exact in double precision (see below).
-//
-// The window test is one comparison per point against a threshold per pixel
-// (window_threshold).  The thresholds lie in LDS beside the sums: the nearest depths of the rectangle are read in coalesced rows
-// while the depths are computed, instead of one by one.
+// The window test is one comparison per point against its pixel's threshold.  The
+// thresholds lie in LDS beside the sums: the nearest depths of the rectangle are read in
+// coalesced rows while the depths are computed, instead of one by one.
 //
 // Sums: R | G << 16 | B << 32 | count << 48 in copies of the tile, four where
 // they fit, else two (neighbouring lanes hold neighbouring points, and the LDS
 // adds of one address follow each other one per cycle).  One of two copies, or a
 // pair of the four, takes the points of 32 lanes of at most 8 points:
 // 256 * 255 < 2^16, so no field carries before the fields are unpacked.
-template <int PPT, bool PW>
-__device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, const Eps &eps,
+template <int PPT>
+__device__ __forceinline__ void accum_wave_fast(const Proj &P, const Trans &T, const Eps &eps,
                                                 const uint64_t *__restrict__ fb,
                                                 const float (&x)[PPT], const float (&y)[PPT],
                                                 const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                                uint64_t *w_tile, uint32_t words,
+                                                const float (&fx)[PPT], const float (&fy)[PPT],
+                                                const Box &box, uint64_t *w_tile, uint32_t words,
                                                 SumFlush<PPT> &flush)
 {
-    flush.t.area = 0;
-    if ((PW && P.nr != 0) || !window_exact(P, eps))
-        return false;
-    float fx[PPT], fy[PPT];
-    Box box;
-    const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
-    if (where == kOffScreen)
-        return true;
-    if (where != kOnScreen || 3 * (box.x1 - box.x0 + 1) * (box.y1 - box.y0 + 1) > words)
-        return false;
     const uint32_t lane = threadIdx.x & 63u;
     const WaveTile t = wave_tile(P, box);
     const gu64 *gfb = (const gu64 *)global_ptr(fb);
-    bool in = true;
-    auto depth_q = [&](int j) {   // q as a double
-        const double d = depth_of(P, T.td, x[j], y[j], z[j]);
-        in = in & (d >= P.dlo[0]) & (d < P.dhi[0]);
-        return floor((d - P.o) * P.s);
-    };
     constexpr int kPre = SumFlush<PPT>::kPre;
     const uint32_t base = lds_addr(w_tile);
     const bool four = 5 * t.area <= words;
@@ -1773,12 +1789,27 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
     zero.x = zero.y = 0ull;
     for (uint32_t i = 16 * lane; i < (t.area << sh); i += 1024)
         *lds_ptr2(base + i) = zero;
-    double q[PPT];
+    double q[PPT];   // infinite for a point out of range, beyond every threshold
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        q[j] = depth_q(j);
-        if (j % 2)
-            __builtin_amdgcn_sched_barrier(0);
+    for (int g = 0; g < PPT; g += 4) {
+        double d[4];
+        bool out = false;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int j = g + k;
+            d[k] = depth_of(P, T.td, x[j], y[j], z[j]);
+            q[j] = floor((d[k] - P.o) * P.s);
+            out = out | (d[k] < P.dlo[0]) | (d[k] >= P.dhi[0]);
+            if (k % 2)
+                __builtin_amdgcn_sched_barrier(0);
+        }
+        if (wave_any(out)) {   // (a NaN fails the window test anyway)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool in = (d[k] >= P.near_) & (d[k] < P.far_);
+                q[g + k] = in ? fmin(q[g + k], kQMax) : __builtin_inf();
+            }
+        }
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j)   // not before the depths are there
@@ -1787,8 +1818,6 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
     for (int k = 1; k < kPre; ++k)
         if (t.area > 64u * k)
             arrive(near[k]);
-    if (wave_any(!in))
-        return false;
     typedef __attribute__((address_space(3))) double lf64;
 #pragma unroll
     for (int k = 0; k < kPre; ++k) {
@@ -1831,25 +1860,62 @@ __device__ __forceinline__ bool accum_wave_fast(const Proj &P, const Trans &T, c
 #pragma unroll
     for (int k = 0; k < kPre; ++k)
         flush.pix[k] = pix[k];
-    return true;
 }
 
-template <int PPT, bool PW, typename Again>
+// Accumulate pass over one chunk with a private LDS tile per wave of `words`
+// words.  Same result bits as accum_chunk.  accum_wave_flush must follow with
+// the same `flush`.
+//
+// As in the depth pass, a wave whose points are all on screen needs no flag per point
+// (accum_wave_fast); every other one goes on from the same window positions with flags
+// (accum_view), and so do waves whose rectangle does not fit the tile, piecewise maps,
+// and windows whose products are not exact in double precision.
+template <int PPT, bool PW>
 __device__ __forceinline__ void accum_chunk_wave(const Proj &P, const Trans &T, const Eps &eps,
                                                  const uint64_t *__restrict__ fb,
                                                  uint64_t *__restrict__ acc, const float (&x)[PPT],
                                                  const float (&y)[PPT], const float (&z)[PPT],
                                                  const uint32_t (&c)[PPT], uint64_t *w_tile,
-                                                 uint32_t words, SumFlush<PPT> &flush,
-                                                 const Again &again)
+                                                 uint32_t words, SumFlush<PPT> &flush)
 {
+    float fx[PPT], fy[PPT];
+    Box box;
+    uint32_t behind = 0u;
     flush.t.area = 0;
-    if constexpr (PPT <= 8) {   // the sums' 16-bit fields
-        if (accum_wave_fast<PPT, PW>(P, T, eps, fb, x, y, z, c, w_tile, words, flush))
-            return;
-        again();
+    const Where where = window_all<PPT>(P, T, x, y, z, fx, fy, box);
+    if (where == kOffScreen)
+        return;
+    if (where == kMixed && sort_w<PPT>(P, T, x, y, z, behind)) {   // no wave in practice
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            float xx = x[j], yy = y[j], zz = z[j];
+            own(xx), own(yy), own(zz);
+            uint32_t px, py;
+            uint64_t q;
+            const bool live = fragment<PW>(P, T, xx, yy, zz, px, py, q);
+            const uint32_t pix = __umul24(py, (uint32_t)P.width) + px;
+            const uint64_t qmin = global_ptr(fb)[live ? pix : 0u] >> 24;
+            if (in_window_live<PW>(P, eps.num, eps.den, q, qmin, live)) {
+                const uint64_t w = pack_sums(c[j]);
+                add_pixel(global_ptr(acc), pix, sums_rg(w), sums_bn(w));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
     }
-    accum_wave_any<PPT, PW>(P, T, eps, fb, acc, x, y, z, c, w_tile, words);
+    if (where != kOnScreen) {
+        box = window_box<PPT>(P, fx, fy, behind);
+        if (box.x1 > kMaxPixel)   // no point on screen
+            return;
+    }
+    if constexpr (PPT <= 8) {   // the sums' 16-bit fields
+        if (where == kOnScreen && !(PW && P.nr != 0) && window_exact(P, eps) &&
+            3 * (box.x1 - box.x0 + 1) * (box.y1 - box.y0 + 1) <= words) {
+            accum_wave_fast<PPT>(P, T, eps, fb, x, y, z, c, fx, fy, box, w_tile, words, flush);
+            return;
+        }
+    }
+    accum_view<PPT, PW>(P, T, eps, fb, acc, x, y, z, c, fx, fy, behind, box, w_tile, words);
 }
 
 // Colour of one pixel from its packed splat sums (section 2.2, third pass):

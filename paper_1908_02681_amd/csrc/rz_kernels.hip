@@ -79,12 +79,12 @@ __global__ void __launch_bounds__(512) k_raster_min_zk(Pts p, Proj P, uint64_t *
     raster_wave_flush(fb, w_tile, flush);
 }
 
-// Accumulation pass of section 2.2 for one view.
+// Accumulation pass of section 2.2 for one view.  At 8 points a thread, the default for
+// large clouds, five waves a SIMD: 96 registers, 100 if the compiler may choose.
 template <int PPT, bool XCD, int BIN, bool PW>
-__global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, Eps eps,
-                                                  const uint64_t *__restrict__ fb,
-                                                  uint64_t *__restrict__ acc, int64_t nchunks,
-                                                  uint32_t words)
+__global__ void __launch_bounds__(512, PPT == 8 && BIN == kBinWave ? 5 : 1)
+    k_hq_accum(Pts p, Proj P, Eps eps, const uint64_t *__restrict__ fb, uint64_t *__restrict__ acc,
+               int64_t nchunks, uint32_t words)
 {
     __shared__ uint64_t s_tile[BIN == kBinBlock ? 2 * kTileHq : 2];
     __shared__ uint32_t s_box[kMaxWaves][4];
@@ -97,15 +97,13 @@ __global__ void __launch_bounds__(512) k_hq_accum(Pts p, Proj P, Eps eps,
     bool in[PPT];
     uint64_t *w_tile = s_waves + (threadIdx.x >> 6) * words;
     // no per-point bounds flags: points past the end load as NaN and are culled
-    auto load = [&] { load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c); };
-    load();
+    load_points_nan<PPT>(p, chunk * (int64_t)blockDim.x * PPT, x, y, z, c);
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
         in[j] = true;
     if (BIN == kBinWave) {
         SumFlush<PPT> flush;
-        accum_chunk_wave<PPT, PW>(P, lane_trans(P), eps, fb, acc, x, y, z, c, w_tile, words, flush,
-                                  load);
+        accum_chunk_wave<PPT, PW>(P, lane_trans(P), eps, fb, acc, x, y, z, c, w_tile, words, flush);
         accum_wave_flush<PPT>(acc, w_tile, flush);
     } else {
         accum_chunk<PPT, BIN == kBinBlock, PW>(P, eps.num, eps.den, fb, acc, x, y, z, c, in,

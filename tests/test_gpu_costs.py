@@ -107,3 +107,17 @@ def test_small_unordered_clouds_on_few_pixels(rz, screen, eye, depth):
         rz.reset_launch()
     r = ratio(f"few pixels {screen} depth {depth[0]}", f, large)
     assert r < 2.0   # 1.0; 7.5 and 5.0 with each wave's atomics on their own
+
+
+@pytest.mark.parametrize("what,limit", [("cut", 1.2),      # 0.95; 1.5 with waves projected twice
+                                        ("window", 1.17),  # 1.02; 1.33
+                                        ("noise", 12.0)])  # 7.1; 20 with two atomics per point
+def test_splats_off_the_common_path(rz, terrain, noisy, what, limit):
+    """Splat frames of waves mostly out of the depth range, under a window without a threshold
+    per pixel, and spread by stray points."""
+    cut = gen.terrain_view(1920, 1080, near=900.0, far=1100.0)
+    f = {"cut": lambda: frame(rz, terrain, cut, True),
+         "window": lambda: frame(rz, terrain, HD, True, eps=(1, 10000)),
+         "noise": lambda: frame(rz, noisy, HD, True)}[what]()
+    r = ratio(f"splat {what}", f, frame(rz, terrain, HD, True))
+    assert r < limit

@@ -244,3 +244,57 @@ def test_waves_that_share_a_tile(rz, oracle, wh, depth):
                                    v2.height, *depth)[0]
     rz.rasterize_atomicmin(rz.Points.from_cloud(c2), v2, depth, fb=fb, keep_keys=True)
     assert np.array_equal(rz.to_u64(fb), want)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("depth,eps", [((0, 0.0), (1, 100)), ((0, 0.0), (1, 4097)),
+                                       ((2, ((0.0, 1e9), (2.015, 1e6), (10.0, 1e3))), (1, 100))])
+@pytest.mark.parametrize("wh", [(9, 7), (24, 20), (41, 25), (300, 200)])
+def test_splats_across_depth_ranges(rz, oracle, wh, depth, eps, shape):
+    """Sums of waves of which some points lie before near, beyond far or in another range,
+    under windows with a threshold per pixel and without, inside the tile and beside it,
+    partly off screen too."""
+    for i, (ox, oy) in enumerate([(37, 21), (-3, -2)]):
+        c, v = rectangle_scene(*wh, n=3001, seed=50 + i, ox=ox, oy=oy, outside=300, behind=40)
+        v.near, v.far = 2.005, 2.05
+        keys, sums, himg = oracle.render_hq(c.x, c.y, c.z, c.rgb, v.vp, v.near, v.far, v.width,
+                                            v.height, *depth, eps=eps)
+        pts = rz.Points.from_cloud(c)
+        rz.reset_launch() if shape is None else rz.set_launch(*shape)
+        try:
+            fb, acc, _, _ = rz.rasterize_hq_splat(pts, v, depth, eps, keep_keys=True)
+        finally:
+            rz.reset_launch()
+        assert np.array_equal(rz.to_u64(fb), keys), (ox, oy)
+        assert np.array_equal(rz.unpack_acc(acc), sums), (ox, oy)
+        b = rz.Batch(pts, [v, v], [1, 1], depth=depth, eps=eps, launch=shape)
+        b.run()
+        assert all(np.array_equal(g, himg) for g in b.images())
+
+
+@pytest.mark.parametrize("shape", [None, (64, 8, 1, 0, 3), (128, 8, 1, 0, 2), (64, 16, 1, 0, 2)])
+@pytest.mark.parametrize("depth,eps", [((0, 0.0), (1, 100)), ((0, 0.0), (1, 4097)),
+                                       ((2, ((0.0, 1e9), (10.0, 1e6))), (1, 100))])
+@pytest.mark.parametrize("rgb", [0xFFFFFF, 0xFF00FF, 0x00FF00])
+def test_splat_word_limits_under_every_window(rz, rgb, depth, eps, shape):
+    """Every point in one pixel with one colour, under windows with a threshold per pixel
+    (16-bit fields in copies of the tile) and under windows and maps without (17-bit fields in
+    one copy): the sums are n times each channel and n, with no carry from field to field,
+    also where a thread's points are summed first."""
+    import torch
+    view = gen.View(np.diag([1.0, 1.0, 0.0, 0.0]) + np.array(
+        [[0, 0, 0, 0], [0, 0, 0, 0], [0, 0, 0, 0], [0, 0, -1.0, 0]]), 1.0, 100.0, 2, 2)
+    n = 5 * 64 * 16 * 8 + 77
+    pts = rz.Points(torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda"),
+                    torch.full((n,), -10.0, device="cuda"),
+                    torch.full((n,), rgb, dtype=torch.int32, device="cuda"))
+    rz.reset_launch() if shape is None else rz.set_launch(*shape)
+    try:
+        _, acc, _, _ = rz.rasterize_hq_splat(pts, view, depth, eps, keep_keys=True)
+    finally:
+        rz.reset_launch()
+    sums = rz.unpack_acc(acc)
+    hit = np.flatnonzero(sums[:, 3])
+    assert hit.size == 1
+    want = [n * (rgb & 0xFF), n * ((rgb >> 8) & 0xFF), n * ((rgb >> 16) & 0xFF), n]
+    assert sums[hit[0]].tolist() == want
