@@ -64,12 +64,24 @@ struct MvResolve {
 // nothing (50M points 140.3 / 140.7 us) and read the current keys.
 constexpr int64_t kCachedReads = 8 << 20;
 
+// A view's constants in the kernels: a copy, in scalar registers; under piecewise maps
+// (PW) the table itself, since a copy would lie in scratch memory for the ranges that
+// its lanes look up.
+template <bool PW>
+struct ViewConst {
+    using type = const Proj;
+};
+template <>
+struct ViewConst<true> {
+    using type = const Proj &;
+};
+
 // Depth passes of views[0 .. nv) over one chunk: the points are loaded
 // once and stay in registers while each view is rasterized in turn.
 template <int PPT, bool XCD, int BIN, bool PW>
-__global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(Pts p, const MvView *__restrict__ views,
-                                                       int32_t nv, int64_t nchunks,
-                                                       uint32_t words)
+__global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1)
+    k_mv_raster_min(Pts p, const MvView *__restrict__ views, int32_t nv, int64_t nchunks,
+                    uint32_t words)
 {
     __shared__ uint64_t s_tile[BIN == kBinBlock ? kTileMin : 1];
     __shared__ uint32_t s_box[kMaxWaves][4];
@@ -92,7 +104,7 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(
         own(x[j]), own(y[j]), own(z[j]), own(c[j]);
     const bool l2 = p.n >= kCachedReads;
     for (int32_t k = 0; k < nv; ++k) {
-        const Proj P = views[k].P;
+        typename ViewConst<PW>::type P = views[k].P;
         const Trans T = lane_trans(P);
 #pragma unroll
         for (int j = 0; j < PPT; ++j)   // nothing derived from the points is kept across views
@@ -113,9 +125,9 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 7 : 1) k_mv_raster_min(
 
 // Accumulate passes of the splatting views views[0 .. nv) over one chunk.
 template <int PPT, bool XCD, int BIN, bool PW>
-__global__ void __launch_bounds__(512, PPT == 4 && !PW ? 6 : 1) k_mv_hq_accum(Pts p, const MvView *__restrict__ views,
-                                                     int32_t nv, int64_t nchunks,
-                                                     uint32_t words)
+__global__ void __launch_bounds__(512, PPT == 4 && !PW ? 6 : 1)
+    k_mv_hq_accum(Pts p, const MvView *__restrict__ views, int32_t nv, int64_t nchunks,
+                  uint32_t words)
 {
     __shared__ uint64_t s_tile[BIN == kBinBlock ? 2 * kTileHq : 2];
     __shared__ uint32_t s_box[kMaxWaves][4];
@@ -137,7 +149,7 @@ __global__ void __launch_bounds__(512, PPT == 4 && !PW ? 6 : 1) k_mv_hq_accum(Pt
     for (int j = 0; j < PPT; ++j)
         own(x[j]), own(y[j]), own(z[j]), own(c[j]);
     for (int32_t k = 0; k < nv; ++k) {
-        const Proj P = views[k].P;
+        typename ViewConst<PW>::type P = views[k].P;
         const Trans T = lane_trans(P);
 #pragma unroll
         for (int j = 0; j < PPT; ++j)   // nothing derived from the points is kept across views

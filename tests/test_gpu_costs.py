@@ -34,6 +34,9 @@ def frame(rz, pts, view, hq=False, depth=(0, 0.0), eps=(1, 100), size=1):
     return lambda: rz.rasterize_points(pts, view, hq=hq, point_size=size, **kw)
 
 
+PIECEWISE = (2, ((0.0, 1e9), (10.0, 1e6), (10000.0, 1e3)))
+
+
 def ratio(label, run, base):
     """Time of `run` by that of `base`: the least of eight times of ten calls each."""
     import torch
@@ -121,3 +124,14 @@ def test_splats_off_the_common_path(rz, terrain, noisy, what, limit):
          "noise": lambda: frame(rz, noisy, HD, True)}[what]()
     r = ratio(f"splat {what}", f, frame(rz, terrain, HD, True))
     assert r < limit
+
+
+@pytest.mark.parametrize("launch", [(256, 4, 1, 0, 3), (64, 16, 1, 0, 2)])
+def test_batches_under_a_piecewise_map(rz, terrain, launch):
+    """Depth frames under a piecewise map beside the same views under the linear one."""
+    pts = rz.Points(*[a[:10_000_000] for a in (terrain.x, terrain.y, terrain.z, terrain.rgb)])
+    views = gen.orbit_views(8, 5, [(1920, 1080), (1280, 720)])
+    b = [rz.Batch(pts, views, [0] * 8, depth=d, views_per_group=8, launch=launch, use_graph=True)
+         for d in (PIECEWISE, (0, 0.0))]
+    r = ratio(f"piecewise batch {launch}", b[0].run, b[1].run)
+    assert r < 2.5   # 1.2; 5 and 14 with the ranges in scratch memory
