@@ -25,11 +25,15 @@ ARCH = "gfx950"
 
 # -ffp-contract=off: the projection must be the exact IEEE operation sequence
 # of the interface (fused multiply-adds only where the source writes them);
-# packed fp32 instructions are disabled for all device code.
+# packed fp32 instructions are disabled for all device code.  A kernel reads its by-value
+# constants in place only while the compiler follows all their uses, by default up to 300;
+# the splat pass at 16 points a thread under a piecewise map has more, and would look the
+# ranges up in a scratch copy (20M points 582 us, 253 in place).
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-fno-gpu-rdc", "-Wall", "-Wno-unused-function",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-instcombine-max-copied-from-constant-users=4096",
     f"-I{INCLUDE}", f"-I{CSRC}",
 ]
 

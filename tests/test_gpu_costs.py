@@ -135,3 +135,17 @@ def test_batches_under_a_piecewise_map(rz, terrain, launch):
          for d in (PIECEWISE, (0, 0.0))]
     r = ratio(f"piecewise batch {launch}", b[0].run, b[1].run)
     assert r < 2.5   # 1.2; 5 and 14 with the ranges in scratch memory
+
+
+def test_large_splat_waves_under_a_piecewise_map(rz, terrain):
+    """16 points a thread beside 8."""
+    f = frame(rz, terrain, HD, True, depth=PIECEWISE)
+
+    def shape(*launch):
+        def run():
+            rz.set_launch(*launch)
+            f()
+            rz.reset_launch()
+        return run
+    r = ratio("piecewise splat 16", shape(64, 16, 1, 0, 2), shape(64, 8, 1, 0, 3))
+    assert r < 2.0   # 1.13; 2.7 with the ranges in scratch memory
