@@ -22,7 +22,9 @@
 // are met again.  Frames at 1920x1080, read past it / through it: 50M points, k = 2,
 // 3, 5, 8, 16: 197 / 191, 196 / 188, 230 / 210, 530 / 417, 1273 / 978 us; 5M points
 // 45 / 44, 54 / 54, 78 / 78, 150 / 150, 684 / 678; 0.5M (few waves fit their tile)
-// 64 / 61, 111 / 108, 233 / 224, 444 / 428, 1281 / 1242.
+// 64 / 61, 111 / 108, 233 / 224, 444 / 428, 1281 / 1242.  Beside the tile that holds for
+// sparse clouds only: 2M points with a stray one in 256, k = 2 and 3, 101 / 115 and 177 /
+// 193 us, so waves with runs of points in one pixel read past it there.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -261,13 +263,18 @@ __global__ void __launch_bounds__(kGenBlock) k_raster_points(Pts p, Proj P, int3
     }
     // consecutive points of a thread with one centre pixel cover the same
     // square: keep only their smaller key (k^2 atomics saved per merge)
+    bool run = false;
 #pragma unroll
     for (int j = 1; j < kGenPpt; ++j) {
         const bool same = live[j] && live[j - 1] && px[j] == px[j - 1] && py[j] == py[j - 1];
         const uint64_t lo = key[j] < key[j - 1] ? key[j] : key[j - 1];
         key[j] = same ? lo : key[j];
         live[j - 1] = live[j - 1] && !same;
+        run = run | same;
     }
+    // Waves with such runs are those of a dense ordered cloud with a stray point in them:
+    // their neighbours lower the same pixels, and an older key costs an atomic.
+    const bool l2 = __builtin_popcountll(__builtin_amdgcn_ballot_w64(run)) < 8;
     const Cover cv = wave_cover(wave_box<kGenPpt>(px, py, live), k, P.width, P.height,
                                 kWaveTileMin);
     if (cv.tiled) {
@@ -316,7 +323,7 @@ __global__ void __launch_bounds__(kGenBlock) k_raster_points(Pts p, Proj P, int3
         for (int32_t yy = y0; yy < y1; ++yy) {
             for (int32_t xx = x0; xx < x1; ++xx) {
                 gu64 *dst = global_ptr(fb) + ((int64_t)yy * P.width + xx);
-                const uint64_t cur = read_nearest(dst, true);
+                const uint64_t cur = read_nearest(dst, l2);
                 if (key[j] < cur)
                     __hip_atomic_fetch_min(dst, key[j], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
