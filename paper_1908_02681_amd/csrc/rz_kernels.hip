@@ -211,7 +211,8 @@ hipError_t raster_min_ppt(const Pts &p, const Proj &P, uint64_t *fb, const Tune 
 }
 
 template <int PPT, int BIN, bool PW>
-hipError_t hq_accum_ppt(const Pts &p, const Proj &P, const Eps &eps, const uint64_t *fb, uint64_t *acc, const Tune &t, hipStream_t s)
+hipError_t hq_accum_ppt(const Pts &p, const Proj &P, const Eps &eps, const uint64_t *fb,
+                        uint64_t *acc, const Tune &t, hipStream_t s)
 {
     const int64_t nchunks = blocks_for(p.n, (int64_t)t.block * PPT);
     const size_t lds = wave_lds(t.bin, t.block, true);
@@ -338,7 +339,8 @@ hipError_t launch_hq_accum(const Pts &p, const Proj &P, uint32_t num, uint32_t d
     Range r("rz splat accumulate pass");
     if (p.n == 0)
         return hipSuccess;
-    const Tune &t = tune.by_size && p.n < kSmallCloud ? kSmallTune : tune;
+    const bool small = p.n < kSmallCloud && (int64_t)P.width * P.height > kFewPixels;
+    const Tune &t = tune.by_size && small ? kSmallTune : tune;
     const Eps eps{num, den, 1.0 / (double)den};
     switch (t.ppt) {
     case 4: return hq_accum_dispatch<4>(p, P, eps, fb, acc, t, s);

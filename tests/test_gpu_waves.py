@@ -298,3 +298,11 @@ def test_splat_word_limits_under_every_window(rz, rgb, depth, eps, shape):
     assert hit.size == 1
     want = [n * (rgb & 0xFF), n * ((rgb >> 8) & 0xFF), n * ((rgb >> 16) & 0xFF), n]
     assert sums[hit[0]].tolist() == want
+
+
+@pytest.mark.parametrize("wh", [(8, 8), (32, 16), (27, 19)])
+@pytest.mark.parametrize("n", [1, 513, 5003])
+def test_splats_on_few_pixels(rz, oracle, n, wh):
+    """Screens on both sides of the size from which small clouds take the small shape."""
+    c, v = rectangle_scene(*wh, n, 60, W=wh[0], H=wh[1], ox=0, oy=0)
+    render_all(rz, oracle, c, v)
