@@ -508,7 +508,7 @@ def main():
     himg = torch.empty(npix, dtype=torch.int32, device="cuda")
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
     torch.cuda.synchronize()
-    log(f"[bench] n={n} {W}x{H} launch={rz.get_launch()}")
+    log(f"[bench] n={n} {W}x{H} launch of large clouds={rz.get_launch()}")
 
     ws = rz.new_workspace(n, W, H) if a.path == "sorted" else None
     kinds = {"linear": rz.DEPTH_LINEAR, "gl24": rz.DEPTH_GL24, "f32rev": rz.DEPTH_F32REV}

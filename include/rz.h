@@ -311,9 +311,10 @@ int rz_resolve_hq(uint64_t *fb, uint64_t *acc, int64_t npix,
  *              its fragments fall in a small screen rectangle); 2: one LDS
  *              tile per wave (no workgroup barrier), 8 KiB; 3: the same with
  *              a 2 KiB tile (more waves per SIMD when registers allow them;
- *              6 KiB in the splat pass; a wave whose fragments span more than
- *              256 pixels, 768 when splatting, takes the direct atomics
- *              instead).
+ *              6 KiB in the splat pass).  A wave whose fragments span more
+ *              than 1024 pixels (3: 256) takes the direct atomics instead;
+ *              when splatting more than 1024 (3: 768), half of that at 16
+ *              points per thread.
  */
 typedef struct rz_launch {
     int32_t block;
@@ -323,11 +324,15 @@ typedef struct rz_launch {
     int32_t bin;
 } rz_launch;
 /* Sets the launch shape of both point passes of the one-view calls and the
-   server (RZ_EINVAL if out of range); NULL restores the library defaults
-   (depth pass 64 threads x 16 points with the 8 KiB per-wave tile, splat
-   pass 64 x 8 with the small per-wave tile, both 256 x 4 with the small tile
-   for clouds of fewer than 2^23 points; early-out, no XCD remap).  rz_get_launch
-   reports the depth pass's shape for large clouds.
+   server, for clouds of any size (RZ_EINVAL if out of range); NULL restores
+   the library defaults: depth pass 64 threads x 16 points with the 8 KiB
+   per-wave tile, splat pass 64 x 8 with the small per-wave tile, early-out, no
+   XCD remap; for clouds of fewer than 2^23 points (3 * 2^23 in the depth pass
+   of the float encodings) 256 x 4 with the small tile in both (the splat pass
+   only on screens of more than 512 pixels); for clouds of fewer than 2^20
+   points without the early-out read of fragments beside a tile.  rz_get_launch reports the depth
+   pass's shape for large clouds; to set the shape that it reports is to turn
+   the shapes by size off, and only NULL turns them on again.
    Thread-safe: a call running concurrently launches with either the old
    or the new shape, and both give the same result. */
 int rz_set_launch(const rz_launch *launch);

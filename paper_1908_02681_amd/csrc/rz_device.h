@@ -301,66 +301,6 @@ __device__ __forceinline__ double depth_of(const Proj &P, const Trans &T, float 
     return depth_of(P, T.td, x, y, z);
 }
 
-__device__ __forceinline__ double depth_of(const Proj &P, float x, float y, float z)
-{
-    return depth_of(P, scalar_trans(P), x, y, z);
-}
-
-// The fragment of one point: pixel coordinates and 40-bit depth (section
-// 2.1).  Returns false when the point is discarded; q is then meaningless.
-// Integer depth maps only (P.zkind == 0).  PW = false: linear or scale map
-// only (P.nr == 0), so the piecewise tables are never read; PW = true serves
-// every integer map.  Straight-line code apart from one wave-uniform skip
-// of the depth when no lane of the wave is on screen.
-// tq: q as a double for the linear and scale maps (meaningless for the
-// piecewise map).
-// vis: the point is on screen (w > 0, inside the framebuffer), whatever its
-// depth.
-template <bool PW>
-__device__ __forceinline__ bool fragment(const Proj &P, const Trans &T, float x, float y, float z,
-                                         uint32_t &px, uint32_t &py, uint64_t &q, double &tq,
-                                         bool &vis)
-{
-    float cw, iw;
-    vis = project(P, T, x, y, z, px, py, cw, iw);
-    q = 0;
-    tq = 0.0;
-    if (!wave_any(vis))
-        return false;
-    const double d = depth_of(P, T, x, y, z);
-    const bool in_range = d >= P.near_ && d < P.far_;
-    if (!PW || P.nr == 0) {
-        tq = fmin(floor((d - P.o) * P.s), kQMax);   // d < near gives garbage, unused
-        q = to_u64(tq);
-    } else {
-        q = piecewise_q(P, in_range ? d : P.near_);
-    }
-    return vis && in_range;
-}
-
-template <bool PW>
-__device__ __forceinline__ bool fragment(const Proj &P, const Trans &T, float x, float y, float z,
-                                         uint32_t &px, uint32_t &py, uint64_t &q, double &tq)
-{
-    bool vis;
-    return fragment<PW>(P, T, x, y, z, px, py, q, tq, vis);
-}
-
-template <bool PW>
-__device__ __forceinline__ bool fragment(const Proj &P, const Trans &T, float x, float y, float z,
-                                         uint32_t &px, uint32_t &py, uint64_t &q)
-{
-    double tq;
-    return fragment<PW>(P, T, x, y, z, px, py, q, tq);
-}
-
-template <bool PW>
-__device__ __forceinline__ bool fragment(const Proj &P, float x, float y, float z,
-                                         uint32_t &px, uint32_t &py, uint64_t &q)
-{
-    return fragment<PW>(P, scalar_trans(P), x, y, z, px, py, q);
-}
-
 // Depth of one point in any of the encodings, without the assumptions of a chunk
 // (ChunkKey): clears `in` for a point outside [near, far) or clipped by the 24-bit
 // window depth of the perspective matrix (RZ_DEPTH_GL24), whose depth is then
@@ -390,6 +330,43 @@ __device__ __forceinline__ uint64_t depth_enc(const Proj &P, const Trans &T, flo
     const float zw = (nz + 1.0f) * 0.5f;
     const float t = zw * 16777215.0f;
     return (uint64_t)(uint32_t)floor((double)(clip ? t : 0.0f) + 0.5);
+}
+
+// The fragment of one point: pixel coordinates and 40-bit depth (section
+// 2.1) under an integer depth map (P.zkind == 0).  Returns false when the point is
+// discarded; q is then meaningless.  PW = false: linear or scale map
+// only (P.nr == 0), so the piecewise tables are never read; PW = true serves
+// every integer map.  Straight-line code apart from one wave-uniform skip
+// of the depth when no lane of the wave is on screen.
+// vis: the point is on screen (w > 0, inside the framebuffer), whatever its
+// depth.
+template <bool PW>
+__device__ __forceinline__ bool fragment(const Proj &P, const Trans &T, float x, float y, float z,
+                                         uint32_t &px, uint32_t &py, uint64_t &q, bool &vis)
+{
+    float cw, iw;
+    vis = project(P, T, x, y, z, px, py, cw, iw);
+    q = 0;
+    bool in = vis;
+    if (!wave_any(vis))
+        return false;
+    q = depth_enc<PW, 0>(P, T, x, y, z, cw, iw, in);
+    return in;
+}
+
+template <bool PW>
+__device__ __forceinline__ bool fragment(const Proj &P, const Trans &T, float x, float y, float z,
+                                         uint32_t &px, uint32_t &py, uint64_t &q)
+{
+    bool vis;
+    return fragment<PW>(P, T, x, y, z, px, py, q, vis);
+}
+
+template <bool PW>
+__device__ __forceinline__ bool fragment(const Proj &P, float x, float y, float z,
+                                         uint32_t &px, uint32_t &py, uint64_t &q)
+{
+    return fragment<PW>(P, scalar_trans(P), x, y, z, px, py, q);
 }
 
 // The fragment of one point in a float encoding (ZK).
@@ -1052,29 +1029,6 @@ __device__ __forceinline__ uint32_t tile_first(const WaveTile &t, uint32_t base,
     return v;
 }
 
-// Box of the on-screen points of a wave.
-template <int PPT>
-__device__ __forceinline__ Box wave_screen_box(const Proj &P, const Trans &T, const float (&x)[PPT],
-                                               const float (&y)[PPT], const float (&z)[PPT])
-{
-    uint32_t lx = 0xFFFFFFFFu, ly = 0xFFFFFFFFu, hx = 0u, hy = 0u;
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-        float xx = x[j], yy = y[j], zz = z[j], cw, iw;
-        own(xx), own(yy), own(zz);
-        uint32_t px, py;   // 0 for a point off screen, which cannot raise a maximum
-        const bool vis = project(P, T, xx, yy, zz, px, py, cw, iw);
-        lx = min(lx, vis ? px : 0xFFFFFFFFu);
-        ly = min(ly, vis ? py : 0xFFFFFFFFu);
-        hx = max(hx, px);
-        hy = max(hy, py);
-        // this point's work ends here, and with it its registers
-        own(lx), own(ly), own(hx), own(hy);
-    }
-    // no point on screen: lx = ~0 > hx, an empty box
-    return Box{wave_min(lx), wave_min(ly), wave_max(hx), wave_max(hy)};
-}
-
 // The nearest key of a pixel, for an early out.  With `l2` the read may be served
 // by the XCD's L2, where a neighbouring chunk left the line; the key may be older
 // then, but like any early one it is an upper bound (at its start a launch sees
@@ -1194,8 +1148,8 @@ __device__ __forceinline__ bool wave_view(const Proj &P, const Trans &T, uint64_
 
 // The second half, with the wave's own tile (raster_chunk_wave).
 template <int PPT, bool PW, int ZK>
-__device__ __forceinline__ void raster_view(const Proj &P, const Trans &T, uint64_t *__restrict__ fb,
-                                            const float (&x)[PPT], const float (&y)[PPT],
+__device__ __forceinline__ void raster_view(const Proj &P, const Trans &T,
+                                            uint64_t *__restrict__ fb, const float (&x)[PPT], const float (&y)[PPT],
                                             const float (&z)[PPT], const uint32_t (&c)[PPT],
                                             const WaveView<PPT> &v, uint64_t *w_tile,
                                             uint32_t words, MinFlush &flush, bool l2, bool early)

@@ -348,9 +348,8 @@ __global__ void __launch_bounds__(kScBlock) k_sort_scatter(Pts p, Proj P,
         for (int j = 0; j < kScPpt; ++j) {
             uint32_t px = 0, py = 0;
             uint64_t qq = 0;
-            double tq;
             bool v = false;
-            const bool live = fragment<PW>(P, T, x[j], y[j], z[j], px, py, qq, tq, v);
+            const bool live = fragment<PW>(P, T, x[j], y[j], z[j], px, py, qq, v);
             key[j] = live ? (qq << 24) | ((uint64_t)c[j] & kRgbMask) : ~0ull;
             lb[j] = bucket_pixel(px, py, ntx);
             rank[j] = v ? atomicAdd(&s_off[lb[j] >> 12], 1u) : ~0u;
