@@ -48,9 +48,12 @@ constexpr uint32_t kWaveTileSmallWords = 256;
 // Tiling modes of the point kernels.  kBinWaveSmall is kBinWave with the
 // small tile: the kernels take the tile size as an argument, so both modes
 // share the kBinWave code.
-// kBinGroup (not a launch option) is kBinWaveSmall in a workgroup whose waves share
-// their tiles where they cover the same pixels.
+// kBinGroup (not a launch option) is kBinWaveSmall in a workgroup of kGroupWaves waves,
+// which share their tiles where they cover the same pixels.
 enum : int { kBinNone = 0, kBinBlock = 1, kBinWave = 2, kBinWaveSmall = 3, kBinGroup = 4 };
+constexpr uint32_t kGroupWaves = 4;
+static_assert(kSmallTune.block == 64 * kGroupWaves && kUnreadTune.block == kSmallTune.block,
+              "small clouds' workgroups");
 
 // Words of one wave's tile in a per-wave tiling mode.  The accumulate pass's
 // small tile has 6 KiB: three words a pixel (two copies of the sums and the
@@ -792,6 +795,18 @@ __device__ __forceinline__ Box bounds_box(int32_t v)
     return box;
 }
 
+// Minimum and sum within each quad of lanes.
+__device__ __forceinline__ uint32_t quad_min(uint32_t v)
+{
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0xB1, 0xF, 0xF, false));
+    return min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x4E, 0xF, 0xF, false));
+}
+__device__ __forceinline__ uint32_t quad_sum(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
+}
+
 // Window positions of a wave's points: kOnScreen, with their pixel rectangle,
 // when every point of the wave has a w in [2^-126, 2^126) and an on-screen window
 // position; kOffScreen when all lie beyond one edge of the screen or behind the
@@ -1146,7 +1161,91 @@ __device__ __forceinline__ bool wave_view(const Proj &P, const Trans &T, uint64_
     return true;
 }
 
-// The second half, with the wave's own tile (raster_chunk_wave).
+// The second half of a wave that spreads too far for its tile: groups of four points.
+// Consecutive points of a thread in one pixel send one atomic, and a group's early-out
+// reads are sent before the atomics of the group before it, which they would have to
+// wait for otherwise (one counter covers all memory operations of a wave, in order).
+template <int PPT, bool PW, int ZK>
+__device__ __forceinline__ void raster_spread(const Proj &P, const Trans &T,
+                                              uint64_t *__restrict__ fb, const float (&x)[PPT],
+                                              const float (&y)[PPT], const float (&z)[PPT],
+                                              const uint32_t (&c)[PPT], const WaveView<PPT> &v,
+                                              bool early)
+{
+    gu64 *gfb = global_ptr(fb);
+    const uint32_t width = (uint32_t)P.width;
+    const ChunkKey<PW, ZK> key_of(P, T, x[0], y[0], z[0]);
+    constexpr int G = 4, N = PPT / G;
+    uint32_t pix[2][G];
+    uint64_t key[2][G], cur[2][G];
+    bool live[2][G];
+    bool general = !PW;   // keys of points in any range
+    auto read = [&](int g) {
+        const int b = g & 1;
+        bool vis[G], run = false;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            const int j = G * g + k;
+            float wx = v.fx[j], wy = v.fy[j];
+            own(wx), own(wy);
+            vis[k] = visible(P, wx, wy, v.behind, j);
+            pix[b][k] = __umul24((uint32_t)(int32_t)(vis[k] ? wy : 0.0f), width) +
+                        (uint32_t)(int32_t)(vis[k] ? wx : 0.0f);
+        }
+        if (!general) {
+            bool all = true;
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                const int j = G * g + k;
+                live[b][k] = true;
+                key[b][k] = key_of(x[j], y[j], z[j], c[j], live[b][k]);
+                all = all & (live[b][k] | !vis[k]);
+                live[b][k] = live[b][k] & vis[k];
+            }
+            general = wave_any(!all);   // and so for the groups after it
+        }
+        if (general) {
+#pragma unroll
+            for (int k = 0; k < G; ++k) {
+                const int j = G * g + k;
+                live[b][k] = vis[k];
+                key[b][k] = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live[b][k]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int k = 1; k < G; ++k)
+            run = run | (live[b][k] & live[b][k - 1] & (pix[b][k] == pix[b][k - 1]));
+        if (wave_any(run)) {
+#pragma unroll
+            for (int k = 1; k < G; ++k) {
+                const bool same = live[b][k] & live[b][k - 1] & (pix[b][k] == pix[b][k - 1]);
+                const uint64_t lo = key[b][k] < key[b][k - 1] ? key[b][k] : key[b][k - 1];
+                key[b][k] = same ? lo : key[b][k];
+                live[b][k - 1] = live[b][k - 1] & !same;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k)   // a point that takes no part reads pixel 0
+            cur[b][k] = early ? read_nearest(gfb + (live[b][k] ? pix[b][k] : 0u), false) : ~0ull;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    read(0);
+#pragma unroll
+    for (int g = 0; g < N; ++g) {
+        const int b = g & 1;
+        if (g + 1 < N)
+            read(g + 1);
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (live[b][k] & (key[b][k] < cur[b][k]))
+                __hip_atomic_fetch_min(gfb + pix[b][k], key[b][k], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The second half, in the wave's own tile where its rectangle fits (raster_chunk_wave).
 template <int PPT, bool PW, int ZK>
 __device__ __forceinline__ void raster_view(const Proj &P, const Trans &T,
                                             uint64_t *__restrict__ fb, const float (&x)[PPT], const float (&y)[PPT],
@@ -1208,78 +1307,7 @@ __device__ __forceinline__ void raster_view(const Proj &P, const Trans &T,
         flush = MinFlush{t, p0, cur, four};
         return;
     }
-    // spread too far for the tile: groups of four points.  Consecutive points of a
-    // thread in one pixel send one atomic, and a group's early-out reads are sent before
-    // the atomics of the group before it, which they would have to wait for otherwise
-    // (one counter covers all memory operations of a wave, in order).
-    constexpr int G = 4, N = PPT / G;
-    uint32_t pix[2][G];
-    uint64_t key[2][G], cur[2][G];
-    bool live[2][G];
-    bool general = !PW;   // keys of points in any range
-    auto read = [&](int g) {
-        const int b = g & 1;
-        bool vis[G], run = false;
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            const int j = G * g + k;
-            float wx = v.fx[j], wy = v.fy[j];
-            own(wx), own(wy);
-            vis[k] = visible(P, wx, wy, v.behind, j);
-            pix[b][k] = __umul24((uint32_t)(int32_t)(vis[k] ? wy : 0.0f), t.width) +
-                        (uint32_t)(int32_t)(vis[k] ? wx : 0.0f);
-        }
-        if (!general) {
-            bool all = true;
-#pragma unroll
-            for (int k = 0; k < G; ++k) {
-                const int j = G * g + k;
-                live[b][k] = true;
-                key[b][k] = key_of(x[j], y[j], z[j], c[j], live[b][k]);
-                all = all & (live[b][k] | !vis[k]);
-                live[b][k] = live[b][k] & vis[k];
-            }
-            general = wave_any(!all);   // and so for the groups after it
-        }
-        if (general) {
-#pragma unroll
-            for (int k = 0; k < G; ++k) {
-                const int j = G * g + k;
-                live[b][k] = vis[k];
-                key[b][k] = key_any<PW, ZK>(P, T, x[j], y[j], z[j], c[j], live[b][k]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-#pragma unroll
-        for (int k = 1; k < G; ++k)
-            run = run | (live[b][k] & live[b][k - 1] & (pix[b][k] == pix[b][k - 1]));
-        if (wave_any(run)) {
-#pragma unroll
-            for (int k = 1; k < G; ++k) {
-                const bool same = live[b][k] & live[b][k - 1] & (pix[b][k] == pix[b][k - 1]);
-                const uint64_t lo = key[b][k] < key[b][k - 1] ? key[b][k] : key[b][k - 1];
-                key[b][k] = same ? lo : key[b][k];
-                live[b][k - 1] = live[b][k - 1] & !same;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < G; ++k)   // a point that takes no part reads pixel 0
-            cur[b][k] = early ? read_nearest(gfb + (live[b][k] ? pix[b][k] : 0u), false) : ~0ull;
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    read(0);
-#pragma unroll
-    for (int g = 0; g < N; ++g) {
-        const int b = g & 1;
-        if (g + 1 < N)
-            read(g + 1);
-#pragma unroll
-        for (int k = 0; k < G; ++k)
-            if (live[b][k] & (key[b][k] < cur[b][k]))
-                __hip_atomic_fetch_min(gfb + pix[b][k], key[b][k], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    raster_spread<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, early);
 }
 
 // Depth pass over one chunk with a private LDS tile per wave: like
@@ -1319,7 +1347,7 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
         raster_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, w_tile, words, flush, l2, early);
 }
 
-// raster_chunk_wave for the waves of one workgroup (at most kMaxWaves of them), with
+// raster_chunk_wave for the kGroupWaves waves of one workgroup, with
 // one tile in place of theirs where they cover the same pixels: the rectangle of all
 // takes at most half of theirs together and fits their tiles' words.  That is an
 // unordered cloud on few pixels, where every wave has an atomic for every pixel, and
@@ -1327,9 +1355,10 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
 // the more of them.  Frames of 700k points on spheres in random order, waves of 256
 // points alone / with this / waves of 1024 points: on 24 x 24 pixels 80.9 / 24.8 / 32.3
 // us, on 32 x 32 204 / 29.8 / 30.1, at 1280x720 from so far away that they cover about
-// 27 x 27 pixels 151 / 36.6 / 39.4; 2M points there 408 / 60.0 / 60.8.  The barrier costs
-// an ordered cloud nothing that shows (the terrain at 1920x1080: 1M points 23.7 / 24.0,
-// 4M 27.4 / 27.7, 7M 35.8 / 35.4).  s_tiles: `words` keys of each wave, one wave after
+// 27 x 27 pixels 151 / 36.6 / 39.4; 2M points there 408 / 60.0 / 60.8.  What the barrier
+// costs, depth passes at 640x480 without / with: spheres in random order 20k points 5.76 /
+// 6.18 us, 100k 7.64 / 8.04, 300k 20.4 / 19.8, 1M 58.3 / 58.7, terrain 6.42 / 5.98, 7.00 /
+// 7.44, 8.00 / 7.56, 7.32 / 7.20.  s_tiles: `words` keys of each wave, one wave after
 // the other.
 template <int PPT, bool PW, int ZK = 0>
 __device__ __forceinline__ void raster_chunk_group(const Proj &P, const Trans &T,
@@ -1344,38 +1373,41 @@ __device__ __forceinline__ void raster_chunk_group(const Proj &P, const Trans &T
     flush.t.area = 0;
     flush.cur = 0;
     const bool some = wave_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v);
-    const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const uint32_t wave = threadIdx.x >> 6;
+    const uint32_t limit = words * kGroupWaves;
     if ((threadIdx.x & 63u) == 0) {
         s_box[wave][0] = some ? v.box.x0 : ~0u;
         s_box[wave][1] = some ? v.box.y0 : ~0u;
         s_box[wave][2] = some ? v.box.x1 : 0u;
         s_box[wave][3] = some ? v.box.y1 : 0u;
     }
+    // a wave beyond the shared tile by itself: its atomics need not wait for the others
+    const bool alone = some && (v.box.x1 - v.box.x0 + 1) * (v.box.y1 - v.box.y0 + 1) > limit;
+    if (alone)
+        raster_spread<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, early);
     __syncthreads();
-    Box all{~0u, ~0u, 0u, 0u};
-    uint32_t sum = 0;   // of the waves' areas, those beyond 2^16 pixels counted as that
-    for (uint32_t w = 0; w < waves; ++w) {
-        const Box b{s_box[w][0], s_box[w][1], s_box[w][2], s_box[w][3]};
-        all = Box{min(all.x0, b.x0), min(all.y0, b.y0), max(all.x1, b.x1), max(all.y1, b.y1)};
-        const uint32_t area = (b.x1 - b.x0 + 1) * (b.y1 - b.y0 + 1);
-        sum += b.x0 > b.x1 ? 0u : min(area, 1u << 16);
-    }
-    all = Box{(uint32_t)__builtin_amdgcn_readfirstlane((int)all.x0),
-              (uint32_t)__builtin_amdgcn_readfirstlane((int)all.y0),
-              (uint32_t)__builtin_amdgcn_readfirstlane((int)all.x1),
-              (uint32_t)__builtin_amdgcn_readfirstlane((int)all.y1)};
+    // lane i takes wave i & 3's rectangle; two steps over the quad make them one
+    const uint32_t *w = s_box[threadIdx.x & (kGroupWaves - 1)];
+    uint32_t x0 = w[0], y0 = w[1], x1 = w[2], y1 = w[3];
+    // the sum of the areas, those beyond 2^16 pixels counted as that
+    uint32_t sum = x0 > x1 ? 0u : min((x1 - x0 + 1) * (y1 - y0 + 1), 1u << 16);
+    x0 = quad_min(x0), y0 = quad_min(y0), x1 = ~quad_min(~x1), y1 = ~quad_min(~y1);
+    sum = quad_sum(sum);
+    Box all;
+    all.x0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)x0);
+    all.y0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)y0);
+    all.x1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)x1);
+    all.y1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)y1);
     sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)sum);
-    if (sum == 0u)
-        return;
     const WaveTile t = wave_tile(P, all);
-    if (t.area > words * waves || 2 * t.area > sum) {
-        if (some)
+    if (t.area > limit || 2 * t.area > sum) {   // (nothing on screen: an area, no sum)
+        if (some && !alone)
             raster_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, s_tiles + wave * words, words, flush,
                                      false, early);
         return;
     }
     const uint32_t base = lds_addr(s_tiles);
-    const bool four = 4 * t.area <= words * waves;
+    const bool four = 4 * t.area <= limit;
     const uint32_t sh = four ? 5u : 3u;
     const uint32_t first = tile_first(t, base + (four ? 8 * (threadIdx.x & 3u) : 0u), sh);
     for (uint32_t i = threadIdx.x; i < t.area << (sh - 3); i += blockDim.x)
