@@ -1162,10 +1162,11 @@ __device__ __forceinline__ bool wave_view(const Proj &P, const Trans &T, uint64_
 }
 
 // The second half of a wave that spreads too far for its tile: groups of four points.
-// Consecutive points of a thread in one pixel send one atomic, and a group's early-out
-// reads are sent before the atomics of the group before it, which they would have to
-// wait for otherwise (one counter covers all memory operations of a wave, in order).
-template <int PPT, bool PW, int ZK>
+// Consecutive points of a thread in one pixel send one atomic, and (AHEAD) a group's
+// early-out reads are sent before the atomics of the group before it, which they would
+// have to wait for otherwise (one counter covers all memory operations of a wave, in
+// order).
+template <int PPT, bool PW, int ZK, bool AHEAD>
 __device__ __forceinline__ void raster_spread(const Proj &P, const Trans &T,
                                               uint64_t *__restrict__ fb, const float (&x)[PPT],
                                               const float (&y)[PPT], const float (&z)[PPT],
@@ -1230,11 +1231,14 @@ __device__ __forceinline__ void raster_spread(const Proj &P, const Trans &T,
             cur[b][k] = early ? read_nearest(gfb + (live[b][k] ? pix[b][k] : 0u), false) : ~0ull;
         __builtin_amdgcn_sched_barrier(0);
     };
-    read(0);
+    if (AHEAD)
+        read(0);
 #pragma unroll
     for (int g = 0; g < N; ++g) {
         const int b = g & 1;
-        if (g + 1 < N)
+        if (!AHEAD)
+            read(g);
+        else if (g + 1 < N)
             read(g + 1);
 #pragma unroll
         for (int k = 0; k < G; ++k)
@@ -1246,12 +1250,13 @@ __device__ __forceinline__ void raster_spread(const Proj &P, const Trans &T,
 }
 
 // The second half, in the wave's own tile where its rectangle fits (raster_chunk_wave).
-template <int PPT, bool PW, int ZK>
+template <int PPT, bool PW, int ZK, bool AHEAD>
 __device__ __forceinline__ void raster_view(const Proj &P, const Trans &T,
-                                            uint64_t *__restrict__ fb, const float (&x)[PPT], const float (&y)[PPT],
-                                            const float (&z)[PPT], const uint32_t (&c)[PPT],
-                                            const WaveView<PPT> &v, uint64_t *w_tile,
-                                            uint32_t words, MinFlush &flush, bool l2, bool early)
+                                            uint64_t *__restrict__ fb, const float (&x)[PPT],
+                                            const float (&y)[PPT], const float (&z)[PPT],
+                                            const uint32_t (&c)[PPT], const WaveView<PPT> &v,
+                                            uint64_t *w_tile, uint32_t words, MinFlush &flush,
+                                            bool l2, bool early)
 {
     gu64 *gfb = global_ptr(fb);
     const uint32_t lane = threadIdx.x & 63u;
@@ -1307,7 +1312,7 @@ __device__ __forceinline__ void raster_view(const Proj &P, const Trans &T,
         flush = MinFlush{t, p0, cur, four};
         return;
     }
-    raster_spread<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, early);
+    raster_spread<PPT, PW, ZK, AHEAD>(P, T, fb, x, y, z, c, v, early);
 }
 
 // Depth pass over one chunk with a private LDS tile per wave: like
@@ -1331,7 +1336,7 @@ __device__ __forceinline__ void raster_view(const Proj &P, const Trans &T,
 // neighbouring lanes hold neighbouring points, and LDS atomics of one address
 // follow each other one per cycle (a depth pass of 100M points over 8 views:
 // 1.99 ms with one copy, 45% of it in such conflicts, 1.50 ms with four).
-template <int PPT, bool PW, int ZK = 0>
+template <int PPT, bool PW, int ZK = 0, bool AHEAD = true>
 __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
                                                   uint64_t *__restrict__ fb,
                                                   const float (&x)[PPT], const float (&y)[PPT],
@@ -1344,7 +1349,7 @@ __device__ __forceinline__ void raster_chunk_wave(const Proj &P, const Trans &T,
     flush.t.area = 0;
     flush.cur = 0;
     if (wave_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v))
-        raster_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, w_tile, words, flush, l2, early);
+        raster_view<PPT, PW, ZK, AHEAD>(P, T, fb, x, y, z, c, v, w_tile, words, flush, l2, early);
 }
 
 // raster_chunk_wave for the kGroupWaves waves of one workgroup, with
@@ -1384,7 +1389,7 @@ __device__ __forceinline__ void raster_chunk_group(const Proj &P, const Trans &T
     // a wave beyond the shared tile by itself: its atomics need not wait for the others
     const bool alone = some && (v.box.x1 - v.box.x0 + 1) * (v.box.y1 - v.box.y0 + 1) > limit;
     if (alone)
-        raster_spread<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, early);
+        raster_spread<PPT, PW, ZK, true>(P, T, fb, x, y, z, c, v, early);
     __syncthreads();
     // lane i takes wave i & 3's rectangle; two steps over the quad make them one
     const uint32_t *w = s_box[threadIdx.x & (kGroupWaves - 1)];
@@ -1402,8 +1407,8 @@ __device__ __forceinline__ void raster_chunk_group(const Proj &P, const Trans &T
     const WaveTile t = wave_tile(P, all);
     if (t.area > limit || 2 * t.area > sum) {   // (nothing on screen: an area, no sum)
         if (some && !alone)
-            raster_view<PPT, PW, ZK>(P, T, fb, x, y, z, c, v, s_tiles + wave * words, words, flush,
-                                     false, early);
+            raster_view<PPT, PW, ZK, true>(P, T, fb, x, y, z, c, v, s_tiles + wave * words, words,
+                                           flush, false, early);
         return;
     }
     const uint32_t base = lds_addr(s_tiles);
