@@ -310,7 +310,7 @@ hipError_t launch_raster_min(const Pts &p, const Proj &P, uint64_t *fb, const Tu
     Range r("rz depth pass");
     if (p.n == 0)
         return hipSuccess;
-    // (the float encodings' kernel holds 141 registers at 16 points a thread, and
+    // (the float encodings' kernel holds 133 registers at 16 points a thread, and
     // the small shape serves them longer: 20M points 71.0 us against 72.9, 50M
     // 159 against 148)
     const int64_t small = P.zkind != 0 ? 3 * kSmallCloud : kSmallCloud;
